@@ -570,7 +570,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
       a.src_row = plan->dev.src_row;
       a.rope_cos = plan->dev.rope_cos;
       a.rope_sin = plan->dev.rope_sin;
-      MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->n_q, &lr, stream));
+      MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->q_off.data(), &lr, stream));
     } else {
       MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, &lr, stream));
     }
@@ -605,7 +605,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     return MPIC_OK;
   }
   if (c.dtype == MPIC_F32) {
-    MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->n_q, nullptr, stream));
+    MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->q_off.data(), nullptr, stream));
   } else {
     MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, nullptr, stream));
   }
@@ -659,23 +659,29 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
                                           : plan->ctx_off[b + 1] - plan->ctx_off[b]);
   // Splits: a workgroup fills a compute unit's LDS, so the keys are cut so that one round of
   // workgroups covers the chip (fewer when the batch alone supplies that many); each split
-  // is a multiple of 128 keys.
+  // is a whole number of key blocks for every wavefront of a workgroup (128 keys; fp32: 256).
   int32_t n_splits = 1, keys_per_split = std::max(max_ctx, 1);
-  if (c.dtype == MPIC_BF16 && max_ctx > 0) {
+  if (max_ctx > 0) {
     constexpr int64_t kTargetWorkgroups = 256;  // one round over the compute units
     const int64_t lanes = static_cast<int64_t>(plan->n_requests) * c.n_kv_heads * ((ctx->group + 31) / 32);
     const int64_t want = std::max<int64_t>(1, kTargetWorkgroups / lanes);
     int64_t kps = (max_ctx + want - 1) / want;
-    kps = (kps + mpic::kDecodeBlockKeys - 1) / mpic::kDecodeBlockKeys * mpic::kDecodeBlockKeys;
+    const int64_t unit = c.dtype == MPIC_F32 ? mpic::kDecodeBlockKeysF32 : mpic::kDecodeBlockKeys;
+    kps = (kps + unit - 1) / unit * unit;
     keys_per_split = static_cast<int32_t>(kps);
     n_splits = static_cast<int32_t>((max_ctx + kps - 1) / kps);  // <= 256, the merge kernel holds up to 1024 weights
   }
   const size_t rows = static_cast<size_t>(plan->n_requests) * c.n_q_heads;
-  const size_t need = rows * n_splits * (c.head_dim + 1) * sizeof(float);
+  size_t need = rows * n_splits * (c.head_dim + 1) * sizeof(float);
   float* ws = nullptr;
   if (static_scratch) {
     size_t have = 0;
     MPIC_HIP(ctx, mpic::decode_static_scratch(&ws, &have));
+    if (need > have && c.dtype == MPIC_F32) {  // fp32 also runs unsplit: fits whenever a row's partial does
+      n_splits = 1;
+      keys_per_split = max_ctx;
+      need = rows * (c.head_dim + 1) * sizeof(float);
+    }
     if (need > have)
       return fail(ctx, MPIC_ERR_UNSUPPORTED, "decode_attn_static: the partial results of this batch (" + std::to_string(need) +
                                              " bytes) exceed the static scratch array (" + std::to_string(have) + " bytes)");

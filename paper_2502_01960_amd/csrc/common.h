@@ -285,6 +285,7 @@ hipError_t launch_attn_bf16(const AttnArgs& a, const AssembleArgs* next, const A
 
 // Keys of a decode split are a multiple of this (four wavefronts x 32-key blocks).
 constexpr int kDecodeBlockKeys = 128;
+constexpr int kDecodeBlockKeysF32 = 256;  // (eight wavefronts)
 struct DecodeArgs {
   const int32_t* ctx_off;
   const int32_t* dst_slot;
@@ -316,8 +317,9 @@ hipError_t launch_decode(int dtype, const DecodeArgs& a, const LazyRefs* lazy, h
 // Device address and size of the file-scope scratch array of the decode kernels on the
 // current GPU (looked up once per device; allocates nothing).
 hipError_t decode_static_scratch(float** ptr, size_t* bytes);
-// `lazy` non-null (lazy_rope contexts): stored keys are turned to their position as they are read.
-hipError_t launch_attn_f32(const AttnArgs& a, int64_t n_q, const LazyRefs* lazy, hipStream_t stream);
+// q_off: host copy of a.q_off.  `lazy` non-null (lazy_rope contexts): stored keys are turned to their
+// position as they are read.
+hipError_t launch_attn_f32(AttnArgs a, const int32_t* q_off, const LazyRefs* lazy, hipStream_t stream);
 
 
 // Can the attention launch of this plan carry the linking of the next layer (device-resident

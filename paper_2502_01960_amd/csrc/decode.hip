@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "f32_tile.h"
 #include "wave_ops.h"
 
 namespace mpic {
@@ -470,103 +471,70 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
   if (a.lse && d == 0) a.lse[row] = m == -INFINITY ? -INFINITY : m + logf(z);
 }
 
-// fp32 path: one wavefront per (request, query head), lanes stride over the keys, two
-// passes (maximum, then weighted sum); writes its result as the only split of the row.
-// kLazy (lazy_rope contexts): stored keys are turned to their position as they are read, in
-// fp32, inside the dot product (see the fp32 prefill kernel); refs.by_ref: stored rows are read
-// in their caches.
+// fp32 path: the query heads of a kv group are the columns of one fp32 tile (f32_tile.h), a
+// workgroup owns one split of the keys.  kLazy (lazy_rope contexts): stored keys are turned to
+// their position as they are read, in fp32; refs.by_ref: stored rows are read in their caches.
 template <int kD, bool kLazy>
-__global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a, LazyRefs refs) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (row >= static_cast<int64_t>(a.n_requests) * a.n_q_heads) return;
-  const int b = static_cast<int>(row / a.n_q_heads);
-  const int h = static_cast<int>(row % a.n_q_heads);
-  const int g = h / (a.n_q_heads / a.n_kv_heads);
+__global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(DecodeArgs a, LazyRefs refs) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int lane = threadIdx.x & 63, col = lane & 31, hi = lane >> 5;
+  const int group = a.n_q_heads / a.n_kv_heads;
+  const int col_blocks = (group + f32tile::kCols - 1) / f32tile::kCols;
+  const int split = blockIdx.x % a.n_splits;
+  const int g = blockIdx.y / col_blocks;
+  const int h0 = g * group + blockIdx.y % col_blocks * f32tile::kCols;
+  const int n_cols = min(f32tile::kCols, (g + 1) * group - h0);
+  const int b = blockIdx.x / a.n_splits;
   const int n_ctx = a.ctx_off[b + 1] - a.ctx_off[b];
-  if (n_ctx == 0) return;  // the merge kernel sees no split for this row
-  const int32_t* slot_of = a.dst_slot + a.ctx_off[b];
-  const int64_t row_elems = static_cast<int64_t>(a.n_kv_heads) * kD;
-  const float* K = static_cast<const float*>(a.k_ctx) + g * kD;
-  const float* V = static_cast<const float*>(a.v_ctx) + g * kD;
-  float q[kD];
-  const float* qp = static_cast<const float*>(a.q) + row * kD;
-#pragma unroll
-  for (int d = 0; d < kD; d += 4) {
-    const float4 t = *reinterpret_cast<const float4*>(qp + d);
-    q[d] = t.x; q[d + 1] = t.y; q[d + 2] = t.z; q[d + 3] = t.w;
+  const int key0 = split * a.keys_per_split;
+  if (key0 >= n_ctx) return;  // this request has fewer splits
+  const int key1 = min(n_ctx, key0 + a.keys_per_split);
+  float q[kD / 2];
+  const int64_t row0 = static_cast<int64_t>(b) * a.n_q_heads + h0;
+  f32tile::load_query<kD>(static_cast<const float*>(a.q) + (row0 + min(col, n_cols - 1)) * kD, hi, q);
+  f32tile::Rows src{};
+  src.off16 = a.kv_off16 + a.ctx_off[b];
+  src.k = static_cast<const char*>(a.k_ctx) + static_cast<int64_t>(g) * kD * 4;
+  src.v = static_cast<const char*>(a.v_ctx) + static_cast<int64_t>(g) * kD * 4;
+  if constexpr (kLazy) {
+    src.inst = a.src_inst + a.ctx_off[b];
+    src.row = a.src_row + a.ctx_off[b];
+    src.rope_cos = a.rope_cos;
+    src.rope_sin = a.rope_sin;
+    src.refs = &refs;
+    src.head_bytes = static_cast<int64_t>(g) * kD * 4;
+    src.row_bytes = static_cast<int64_t>(a.n_kv_heads) * kD * 4;
+    src.interleaved = a.interleaved;
   }
-  const int32_t* inst_of = kLazy ? a.src_inst + a.ctx_off[b] : nullptr;
-  const int32_t* row_of = kLazy ? a.src_row + a.ctx_off[b] : nullptr;
-  auto row_ptr = [&](int j, const float* ctx_base, const void* const* tab) {
-    if constexpr (kLazy) {
-      const int inst = inst_of[j];
-      if (inst >= 0 && refs.by_ref)
-        return static_cast<const float*>(tab[inst]) + g * kD + static_cast<int64_t>(row_of[j]) * row_elems;
-    }
-    return ctx_base + static_cast<int64_t>(slot_of[j]) * row_elems;
-  };
-  auto logit = [&](int j) {
-    const float* kp = row_ptr(j, K, refs.k);
-    if constexpr (kLazy) {
-      const int inst = inst_of[j];
-      if (inst >= 0) {
-        const float* ct = a.rope_cos + static_cast<int64_t>(inst) * (kD / 2);
-        const float* st = a.rope_sin + static_cast<int64_t>(inst) * (kD / 2);
-        float acc = 0.f;
-        for (int i = 0; i < kD / 2; ++i) {
-          const int ix = a.interleaved ? 2 * i : i, iy = a.interleaved ? 2 * i + 1 : i + kD / 2;
-          const float x = kp[ix], y = kp[iy], c = ct[i], s = st[i];
-          acc = fmaf(q[ix], x * c - y * s, acc);
-          acc = fmaf(q[iy], x * s + y * c, acc);
-        }
-        return acc * a.scale;
-      }
-    }
-    float acc = 0.f;
+  f32tile::attend<kD, kLazy>(src, q, key1 - 1, key0, key1, a.scale, lds,
+                             [&](int c, int d0, const float(&o)[f32tile::Geo<kD>::kPerThread], float m, float l) {
+    if (c >= n_cols) return;
+    const int64_t part = (row0 + c) * a.n_splits + split;
+    const float inv = 1.f / l;
+    float* po = a.ws_o + part * kD + d0;
 #pragma unroll
-    for (int d = 0; d < kD; d += 4) {
-      const float4 t = *reinterpret_cast<const float4*>(kp + d);
-      acc = fmaf(q[d], t.x, acc);
-      acc = fmaf(q[d + 1], t.y, acc);
-      acc = fmaf(q[d + 2], t.z, acc);
-      acc = fmaf(q[d + 3], t.w, acc);
-    }
-    return acc * a.scale;
-  };
-  float m = -INFINITY;
-  for (int j = lane; j < n_ctx; j += 64) m = fmaxf(m, logit(j));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  float o[kD];
-#pragma unroll
-  for (int d = 0; d < kD; ++d) o[d] = 0.f;
-  float z = 0.f;
-  for (int j = lane; j < n_ctx; j += 64) {
-    const float w = expf(logit(j) - m);
-    z += w;
-    const float* vp = row_ptr(j, V, refs.v);
-#pragma unroll
-    for (int d = 0; d < kD; d += 4) {
-      const float4 t = *reinterpret_cast<const float4*>(vp + d);
-      o[d] = fmaf(w, t.x, o[d]);
-      o[d + 1] = fmaf(w, t.y, o[d + 1]);
-      o[d + 2] = fmaf(w, t.z, o[d + 2]);
-      o[d + 3] = fmaf(w, t.w, o[d + 3]);
-    }
+    for (int i = 0; i < f32tile::Geo<kD>::kPerThread; i += 4)
+      *reinterpret_cast<f32x4*>(po + i) = f32x4{o[i], o[i + 1], o[i + 2], o[i + 3]} * inv;
+    if (d0 == 0) a.ws_lse[part] = m * a.scale + logf(l);
+  });
+}
+
+template <int kD, bool kLazy>
+hipError_t launch_f32(const DecodeArgs& a, const LazyRefs& refs, int dev, hipStream_t stream) {
+  if (a.max_ctx > 0) {
+    constexpr int kLds = f32tile::Geo<kD>::kLdsBytes;
+    static LdsOptIn opt_in;
+    const hipError_t e = opt_in.ensure(dev, [] {
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(decode_f32_kernel<kD, kLazy>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    });
+    if (e != hipSuccess) return e;
+    const int group = a.n_q_heads / a.n_kv_heads;
+    const dim3 grid(static_cast<unsigned>(a.n_splits) * a.n_requests, a.n_kv_heads * ((group + f32tile::kCols - 1) / f32tile::kCols));
+    hipLaunchKernelGGL((decode_f32_kernel<kD, kLazy>), grid, dim3(f32tile::kThreads), kLds, stream, a, refs);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    z += __shfl_xor(z, off);
-#pragma unroll
-    for (int d = 0; d < kD; ++d) o[d] += __shfl_xor(o[d], off);
-  }
-  const float inv = 1.f / z;
-  float* po = a.ws_o + row * a.n_splits * kD;  // split 0 of this row
-#pragma unroll
-  for (int d = 0; d < kD; ++d)
-    if (lane == (d & 63)) po[d] = o[d] * inv;
-  if (lane == 0) a.ws_lse[row * a.n_splits] = m + logf(z);
+  const unsigned rows = static_cast<unsigned>(a.n_requests) * a.n_q_heads;
+  hipLaunchKernelGGL((decode_merge_kernel<float, kD>), dim3(rows), dim3(kD), 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -601,28 +569,15 @@ hipError_t decode_static_scratch(float** ptr, size_t* bytes) {
 hipError_t launch_decode(int dtype, const DecodeArgs& a, const LazyRefs* lazy, hipStream_t stream) {
   const int64_t rows = static_cast<int64_t>(a.n_requests) * a.n_q_heads;
   if (rows <= 0) return hipSuccess;
-  if (dtype == MPIC_F32) {
-    const dim3 grid(static_cast<unsigned>((rows + 3) / 4)), block(256);
-    const LazyRefs refs = lazy ? *lazy : LazyRefs{};
-    if (a.head_dim == 64) {
-      if (lazy)
-        hipLaunchKernelGGL((decode_f32_kernel<64, true>), grid, block, 0, stream, a, refs);
-      else
-        hipLaunchKernelGGL((decode_f32_kernel<64, false>), grid, block, 0, stream, a, refs);
-      hipLaunchKernelGGL((decode_merge_kernel<float, 64>), dim3(static_cast<unsigned>(rows)), dim3(64), 0, stream, a);
-    } else {
-      if (lazy)
-        hipLaunchKernelGGL((decode_f32_kernel<128, true>), grid, block, 0, stream, a, refs);
-      else
-        hipLaunchKernelGGL((decode_f32_kernel<128, false>), grid, block, 0, stream, a, refs);
-      hipLaunchKernelGGL((decode_merge_kernel<float, 128>), dim3(static_cast<unsigned>(rows)), dim3(128), 0, stream, a);
-    }
-    return hipGetLastError();
-  }
-  static LdsOptIn opt_in;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
+  if (dtype == MPIC_F32) {
+    if (a.head_dim == 64)
+      return lazy ? launch_f32<64, true>(a, *lazy, dev, stream) : launch_f32<64, false>(a, LazyRefs{}, dev, stream);
+    return lazy ? launch_f32<128, true>(a, *lazy, dev, stream) : launch_f32<128, false>(a, LazyRefs{}, dev, stream);
+  }
+  static LdsOptIn opt_in;
   e = opt_in.ensure(dev, [] {
     const hipError_t e0 = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_bf16_kernel<NoLazy>),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);

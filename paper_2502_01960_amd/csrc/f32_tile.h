@@ -1,0 +1,277 @@
+// One tile of fp32 attention on the matrix cores, shared by the fp32 prefill and decode kernels.
+//
+// App. A in plain fp32: 32 queries of one (request, kv head) attend to a range of positions of
+// the request.  Bound by the fp32 matrix rate (v_mfma_f32_32x32x2_f32, 256 flop per cycle and
+// compute unit) for prefill rows and by the stream of rows for decode rows.
+//
+// Split.  The eight wavefronts of a workgroup take the 32-key blocks of the range in turn, each
+// with its own running softmax, and merge through LDS at the end: a small request (one block per
+// wavefront) then takes the time of one block instead of that of the whole range, and nothing
+// inside the loop waits for another wavefront.
+//
+// Both products are computed transposed (a query is a lane column, softmax statistics are per-lane
+// scalars), with the lane layout A[i][k]: lane i + 32 k, B[k][j]: lane j + 32 k, C[i][j]: lane
+// j + 32 ((i / 4) % 2), register (i / 8) * 4 + i % 4:
+//   S^T[key][query] = K . Q^T   the two halves of a wavefront contract 16-byte chunks of a row in
+//                               turn, so a lane's operand is a 16-byte LDS read of its key's row.
+//                               Key rows are staged by direct global->LDS loads; chunk c of row i
+//                               lies at chunk c ^ (i & 15), which makes the reads conflict-free.
+//   O^T[d][query] = V^T . P^T   step r contracts keys (r/4)*8 + r%4 and +4, which is where register
+//                               r of S^T already lies; row index i of block db is coordinate
+//                               (D/32) i + db, so a lane's operands of all blocks are one vector
+//                               load of a value row -- straight from memory, without LDS.
+// The value rows of a block arrive while its keys are multiplied, the keys of the next block while
+// this one is normalised and multiplied with the values.
+#pragma once
+
+#include "common.h"
+#include "wave_ops.h"
+
+namespace mpic {
+namespace f32tile {
+
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * 64;
+constexpr int kKeys = 32;  // keys per block
+constexpr int kCols = 32;  // queries per tile
+
+template <int D>
+struct Geo {
+  static constexpr int kChunks = D / 4;               // 16-byte chunks of a row
+  static constexpr int kArea = kKeys * D * 4;         // staged key block of one wavefront
+  static constexpr int kLoads = kArea / 1024;         // direct loads per block
+  static constexpr int kBlocks = D / 32;              // 32-row blocks of O^T
+  static constexpr int kPerThread = D / (kThreads / kCols);  // coordinates a thread merges
+  static constexpr int kLdsBytes = kWaves * kArea + 2 * kWaves * kCols * 4;
+  static_assert(kCols * D * 4 == kArea, "a wavefront's partial result takes the place of its key block");
+};
+
+// Where the rows of one (request, kv head) are: every position in the context buffers, or (kLazy)
+// stored keys still without their shift, possibly in their caches.
+struct Rows {
+  const uint32_t* off16;  // context row offsets of the request's positions, 16-byte units
+  const char* k;          // context base + this head's offset inside a row
+  const char* v;
+  // lazy_rope contexts
+  const int32_t* inst;    // chunk instance of every position, -1 = fresh row
+  const int32_t* row;     // row inside that instance's cache
+  const float* rope_cos;
+  const float* rope_sin;
+  const LazyRefs* refs;   // by_ref: stored rows are read at refs->k / refs->v
+  int64_t row_bytes;
+  int64_t head_bytes;
+  int interleaved;
+};
+
+__device__ inline const char* from_lane(const char* p, int lane) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __shfl(static_cast<uint32_t>(u), lane), hi = __shfl(static_cast<uint32_t>(u >> 32), lane);
+  return reinterpret_cast<const char*>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+// The value again, in a form whose derived addresses the compiler does not keep across the loop
+// (it would hold some 60 registers of them, and spill).
+__device__ inline int here(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// q: this lane's query, q[4 j + e] = coordinate 4 (2 j + lane / 32) + e of column lane % 32.
+// my_pos: last position the column sees, key0 .. key1 - 1: the range.  emit(column, first coordinate,
+// values, reference maximum of the raw logits, denominator) is called once per thread and column.
+template <int D, bool kLazy, typename Emit>
+__device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2], int my_pos, int key0, int key1, float scale,
+                                       char* lds, Emit&& emit) {
+  using G = Geo<D>;
+  typedef float vrow __attribute__((ext_vector_type(G::kBlocks)));
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, col = lane & 31, hi = lane >> 5;
+  char* area = lds + wave * G::kArea;
+  const uint32_t area_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, area)));
+  const float c = scale * 1.4426950408889634f;
+  const int lo_pos = wave_min_i32(my_pos);
+
+  // addresses of the key and value row that lane `lane % 32` stands for, and its rotary table row
+  const char* kp = nullptr;
+  const char* vp = nullptr;
+  int inst = -1;
+  auto locate = [&](int j0) __attribute__((always_inline)) {
+    const int j = min(j0 + col, key1 - 1);  // past the range: its last row again (masked)
+    const int64_t off = static_cast<int64_t>(src.off16[j]) << 4;
+    kp = src.k + off;
+    vp = src.v + off;
+    if constexpr (kLazy) {
+      inst = src.inst[j];
+      if (inst >= 0 && src.refs->by_ref) {
+        const int64_t at = src.row[j] * src.row_bytes + src.head_bytes;
+        kp = static_cast<const char*>(src.refs->k[inst]) + at;
+        vp = static_cast<const char*>(src.refs->v[inst]) + at;
+      }
+    }
+  };
+  auto stage_keys = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < G::kLoads; ++p) {
+      const int ln = here(lane);
+      const int r = (ln + 64 * p) / G::kChunks;
+      const int ch = (ln % G::kChunks) ^ (r & 15);
+      load_to_lds_16B(from_lane(kp, r) + ch * 16, area_addr + p * 1024);
+      if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // few addresses in registers at a time
+    }
+  };
+
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 acc_o[G::kBlocks];
+#pragma unroll
+  for (int i = 0; i < G::kBlocks; ++i) acc_o[i] = f32x16{0};
+
+  const int n_blk = (key1 - key0 + kKeys - 1) / kKeys;
+  MPIC_WAIT_VMCNT(0);  // ordinary loads first: from here on the counter is managed by hand
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave < n_blk) {
+    locate(key0 + wave * kKeys);
+    stage_keys();
+  }
+  for (int t = wave; t < n_blk; t += kWaves) {
+    const int j0 = key0 + t * kKeys;
+    MPIC_WAIT_VMCNT(0);  // this block's keys have landed
+    asm volatile("" ::: "memory");
+    vrow v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      v[r] = *reinterpret_cast<const vrow*>(from_lane(vp, (r >> 2) * 8 + here(hi) * 4 + (r & 3)) + col * (G::kBlocks * 4));
+      if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kLazy) {
+      // stored keys are turned to their position where they lie, a row per lane and half the chunks per half
+      if (inst >= 0) {
+        const float* ct = src.rope_cos + static_cast<int64_t>(inst) * (D / 2);
+        const float* st = src.rope_sin + static_cast<int64_t>(inst) * (D / 2);
+        auto chunk = [&](int ch) { return reinterpret_cast<f32x4*>(area + col * (D * 4) + ((ch ^ (col & 15)) << 4)); };
+        if (src.interleaved) {
+          for (int ch = hi; ch < G::kChunks; ch += 2) {
+            const f32x4 x = *chunk(ch);
+            const float c0 = ct[2 * ch], s0 = st[2 * ch], c1 = ct[2 * ch + 1], s1 = st[2 * ch + 1];
+            *chunk(ch) = f32x4{x[0] * c0 - x[1] * s0, x[0] * s0 + x[1] * c0, x[2] * c1 - x[3] * s1, x[2] * s1 + x[3] * c1};
+          }
+        } else {
+          for (int ch = hi; ch < G::kChunks / 2; ch += 2) {
+            const f32x4 x = *chunk(ch), y = *chunk(ch + G::kChunks / 2);
+            const f32x4 cc = *reinterpret_cast<const f32x4*>(ct + 4 * ch), ss = *reinterpret_cast<const f32x4*>(st + 4 * ch);
+            *chunk(ch) = x * cc - y * ss;
+            *chunk(ch + G::kChunks / 2) = x * ss + y * cc;
+          }
+        }
+      }
+      asm volatile("" ::: "memory");
+    }
+    f32x16 s = f32x16{0};
+    // (key operands are read two steps ahead; the scheduling barriers keep the compiler from reading
+    // all of them first, which costs 64 registers and spills)
+    auto key_chunk = [&](int j) __attribute__((always_inline)) {
+      return *reinterpret_cast<const f32x4*>(area + here(col) * (D * 4) + (((2 * j + hi) ^ (here(col) & 15)) << 4));
+    };
+    f32x4 kf[2] = {key_chunk(0), key_chunk(1)};
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < G::kChunks / 2; ++j) {
+      const f32x4 k = kf[j & 1];
+      if (j + 2 < G::kChunks / 2) kf[j & 1] = key_chunk(j + 2);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[4 * j + e], s, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the values have arrived by now; settled before the next keys go out, so that the compiler's
+    // waits for them never count those
+#pragma unroll
+    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(v[r]));
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // every LDS read of this block is done (lgkmcnt 0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + kWaves < n_blk) {
+      locate(j0 + kWaves * kKeys);
+      MPIC_WAIT_VMCNT(0);
+      stage_keys();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (j0 + kKeys - 1 > lo_pos || j0 + kKeys > key1) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int j = j0 + (r >> 2) * 8 + hi * 4 + (r & 3);
+        s[r] = j <= my_pos && j < key1 ? s[r] : -INFINITY;
+      }
+    }
+    float m_blk = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) m_blk = fmaxf(m_blk, s[r]);
+    const float m_new = fmaxf(m_run, max_across_halves(m_blk));
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet: every weight below is exp2(-inf)
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_ref) * c);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < G::kBlocks; ++db) acc_o[db] *= alpha;
+      m_run = m_new;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f((s[r] - m_ref) * c);
+      l_run += s[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int db = 0; db < G::kBlocks; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[r][db], s[r], acc_o[db], 0, 0, 0);
+  }
+
+  // ---- merge the wavefronts: partial results as [wave][coordinate][column] ----
+  const float l_wave = sum_across_halves(l_run);
+  __syncthreads();
+  float* part = reinterpret_cast<float*>(lds);
+  float* m_of = part + kWaves * D * kCols;
+  float* l_of = m_of + kWaves * kCols;
+#pragma unroll
+  for (int db = 0; db < G::kBlocks; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = (r >> 2) * 8 + hi * 4 + (r & 3);
+      part[(wave * D + G::kBlocks * i + db) * kCols + col] = acc_o[db][r];
+    }
+  if (hi == 0) {
+    m_of[wave * kCols + col] = m_run;
+    l_of[wave * kCols + col] = l_wave;
+  }
+  __syncthreads();
+  const int mc = tid & 31, d0 = (tid >> 5) * G::kPerThread;
+  float m_tot = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) m_tot = fmaxf(m_tot, m_of[w * kCols + mc]);
+  float l_tot = 0.f;
+  float o[G::kPerThread];
+#pragma unroll
+  for (int i = 0; i < G::kPerThread; ++i) o[i] = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const float mw = m_of[w * kCols + mc];
+    const float wgt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - m_tot) * c);
+    l_tot = fmaf(wgt, l_of[w * kCols + mc], l_tot);
+#pragma unroll
+    for (int i = 0; i < G::kPerThread; ++i) o[i] = fmaf(wgt, part[(w * D + d0 + i) * kCols + mc], o[i]);
+  }
+  emit(mc, d0, o, m_tot, l_tot);
+}
+
+// This lane's share of a query row (see attend).
+template <int D>
+__device__ __forceinline__ void load_query(const float* row, int hi, float (&q)[D / 2]) {
+#pragma unroll
+  for (int j = 0; j < D / 8; ++j) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(row + 4 * (2 * j + hi));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[4 * j + e] = x[e];
+  }
+}
+
+}  // namespace f32tile
+}  // namespace mpic
