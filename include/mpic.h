@@ -138,11 +138,11 @@ enum {
   MPIC_PLAN_KEY_BLOCKS_96 = 18, /* every request cut into blocks of at most 32 / 64 / 96 keys  */
                              /* that never straddle a change of source; request after request, */
                              /* inside a request the blocks of fresh rows first, then those of */
-                             /* stored rows, each part in position order.  The decode kernel   */
-                             /* walks the first list, the two shapes of the attention kernel   */
-                             /* the others                                                     */
+                             /* stored rows, each part in position order.  (A description of   */
+                             /* the sources by position, built when asked for: the kernels     */
+                             /* gather the keys of a source further, across such runs)         */
   MPIC_PLAN_LAZY_TILES_64 = 19, /* lazy_rope contexts: [n_tiles][4] for every entry of         */
-  MPIC_PLAN_LAZY_TILES_96 = 20, /* MPIC_PLAN_ATTN_TILES the blocks it visits, as (f0, f1, s0,  */
+  MPIC_PLAN_LAZY_TILES_96 = 20, /* MPIC_PLAN_ATTN_TILES the blocks in its range, as (f0, f1, s0,  */
                              /* s1): fresh blocks f0..f1-1 and stored blocks s0..s1-1 of its   */
                              /* request, counted inside their parts                            */
   MPIC_PLAN_KEY_BLOCK_PARTS_32 = 21, /* lazy_rope contexts: [B][3] (first fresh block, first   */

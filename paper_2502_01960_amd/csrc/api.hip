@@ -87,11 +87,13 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p) {
       // slots past n_valid repeat the block's last row: what is staged there is masked, but it
       // must be a row that exists (in-place reads must stay inside their source)
       std::vector<uint32_t> vctx(blocks.size() * bn + kTablePad, 0u), vref(vctx.size(), 0u);
+      int32_t req = 0;
       for (size_t t = 0; t < blocks.size(); ++t) {
         const KeyBlock& kb = blocks[t];
-        const size_t ctx0 = p->ctx_off[kb.req];
+        while (t >= static_cast<size_t>(p->kblk_first[s][req + 1])) ++req;
+        const int32_t* keys = p->key_order.data() + p->ctx_off[req] + kb.rank0 + (kb.inst < 0 ? 0 : p->q_off[req + 1] - p->q_off[req]);
         for (size_t i = 0; i < bn; ++i) {
-          const size_t pos = ctx0 + kb.pos0 + std::min<size_t>(i, kb.n_valid - 1);
+          const size_t pos = keys[std::min<size_t>(i, kb.n_valid - 1)];
           vctx[t * bn + i] = off[pos];
           vref[t * bn + i] = kb.inst < 0 ? off[pos] : static_cast<uint32_t>(static_cast<uint64_t>(p->src_row[pos]) * units);
         }

@@ -177,12 +177,14 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
   const int local = wave * ROWS_PER_WAVE + col;
   const bool valid = local < tile.n_rows;
   const int flat = tile.row0 + (valid ? local : 0);
+  // lazy: keys of the fresh part this row sees (it is one of them); of the stored part it sees the rest
+  const int my_fresh = valid ? flat / group + 1 : 0x1fffffff;
   const int64_t fresh_row = a.q_off[b] + flat / group;
   const int head = g * group + flat % group;
   // Last key of this tile (or piece) the row may see.  Padding columns see every key; a row
   // below key0 (negative here) sees none of this piece; a row beyond the end of a piece sees the
   // piece up to its last key (blocks need not end where pieces do).
-  // (lazy: positions stay absolute, the blocks carry theirs; a piece owns whole blocks)
+  // (lazy: positions stay absolute; a piece owns whole blocks)
   const int my_pos = kLazy ? (valid ? a.q_pos[fresh_row] : 0x3fffffff)
                            : min(valid ? a.q_pos[fresh_row] - key0 : 0x7fffffff, n_keys - 1);
   const int n_iter = kLazy ? nf + ns : (n_keys + BN - 1) / BN;
@@ -195,11 +197,13 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
       d.pos0 = raw[0];
       d.n_valid = raw[1];
       d.inst = raw[2];
+      d.rank0 = raw[3];
     }
     return d;
   };
   // does the row see any key of this tile (or piece)?
   // first position of the tile (or piece): the smaller of its first fresh and first stored block's
+  // (a row may see none of the fresh blocks of a piece and still see its stored ones)
   const int piece_pos0 = kLazy ? min(desc_of(0).pos0, desc_of(nf < n_iter ? nf : 0).pos0) : 0;
   auto sees = [&]() { return my_pos >= piece_pos0; };
   const __bf16* qp = static_cast<const __bf16*>(a.q) + (fresh_row * a.n_q_heads + head) * D;
@@ -328,6 +332,8 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
 
   const int wave_hi_pos = wave_max_i32(valid ? my_pos : -1);  // negative: idle wave
   const int wave_lo_pos = wave_min_i32(valid ? my_pos : 0x7fffffff);
+  const int wave_lo_fresh = kLazy ? wave_min_i32(my_fresh) : 0;  // (both counts grow with the position)
+  const int wave_lo_stored = kLazy ? wave_lo_pos + 1 - wave_lo_fresh : 0;
 
   const float scale_log2 = a.scale * 1.4426950408889634f;
   float m_run = -INFINITY;  // running reference maximum of the raw logits (scale > 0 keeps the order)
@@ -520,10 +526,11 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
       return;
     }
     if constexpr (kLazy) {
-      // keys of the block sit at positions pos0 .. pos0 + n_valid - 1; slots behind them are
-      // padding; masked on blocks with padding and on the diagonal blocks
-      if (kd.n_valid < BN || kd.pos0 + BN - 1 > wave_lo_pos) {
-        const int bound = min(my_pos - kd.pos0, kd.n_valid - 1) - hi * 4;  // last visible slot (may be negative)
+      // a row sees the first (rank - rank0) slots of the block; slots behind n_valid are padding;
+      // masked on blocks with padding and on those that some row of the wave sees in part
+      if (kd.n_valid < BN || kd.rank0 + BN > (kd.inst < 0 ? wave_lo_fresh : wave_lo_stored)) {
+        const int rank = kd.inst < 0 ? my_fresh : my_pos + 1 - my_fresh;
+        const int bound = min(rank - kd.rank0, kd.n_valid) - 1 - hi * 4;  // last visible slot (may be negative)
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -580,12 +587,14 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
         for (int v = 0; v < 16; ++v) m_blk = fmaxf(m_blk, acc_s[kb][v]);
       m_blk = max_across_halves(m_blk);
       const float m_new = fmaxf(m_run, m_blk);
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2);  // first block: 0
+      // first block: 0.  (lazy: a row may meet blocks it sees nothing of before its first one;
+      // they add nothing and leave it without a reference point)
+      const float alpha = kLazy && m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2);
       m_run = m_new;
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < 4; ++db) acc_o[db] *= alpha;
-      const float m_scaled = m_run * scale_log2;
+      const float m_scaled = kLazy && m_new == -INFINITY ? 0.f : m_run * scale_log2;
       l_blk = 0.f;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -32,17 +33,27 @@ struct AttnMerge {
 };
 static_assert(sizeof(AttnMerge) == 32, "merge item layout");
 
-// Contexts with lazy_rope: the keys of a request, cut into blocks that never straddle a change
-// of source (a chunk instance, or a run of fresh rows).  Inside a block all keys come from
-// consecutive rows of one source and lack the same position shift, so a kernel can turn the
-// query back once per block instead of turning every key forward (Sec. 4.1: the linker joins
-// caches and touches nothing else).  A block holds n_valid <= BN keys at positions pos0 ..
-// pos0 + n_valid - 1; the rest of its BN slots are padding that the kernels mask.
+// Contexts with lazy_rope: the keys of a request, gathered into blocks of one source each (a chunk
+// instance, or the fresh rows).  All keys of a block lack the same position shift, so a kernel can
+// turn the query back once per block instead of turning every key forward (Sec. 4.1: the linker
+// joins caches and touches nothing else).  The keys of a block need not be neighbours in the
+// request: the fresh rows follow each other without gaps, and so do the stored rows of an instance,
+// whatever lies between them, so that only the last block of a source has padding (slots n_valid ..
+// BN - 1, masked by the kernels).  Blocks that ended at every change of source were mostly padding
+// where the recompute set is named token by token: 48 tokens all over a chunk of 1024 leave runs of
+// 20 stored rows in blocks of 96 (scatter + attention of 2 such requests of 5K tokens: 925 -> 147 us).
+// Keys are in position order inside their part (fresh, stored), so what a query sees of a block is
+// its first rank - rank0 slots, rank = keys of that part at positions up to the query's own.
 struct KeyBlock {
   int32_t pos0;     // position (inside its request) of the block's first key
   int32_t n_valid;  // keys in the block, 1 .. BN
   int32_t inst;     // chunk instance that stores the keys (they lack its shift), -1 = fresh rows
-  int32_t req;      // owning request
+  int32_t rank0;    // keys of the request's part (fresh, stored) in front of the block
+};
+// A run of consecutive positions with one source, cut to at most BN keys: what mpic_plan_get
+// tells about the sources of a request (MPIC_PLAN_KEY_BLOCKS_*); no kernel reads it.
+struct KeyRun {
+  int32_t pos0, n_valid, inst, req;
 };
 static_assert(sizeof(KeyBlock) == 16, "key block layout");
 constexpr int kNumBlockSizes = 3;
@@ -134,12 +145,17 @@ struct mpic_plan {
   std::vector<float> rope_cos, rope_sin;
   // contexts with lazy_rope only: key blocks per block size, first block of every request,
   // attention tiles in block indices (empty for the decode block size)
+  std::vector<int32_t> key_order;  // [n_ctx] positions of every request (batch-flattened): its fresh ones, then its stored ones
   std::vector<mpic::KeyBlock> kblk[mpic::kNumBlockSizes];
   std::vector<int32_t> kblk_first[mpic::kNumBlockSizes];
   std::vector<int32_t> kblk_mid[mpic::kNumBlockSizes];    // [B] first stored block of every request (its fresh blocks come first)
   std::vector<int32_t> lazy_range[mpic::kNumBlockSizes];  // [n_tiles][4] fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
-  std::vector<int32_t> kblk_flat[mpic::kNumBlockSizes];   // the blocks as int32 quadruples, for mpic_plan_get
-  std::vector<int32_t> kblk_parts[mpic::kNumBlockSizes];  // [B][3] first fresh block, first stored block, end, for mpic_plan_get
+  // the sources by position, for mpic_plan_get only: built when first asked for
+  std::mutex runs_mu;
+  bool runs_built = false;
+  std::vector<int32_t> run_blocks[mpic::kNumBlockSizes];  // [n][4] KeyRun
+  std::vector<int32_t> run_parts[mpic::kNumBlockSizes];   // [B][3] first fresh block, first stored block, end
+  std::vector<int32_t> run_range[mpic::kNumBlockSizes];   // [n_tiles][4] blocks of every tile
   std::vector<int32_t> fresh_rot;            // contexts with fresh_pre_rope only
   std::vector<float> fresh_cos, fresh_sin;   // one row per distinct position id
   mpic::PlanDevice dev;
@@ -258,8 +274,8 @@ enum { kAblateLoads = 1,     // K/V blocks are staged only until every ring slot
        kAblateAddressesOnly = 64 };// the addresses of the direct loads are formed, the loads are not issued
 constexpr int kProbeOptionAblate = 1000;  // mpic_set_option of the probe library: value = mask of kAblate*
 // Contexts with lazy_rope: stored keys are never turned to their global position.  The kernel
-// walks the request's key blocks (KeyBlock: all keys of a block come from consecutive rows of
-// one source and lack the same shift) and turns its *queries* back by that shift whenever the
+// walks the request's key blocks (KeyBlock: all keys of a block come from one source and lack
+// the same shift) and turns its *queries* back by that shift whenever the
 // source changes, <Rot(-s) q, k> = <q, Rot(s) k>.  Each block is staged from the base address of
 // its source: the context buffers for fresh rows (and for stored rows that were copied there),
 // or the chunk's cache itself when the caches are linked by reference.

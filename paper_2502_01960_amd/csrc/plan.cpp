@@ -253,15 +253,89 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   while (!p.tiles.empty() && p.tiles.back().n_rows == 0) p.tiles.pop_back();
 }
 
-// Key blocks of a lazy_rope plan (see KeyBlock).  A block ends where the source of the keys
-// changes (next chunk instance, or stored rows <-> fresh rows), where a tile that was cut
-// along the keys starts a new piece (so that a piece owns whole blocks), and after BN keys.
-// The list of a request holds its fresh blocks first and its stored blocks after them, each
-// part in position order: a kernel that walks a tile in list order changes the shift its
-// queries are turned back by once per chunk instance instead of twice (softmax does not care
-// about the order of the keys; the mask goes by the positions the blocks carry).  The tiles are
-// restated as two ranges of block indices, once per kernel shape.
+// Key blocks of a lazy_rope plan (see KeyBlock), as the kernels walk them.  The list of a request
+// holds its fresh blocks first and its stored blocks after them, each part in position order: a
+// kernel that walks a tile in list order changes the shift its queries are turned back by once per
+// chunk instance (softmax does not care about the order of the keys).  A tile visits the blocks
+// that start at or before its last row, a prefix of both parts; the pieces of a tile that was cut
+// along the keys share those blocks evenly, in list order.
 void build_key_blocks(mpic_plan& p) {
+  const int B = p.n_requests;
+  p.key_order.clear();
+  p.key_order.reserve(p.n_ctx);
+  for (int b = 0; b < B; ++b) {
+    for (int32_t r = p.q_off[b]; r < p.q_off[b + 1]; ++r) p.key_order.push_back(p.ctx_off[b] + p.q_pos[r]);
+    for (int32_t pos = p.ctx_off[b]; pos < p.ctx_off[b + 1]; ++pos)
+      if (p.src_inst[pos] >= 0) p.key_order.push_back(pos);
+  }
+  // the pieces of every cut tile: which one of how many, and where the tile ends
+  struct Piece {
+    int32_t index = 0, count = 1, n_keys = 0;
+  };
+  std::vector<Piece> pieces(p.n_parts);
+  for (const AttnMerge& m : p.merges)
+    for (int32_t i = 0; i < m.n_parts; ++i) {
+      pieces[m.first_part + i].index = i;
+      pieces[m.first_part + i].count = m.n_parts;
+    }
+  for (const AttnTile& t : p.tiles)
+    if (t.n_rows > 0 && t.part >= 0) pieces[t.part].n_keys = t.n_keys;
+  for (const AttnMerge& m : p.merges)  // (the last piece ends where the tile does)
+    for (int32_t i = 0; i + 1 < m.n_parts; ++i) pieces[m.first_part + i].n_keys = pieces[m.first_part + m.n_parts - 1].n_keys;
+
+  for (int s = 0; s < kNumBlockSizes; ++s) {
+    const int32_t bn = kBlockSizes[s];
+    auto& blocks = p.kblk[s];
+    auto& first = p.kblk_first[s];
+    auto& mid = p.kblk_mid[s];
+    blocks.clear();
+    first.assign(1, 0);
+    mid.clear();
+    for (int b = 0; b < B; ++b) {
+      const int32_t ctx0 = p.ctx_off[b], n = p.ctx_off[b + 1] - ctx0, n_fresh = p.q_off[b + 1] - p.q_off[b];
+      const int32_t* order = p.key_order.data() + ctx0;
+      for (int32_t i = 0; i < n_fresh; i += bn) blocks.push_back(KeyBlock{order[i] - ctx0, std::min(bn, n_fresh - i), -1, i});
+      mid.push_back(static_cast<int32_t>(blocks.size()));
+      for (int32_t i = n_fresh; i < n;) {
+        const int32_t inst = p.src_inst[order[i]];
+        int32_t end = i + 1;
+        while (end < n && end - i < bn && p.src_inst[order[end]] == inst) ++end;
+        blocks.push_back(KeyBlock{order[i] - ctx0, end - i, inst, i - n_fresh});
+        i = end;
+      }
+      first.push_back(static_cast<int32_t>(blocks.size()));
+    }
+    auto& ranges = p.lazy_range[s];
+    ranges.clear();
+    if (bn == 32) continue;  // the decode kernel splits its blocks at launch
+    ranges.reserve(p.tiles.size() * 4);
+    for (const AttnTile& t : p.tiles) {
+      if (t.n_rows <= 0) {
+        ranges.insert(ranges.end(), {0, 0, 0, 0});
+        continue;
+      }
+      const Piece pc = t.part >= 0 ? pieces[t.part] : Piece{0, 1, t.n_keys};
+      auto before_end = [&](int32_t lo, int32_t hi) {  // blocks of [lo, hi) that start below the tile's end
+        const KeyBlock* it = std::lower_bound(blocks.data() + lo, blocks.data() + hi, pc.n_keys,
+                                              [](const KeyBlock& k, int32_t v) { return k.pos0 < v; });
+        return static_cast<int32_t>(it - (blocks.data() + lo));
+      };
+      // no piece is empty: pieces own at least three 64-key blocks of positions on average, and a
+      // gathered block holds 96 keys at most.  Every row sees a key of the first piece, which starts
+      // with the request's first fresh row
+      const int32_t nf = before_end(first[t.req], mid[t.req]), ns = before_end(mid[t.req], first[t.req + 1]);
+      const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * pc.index / pc.count);
+      const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * (pc.index + 1) / pc.count);
+      ranges.insert(ranges.end(), {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf});
+    }
+  }
+}
+
+// What mpic_plan_get tells about the sources of a lazy_rope plan, by position (see KeyRun).  A run
+// ends where the source of the keys changes (next chunk instance, or stored rows <-> fresh rows),
+// where a tile that was cut along the keys starts a new piece, and after BN keys; the tiles are
+// restated as the runs inside their key range.
+void build_key_runs(mpic_plan& p) {
   const int B = p.n_requests;
   std::vector<std::vector<int32_t>> cuts(B);
   for (const AttnTile& t : p.tiles)
@@ -272,13 +346,9 @@ void build_key_blocks(mpic_plan& p) {
   }
   for (int s = 0; s < kNumBlockSizes; ++s) {
     const int32_t bn = kBlockSizes[s];
-    auto& blocks = p.kblk[s];
-    auto& first = p.kblk_first[s];
-    auto& mid = p.kblk_mid[s];
-    blocks.clear();
-    first.assign(1, 0);
-    mid.clear();
-    std::vector<KeyBlock> fresh, stored;
+    std::vector<KeyRun> runs, fresh, stored;
+    auto& parts = p.run_parts[s];
+    parts.clear();
     for (int b = 0; b < B; ++b) {
       const int32_t ctx0 = p.ctx_off[b], n = p.ctx_off[b + 1] - ctx0;
       fresh.clear();
@@ -290,36 +360,33 @@ void build_key_blocks(mpic_plan& p) {
         const int32_t inst = p.src_inst[ctx0 + pos];
         int32_t end = pos + 1;
         while (end < limit && p.src_inst[ctx0 + end] == inst) ++end;
-        for (int32_t q = pos; q < end; q += bn) (inst < 0 ? fresh : stored).push_back(KeyBlock{q, std::min(bn, end - q), inst, b});
+        for (int32_t q = pos; q < end; q += bn) (inst < 0 ? fresh : stored).push_back(KeyRun{q, std::min(bn, end - q), inst, b});
         pos = end;
       }
-      blocks.insert(blocks.end(), fresh.begin(), fresh.end());
-      mid.push_back(static_cast<int32_t>(blocks.size()));
-      blocks.insert(blocks.end(), stored.begin(), stored.end());
-      first.push_back(static_cast<int32_t>(blocks.size()));
+      const int32_t lo = static_cast<int32_t>(runs.size());
+      runs.insert(runs.end(), fresh.begin(), fresh.end());
+      const int32_t mid = static_cast<int32_t>(runs.size());
+      runs.insert(runs.end(), stored.begin(), stored.end());
+      parts.insert(parts.end(), {lo, mid, static_cast<int32_t>(runs.size())});
     }
-    p.kblk_flat[s].resize(blocks.size() * 4);
-    if (!blocks.empty()) std::memcpy(p.kblk_flat[s].data(), blocks.data(), blocks.size() * sizeof(KeyBlock));
-    p.lazy_range[s].clear();
-    if (bn == 32) continue;  // the decode kernel splits its blocks at launch
-    // blocks of [lo, hi) whose first position is below `pos` (the parts are in position order)
+    p.run_blocks[s].resize(runs.size() * 4);
+    if (!runs.empty()) std::memcpy(p.run_blocks[s].data(), runs.data(), runs.size() * sizeof(KeyRun));
+    auto& ranges = p.run_range[s];
+    ranges.clear();
+    if (bn == 32) continue;
     auto below = [&](int32_t lo, int32_t hi, int32_t pos) {
-      const KeyBlock* it = std::lower_bound(blocks.data() + lo, blocks.data() + hi, pos,
-                                            [](const KeyBlock& k, int32_t v) { return k.pos0 < v; });
-      return static_cast<int32_t>(it - (blocks.data() + lo));
+      const KeyRun* it = std::lower_bound(runs.data() + lo, runs.data() + hi, pos,
+                                          [](const KeyRun& k, int32_t v) { return k.pos0 < v; });
+      return static_cast<int32_t>(it - (runs.data() + lo));
     };
-    // per tile: fresh blocks [f0, f1) and stored blocks [s0, s1), counted inside their parts.  A
-    // piece starts at a forced block boundary, so every block with a first position in
-    // [first key, end key) belongs to it, and only those
-    p.lazy_range[s].reserve(p.tiles.size() * 4);
     for (const AttnTile& t : p.tiles) {
       if (t.n_rows <= 0) {
-        p.lazy_range[s].insert(p.lazy_range[s].end(), {0, 0, 0, 0});
+        ranges.insert(ranges.end(), {0, 0, 0, 0});
         continue;
       }
-      const int32_t f_lo = first[t.req], f_hi = mid[t.req], s_hi = first[t.req + 1];
-      p.lazy_range[s].insert(p.lazy_range[s].end(), {below(f_lo, f_hi, t.key0), below(f_lo, f_hi, t.n_keys),
-                                                      below(f_hi, s_hi, t.key0), below(f_hi, s_hi, t.n_keys)});
+      const int32_t* part = parts.data() + 3 * static_cast<size_t>(t.req);
+      ranges.insert(ranges.end(), {below(part[0], part[1], t.key0), below(part[0], part[1], t.n_keys),
+                                   below(part[1], part[2], t.key0), below(part[1], part[2], t.n_keys)});
     }
   }
 }
@@ -577,14 +644,7 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
       }
     if (ctx->cfg.fresh_pre_rope) mpic::build_fresh_rope(*p, ctx->cfg);
     mpic::build_tiles(*p, ctx->group, ctx->cfg.n_kv_heads);
-    if (ctx->cfg.lazy_rope) {
-      mpic::build_key_blocks(*p);
-      for (int s = 0; s < mpic::kNumBlockSizes; ++s) {
-        p->kblk_parts[s].clear();
-        for (int b = 0; b < n_requests; ++b)
-          p->kblk_parts[s].insert(p->kblk_parts[s].end(), {p->kblk_first[s][b], p->kblk_mid[s][b], p->kblk_first[s][b + 1]});
-      }
-    }
+    if (ctx->cfg.lazy_rope) mpic::build_key_blocks(*p);
     {
       auto clamp = [](int64_t x) { return static_cast<int32_t>(std::min<int64_t>(x, INT32_MAX)); };
       p->launch_est = {clamp(p->est_makespan_blocks), clamp(p->est_idle_blocks),
@@ -601,6 +661,16 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
 
 extern "C" int mpic_plan_get(const mpic_plan* plan, int32_t what, const int32_t** host_ptr, size_t* n) {
   if (!plan || !host_ptr || !n) return MPIC_ERR_INVALID;
+  if (what >= MPIC_PLAN_KEY_BLOCKS_32 && what <= MPIC_PLAN_KEY_BLOCK_PARTS_96 && plan->ctx->cfg.lazy_rope) {
+    mpic_plan* p = const_cast<mpic_plan*>(plan);
+    try {
+      std::lock_guard<std::mutex> lock(p->runs_mu);
+      if (!p->runs_built) mpic::build_key_runs(*p);
+      p->runs_built = true;
+    } catch (const std::bad_alloc&) {
+      return MPIC_ERR_OOM;
+    }
+  }
   const std::vector<int32_t>* v = nullptr;
   switch (what) {
     case MPIC_PLAN_CTX_OFF: v = &plan->ctx_off; break;
@@ -618,14 +688,14 @@ extern "C" int mpic_plan_get(const mpic_plan* plan, int32_t what, const int32_t*
     case MPIC_PLAN_INST_REQ: v = &plan->inst_req; break;
     case MPIC_PLAN_RUNS: v = &plan->runs; break;
     case MPIC_PLAN_LAUNCH_ESTIMATE: v = &plan->launch_est; break;
-    case MPIC_PLAN_KEY_BLOCKS_32: v = &plan->kblk_flat[0]; break;
-    case MPIC_PLAN_KEY_BLOCKS_64: v = &plan->kblk_flat[1]; break;
-    case MPIC_PLAN_KEY_BLOCKS_96: v = &plan->kblk_flat[2]; break;
-    case MPIC_PLAN_LAZY_TILES_64: v = &plan->lazy_range[1]; break;
-    case MPIC_PLAN_LAZY_TILES_96: v = &plan->lazy_range[2]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_32: v = &plan->kblk_parts[0]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_64: v = &plan->kblk_parts[1]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_96: v = &plan->kblk_parts[2]; break;
+    case MPIC_PLAN_KEY_BLOCKS_32: v = &plan->run_blocks[0]; break;
+    case MPIC_PLAN_KEY_BLOCKS_64: v = &plan->run_blocks[1]; break;
+    case MPIC_PLAN_KEY_BLOCKS_96: v = &plan->run_blocks[2]; break;
+    case MPIC_PLAN_LAZY_TILES_64: v = &plan->run_range[1]; break;
+    case MPIC_PLAN_LAZY_TILES_96: v = &plan->run_range[2]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_32: v = &plan->run_parts[0]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_64: v = &plan->run_parts[1]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_96: v = &plan->run_parts[2]; break;
     case MPIC_PLAN_ATTN_TILES:
       *host_ptr = reinterpret_cast<const int32_t*>(plan->tiles.data());
       *n = plan->tiles.size() * 8;

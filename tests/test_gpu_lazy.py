@@ -239,3 +239,18 @@ def test_lazy_layers_through_the_pipeline(tmp_path):
                     want = p.raw[s_][0][l][int(p.oplan["src_row"][g])]
                     assert torch.equal(k_log[g].cpu().view(torch.int16), want.view(torch.int16))
         p.close()
+
+
+@pytest.mark.parametrize("block_keys", [64, 96])
+def test_lazy_pieces_between_the_fresh_and_the_stored_part(block_keys):
+    """Key blocks gathered across runs, shared by the pieces of a cut tile in list order: a piece that
+    starts inside the fresh part and ends inside the stored one holds fresh blocks that its first rows
+    see nothing of, and stored blocks that they do see."""
+    rng = np.random.default_rng(11)
+    pick = lambda L, n: tuple(sorted(rng.choice(L, size=n, replace=False).tolist()))
+    reqs = [[("chunk", 0, 1500, pick(1500, 600)), ("text", 1)],
+            [("chunk", 1, 97, pick(97, 1)), ("chunk", 0, 1500, pick(1500, 385)), ("chunk", 1, 97, 97), ("text", 5)]]
+    p = _custom(reqs, 2, [1500, 97], 0)
+    p.block_keys = block_keys
+    _run_lazy(p)
+    assert (p.plan.get("attn_tiles")[:, 6] >= 0).any()
