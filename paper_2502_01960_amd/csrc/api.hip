@@ -562,6 +562,10 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   a.q_sin = plan->dev.fresh_sin;
   a.interleaved = c.rope_interleaved;
   a.ablate = ctx->attn_ablate;
+  int64_t n_tiles_f32 = 0;
+  if (c.dtype == MPIC_F32)
+    for (int b = 0; b < plan->n_requests; ++b)
+      n_tiles_f32 += ((plan->q_off[b + 1] - plan->q_off[b]) * static_cast<int64_t>(ctx->group) + mpic::kAttnTileRowsF32 - 1) / mpic::kAttnTileRowsF32;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   if (lazy) {
     mpic::LazyRefs lr;
@@ -572,7 +576,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
       a.src_row = plan->dev.src_row;
       a.rope_cos = plan->dev.rope_cos;
       a.rope_sin = plan->dev.rope_sin;
-      MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->q_off.data(), &lr, stream));
+      MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_tiles_f32, &lr, stream));
     } else {
       MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, &lr, stream));
     }
@@ -607,7 +611,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     return MPIC_OK;
   }
   if (c.dtype == MPIC_F32) {
-    MPIC_HIP(ctx, mpic::launch_attn_f32(a, plan->q_off.data(), nullptr, stream));
+    MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_tiles_f32, nullptr, stream));
   } else {
     MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, nullptr, stream));
   }

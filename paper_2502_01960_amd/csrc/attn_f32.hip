@@ -96,30 +96,30 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void attn_f32_kernel(AttnArgs
 }
 
 template <int D, bool kLazy>
-hipError_t launch(const AttnArgs& a, const LazyRefs& refs, int dev, hipStream_t stream) {
+hipError_t launch(const AttnArgs& a, int64_t n_tiles, const LazyRefs& refs, int dev, hipStream_t stream) {
   constexpr int kLds = f32tile::Geo<D>::kLdsBytes;
   static LdsOptIn opt_in;
   const hipError_t e = opt_in.ensure(dev, [] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_kernel<D, kLazy>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   });
   if (e != hipSuccess) return e;
-  const dim3 grid(static_cast<unsigned>(a.n_tiles) * a.n_kv_heads);
+  const dim3 grid(static_cast<unsigned>(n_tiles) * a.n_kv_heads);
   hipLaunchKernelGGL((attn_f32_kernel<D, kLazy>), grid, dim3(f32tile::kThreads), kLds, stream, a, refs);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_attn_f32(AttnArgs a, const int32_t* q_off, const LazyRefs* lazy, hipStream_t stream) {
-  const int group = a.n_q_heads / a.n_kv_heads;
-  a.n_tiles = 0;  // tiles of 32 flattened rows, per kv head
-  for (int b = 0; b < a.n_requests; ++b) a.n_tiles += ((q_off[b + 1] - q_off[b]) * group + f32tile::kCols - 1) / f32tile::kCols;
-  if (a.n_tiles <= 0) return hipSuccess;
+static_assert(f32tile::kCols == kAttnTileRowsF32, "tile size and kernel shape must agree");
+
+hipError_t launch_attn_f32(const AttnArgs& a, int64_t n_tiles, const LazyRefs* lazy, hipStream_t stream) {
+  if (n_tiles <= 0) return hipSuccess;
   int dev = 0;
   const hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  if (a.head_dim == 64) return lazy ? launch<64, true>(a, *lazy, dev, stream) : launch<64, false>(a, LazyRefs{}, dev, stream);
-  return lazy ? launch<128, true>(a, *lazy, dev, stream) : launch<128, false>(a, LazyRefs{}, dev, stream);
+  if (a.head_dim == 64)
+    return lazy ? launch<64, true>(a, n_tiles, *lazy, dev, stream) : launch<64, false>(a, n_tiles, LazyRefs{}, dev, stream);
+  return lazy ? launch<128, true>(a, n_tiles, *lazy, dev, stream) : launch<128, false>(a, n_tiles, LazyRefs{}, dev, stream);
 }
 
 }  // namespace mpic

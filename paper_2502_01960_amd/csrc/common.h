@@ -197,6 +197,7 @@ int attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q, int64_t n_fresh_
 
 // Rows of the attention tile handled by one workgroup of the bf16 kernel.
 constexpr int kAttnTileRows = 256;
+constexpr int kAttnTileRowsF32 = 32;  // the same of the fp32 kernel
 
 // ---- kernel launchers (each validates nothing: callers have done so) ----
 
@@ -333,9 +334,9 @@ hipError_t launch_decode(int dtype, const DecodeArgs& a, const LazyRefs* lazy, h
 // Device address and size of the file-scope scratch array of the decode kernels on the
 // current GPU (looked up once per device; allocates nothing).
 hipError_t decode_static_scratch(float** ptr, size_t* bytes);
-// q_off: host copy of a.q_off.  `lazy` non-null (lazy_rope contexts): stored keys are turned to their
-// position as they are read.
-hipError_t launch_attn_f32(AttnArgs a, const int32_t* q_off, const LazyRefs* lazy, hipStream_t stream);
+// n_tiles: tiles of kAttnTileRowsF32 flattened rows of all requests, per kv head.  `lazy` non-null
+// (lazy_rope contexts): stored keys are turned to their position as they are read.
+hipError_t launch_attn_f32(const AttnArgs& a, int64_t n_tiles, const LazyRefs* lazy, hipStream_t stream);
 
 
 // Can the attention launch of this plan carry the linking of the next layer (device-resident
