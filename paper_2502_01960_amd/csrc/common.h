@@ -246,7 +246,7 @@ struct AttnArgs {
   float scale;
   int32_t n_q_heads, n_kv_heads, head_dim;
   int32_t n_requests;
-  float* ws_o;    // [n_parts][kAttnTileRows][D] normalised partial outputs of cut tiles
+  float* ws_o;    // [n_parts][kAttnTileRows * D] normalised partial outputs of cut tiles, in register order
   float* ws_lse;  // [n_parts][kAttnTileRows] their log-sum-exp (-inf: the row saw no key of the piece)
   const AttnMerge* merges;
   int32_t n_merges;
