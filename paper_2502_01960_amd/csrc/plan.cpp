@@ -41,14 +41,11 @@ constexpr int kComputeUnits = 256;
 // straddles two runs costs no more than its parts while full tiles keep the K/V
 // stream per flop low.
 //
-// Small and medium problems do not have a tile per compute unit, or only a few, very
-// unequal ones (a tile's work grows with the position of its rows).  Such tiles are also
-// cut along the keys: every piece visits a range of 64-key blocks and leaves a partial
-// result (normalised output + log-sum-exp) that a merge kernel combines.  The piece size
-// is chosen so that the pieces make kSplitRounds rounds over the chip at most -- one round
-// when the whole problem is only a few blocks per compute unit -- and never less than
-// kMinPieceBlocks blocks (the fixed cost of a workgroup is about one and a half blocks).
-// Large problems (more blocks per compute unit than the longest tile has) are not cut.
+// A launch ends when its last tile does, and a tile's work grows with the position of its rows.
+// Where the longest tile is more than half of a compute unit's share, tiles are also cut along the
+// keys: every piece visits a range of 64-key blocks and leaves a partial result (normalised output
+// + log-sum-exp) that a merge kernel combines.  How long the pieces are is decided by list
+// scheduling of a few candidates (choose_cut below).
 //
 // Launch order: tiles that read the same K/V (same request and kv head) are dealt to the
 // same L2 domain, and inside a domain the longest tiles come first so the tail of the
@@ -60,7 +57,14 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   };
   constexpr int64_t kBlock = 64;          // keys per block of the attention kernel
   constexpr int64_t kMinPieceBlocks = 4;
-  constexpr int64_t kSplitRounds = 2;
+  // Fixed costs in blocks (1.3 us each with one workgroup per compute unit): of a tile, of a piece
+  // (its partial result is written and read again) and of the merge launch.  Measured over ten
+  // batches with every cap from 4 blocks up: the launches chosen with 12 or 20 for a piece differ by
+  // 3 % at most.  Pieces of one size for a whole launch that had to fit one or two rounds over the
+  // chip left it half idle: one request of 2177 rows with 87-block tiles 94 -> 66 us, 8 requests of
+  // 13K tokens 235 -> 198 us, 2 lazy requests of 5K tokens 136 -> 126 us.
+  constexpr int64_t kTileCost = 6, kPieceCost = 16, kMergeCost = 4;
+  constexpr int64_t kUnit = 10;
   const int B = p.n_requests;
   const int n_combo = B * n_kv_heads;
   auto last_pos = [&](int b, int64_t row_end) {  // position of the last fresh row below flattened row `row_end`
@@ -83,104 +87,193 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     return n;
   };
   while (tile_rows > 64 && count_pieces(tile_rows, nullptr) < kComputeUnits) tile_rows /= 2;
-  int64_t total_blocks = 0;
-  count_pieces(tile_rows, &total_blocks);
+  // the tiles of one kv head
+  struct RowTile {
+    int b;
+    int64_t row, n, n_keys, blocks;
+  };
+  std::vector<RowTile> row_tiles;
+  int64_t total_blocks = 0, longest = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t rows = static_cast<int64_t>(p.q_off[b + 1] - p.q_off[b]) * group;
+    for (int64_t row = 0; row < rows; row += tile_rows) {
+      const int64_t n = std::min<int64_t>(tile_rows, rows - row), n_keys = last_pos(b, row + n) + 1;
+      row_tiles.push_back(RowTile{b, row, n, n_keys, (n_keys + kBlock - 1) / kBlock});
+      total_blocks += row_tiles.back().blocks * n_kv_heads;
+      longest = std::max(longest, row_tiles.back().blocks);
+    }
+  }
   const int64_t per_cu = (total_blocks + kComputeUnits - 1) / kComputeUnits;
-  const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(kSplitRounds, per_cu / 16));
-  int64_t cap = std::max<int64_t>(kMinPieceBlocks, (total_blocks + kComputeUnits * rounds - 1) / (kComputeUnits * rounds));
-  // rounding up per tile makes more pieces than total / cap: grow the cap until they fit the rounds
-  auto count_at_cap = [&](int64_t c) {
-    int64_t n = 0;
-    for (int b = 0; b < B; ++b) {
-      const int64_t rows = static_cast<int64_t>(p.q_off[b + 1] - p.q_off[b]) * group;
-      for (int64_t row = 0; row < rows; row += tile_rows) {
-        const int64_t blocks = (last_pos(b, std::min(rows, row + tile_rows)) + 1 + kBlock - 1) / kBlock;
-        n += (blocks + c - 1) / c * n_kv_heads;
+  // How a tile of `blocks` blocks is cut: tiles longer than `cap` into even pieces, or into pieces
+  // of exactly `cap` and a remainder.  Even pieces suit launches of one round, where the longest
+  // piece decides; equal pieces with remainders fill the end of a launch of several.
+  struct Cut {
+    int64_t cap;
+    bool even;
+  };
+  auto n_pieces = [&](int64_t blocks, const Cut& c) {
+    if (blocks <= c.cap) return int64_t{1};
+    if (c.even) return std::max<int64_t>(1, std::min((blocks + c.cap - 1) / c.cap, blocks / kMinPieceBlocks));
+    return blocks % c.cap >= kMinPieceBlocks ? blocks / c.cap + 1 : blocks / c.cap;
+  };
+  auto piece_begin = [&](int64_t blocks, const Cut& c, int64_t parts, int64_t i) {
+    // (a remainder shorter than the smallest piece is shared by the others)
+    return c.even || blocks % c.cap < kMinPieceBlocks || i == parts ? blocks * i / parts : i * c.cap;
+  };
+  // How long a piece of `keys` keys of tile t (cut into `parts`) occupies a compute unit.
+  auto duration = [&](const RowTile& t, int64_t keys, int64_t parts) {
+    const int64_t blocks = (keys + kBlock - 1) / kBlock + (parts > 1 ? kPieceCost : kTileCost);
+    return blocks * (t.n > kAttnTileRows / 2 ? kUnit : kUnit * 4 / 5);
+  };
+  // Predicted end of the launch, in blocks / kUnit: list scheduling, longest piece first, over the compute
+  // units that one kv head has to itself.
+  int64_t heads = n_kv_heads, per_head_cus = kComputeUnits;
+  while (heads % 2 == 0 && per_head_cus > kComputeUnits / kXcds) heads /= 2, per_head_cus /= 2;
+  std::vector<int64_t> costs, load;
+  auto simulate = [&](const Cut& c, int64_t best) {
+    costs.clear();
+    int64_t sum = 0;
+    bool cut = false;
+    for (const RowTile& t : row_tiles) {
+      const int64_t parts = n_pieces(t.blocks, c);
+      cut = cut || parts > 1;
+      for (int64_t i = 0; i < parts; ++i) {
+        const int64_t cost = duration(t, (piece_begin(t.blocks, c, parts, i + 1) - piece_begin(t.blocks, c, parts, i)) * kBlock, parts);
+        for (int64_t h = 0; h < heads; ++h) costs.push_back(cost);
+        sum += cost * heads;
       }
     }
-    return n;
+    const int64_t merge = cut ? kMergeCost * kUnit : 0;
+    if (sum / per_head_cus + merge >= best) return best;  // cannot be better
+    std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
+    if (costs.empty() || costs.front() + merge >= best) return best;
+    load.assign(per_head_cus, 0);
+    int64_t end = 0;
+    for (const int64_t cost : costs) {
+      std::pop_heap(load.begin(), load.end(), std::greater<int64_t>());
+      load.back() += cost;
+      end = std::max(end, load.back());
+      std::push_heap(load.begin(), load.end(), std::greater<int64_t>());
+    }
+    return end + merge;
   };
-  while (count_at_cap(cap) > kComputeUnits * rounds && cap < total_blocks) cap += std::max<int64_t>(1, cap / 16);
-  // One candidate launch: the tiles cut with pieces of at most `cap` blocks, dealt to the L2
-  // domains and ordered inside each.
+  auto choose_cut = [&]() {
+    Cut chosen{longest, true};  // uncut
+    if (2 * longest <= per_cu) return chosen;
+    int64_t best = simulate(chosen, INT64_MAX);
+    best -= best * 3 / 100;  // a cut launch has to be worth its partial results
+    // Long launches are only cut where a few tiles stand out, coarsely: finer pieces end the launch
+    // up to 2 % earlier, but the linking of the next layer then no longer fits beside its end.
+    const bool is_long = per_cu > 256;
+    const std::vector<int64_t> percents =
+        is_long ? std::vector<int64_t>{70, 60, 50, 40} : std::vector<int64_t>{100, 80, 115, 90, 65, 130, 150, 55, 180, 220, 270, 330};
+    int64_t last = 0;
+    for (const int64_t percent : percents) {
+      const int64_t cap = std::max<int64_t>(kMinPieceBlocks, (per_cu * percent + 99) / 100);
+      if (cap >= longest || cap == last) continue;
+      last = cap;
+      for (const bool even : {true, false}) {
+        if (is_long && !even) continue;
+        const int64_t m = simulate(Cut{cap, even}, best);
+        if (m < best) {
+          best = m;
+          chosen = Cut{cap, even};
+        }
+      }
+    }
+    return chosen;
+  };
+  const Cut cut = choose_cut();
+  // The launch: the tiles cut, dealt to the L2 domains and ordered inside each.
   struct Layout {
     std::vector<std::vector<Item>> queue;  // per L2 domain, in launch order
     std::vector<AttnMerge> merges;
     int32_t n_parts = 0;
   };
   auto by_cost = [](const Item& a, const Item& b) { return a.cost > b.cost; };
-  auto lay_out = [&](int64_t cap_blocks) {
+  auto lay_out = [&]() {
     Layout out;
     std::vector<std::vector<Item>> per_combo(n_combo);
-    for (int b = 0; b < B; ++b) {
-      const int64_t rows = static_cast<int64_t>(p.q_off[b + 1] - p.q_off[b]) * group;
-      for (int64_t row = 0; row < rows; row += tile_rows) {
-        const int64_t n = std::min<int64_t>(tile_rows, rows - row);
-        const int64_t n_keys = last_pos(b, row + n) + 1;
-        const int64_t blocks = (n_keys + kBlock - 1) / kBlock;
-        int64_t parts = (blocks > cap_blocks) ? (blocks + cap_blocks - 1) / cap_blocks : 1;
-        const int64_t per = (blocks + parts - 1) / parts;  // blocks per piece
-        parts = (blocks + per - 1) / per;
-        for (int64_t i = 0; i < parts; ++i) {
-          const int64_t key0 = i * per * kBlock;
-          const int64_t key1 = std::min<int64_t>(n_keys, (i + 1) * per * kBlock);
-          // cost = keys visited, summed over the wavefronts of 32 rows (each stops at its own last row)
-          int64_t cost = 64;
-          for (int64_t w = row; w < row + n; w += 32)
-            cost += std::max<int64_t>(0, std::min<int64_t>(last_pos(b, std::min(w + 32, row + n)) + 1, key1) - key0);
-          for (int g = 0; g < n_kv_heads; ++g) {
-            Item it{};
-            it.t.req = b;
-            it.t.kv_head = g;
-            it.t.row0 = static_cast<int32_t>(row);
-            it.t.n_rows = static_cast<int32_t>(n);
-            it.t.n_keys = static_cast<int32_t>(key1);
-            it.t.key0 = static_cast<int32_t>(key0);
-            it.t.part = -1;  // set below for the pieces of a cut tile
-            it.cost = cost;
-            per_combo[b * n_kv_heads + g].push_back(it);
-          }
+    for (const RowTile& rt : row_tiles) {
+      const int b = rt.b;
+      const int64_t row = rt.row, n = rt.n;
+      const int64_t parts = n_pieces(rt.blocks, cut);
+      for (int64_t i = 0; i < parts; ++i) {
+        const int64_t key0 = piece_begin(rt.blocks, cut, parts, i) * kBlock;
+        const int64_t key1 = std::min<int64_t>(rt.n_keys, piece_begin(rt.blocks, cut, parts, i + 1) * kBlock);
+        const int64_t cost = duration(rt, key1 - key0, parts);
+        for (int g = 0; g < n_kv_heads; ++g) {
+          Item it{};
+          it.t.req = b;
+          it.t.kv_head = g;
+          it.t.row0 = static_cast<int32_t>(row);
+          it.t.n_rows = static_cast<int32_t>(n);
+          it.t.n_keys = static_cast<int32_t>(key1);
+          it.t.key0 = static_cast<int32_t>(key0);
+          it.t.part = -1;  // set below for the pieces of a cut tile
+          it.cost = cost;
+          per_combo[b * n_kv_heads + g].push_back(it);
         }
-        if (parts > 1) {
-          for (int g = 0; g < n_kv_heads; ++g) {
-            AttnMerge m{};
-            m.req = b;
-            m.kv_head = g;
-            m.row0 = static_cast<int32_t>(row);
-            m.n_rows = static_cast<int32_t>(n);
-            m.first_part = out.n_parts;
-            m.n_parts = static_cast<int32_t>(parts);
-            out.n_parts += static_cast<int32_t>(parts);
-            out.merges.push_back(m);
-            // the pieces of this (tile, g) were pushed last into their group, in key order
-            auto& v = per_combo[b * n_kv_heads + g];
-            for (int64_t i = 0; i < parts; ++i) v[v.size() - parts + i].t.part = m.first_part + static_cast<int32_t>(i);
-          }
+      }
+      if (parts > 1) {
+        for (int g = 0; g < n_kv_heads; ++g) {
+          AttnMerge m{};
+          m.req = b;
+          m.kv_head = g;
+          m.row0 = static_cast<int32_t>(row);
+          m.n_rows = static_cast<int32_t>(n);
+          m.first_part = out.n_parts;
+          m.n_parts = static_cast<int32_t>(parts);
+          out.n_parts += static_cast<int32_t>(parts);
+          out.merges.push_back(m);
+          // the pieces of this (tile, g) were pushed last into their group, in key order
+          auto& v = per_combo[b * n_kv_heads + g];
+          for (int64_t i = 0; i < parts; ++i) v[v.size() - parts + i].t.part = m.first_part + static_cast<int32_t>(i);
         }
       }
     }
     out.queue.assign(kXcds, {});
-    if (n_combo >= kXcds) {
-      // whole (request, kv head) groups go to the currently lightest domain, heaviest first
-      std::vector<int> order(n_combo);
-      std::iota(order.begin(), order.end(), 0);
-      std::vector<int64_t> total(n_combo, 0);
-      for (int c = 0; c < n_combo; ++c)
-        for (const Item& it : per_combo[c]) total[c] += it.cost;
-      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return total[a] > total[b]; });
-      std::vector<int64_t> load(kXcds, 0);
-      for (int c : order) {
-        const int x = static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
-        load[x] += total[c];
-        out.queue[x].insert(out.queue[x].end(), per_combo[c].begin(), per_combo[c].end());
-      }
-    } else {
-      // fewer groups than domains: spread each group over `share` domains, tile by tile
-      const int share = std::max(1, kXcds / std::max(1, n_combo));
+    std::vector<int64_t> total(n_combo, 0);
+    int64_t sum = 0;
+    for (int c = 0; c < n_combo; ++c) {
+      for (const Item& it : per_combo[c]) total[c] += it.cost;
+      sum += total[c];
+    }
+    // whole (request, kv head) groups go to the currently lightest domain, heaviest first ...
+    std::vector<int> order(n_combo), home(n_combo);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return total[a] > total[b]; });
+    std::vector<int64_t> domain(kXcds, 0);
+    for (int c : order) {
+      home[c] = static_cast<int>(std::min_element(domain.begin(), domain.end()) - domain.begin());
+      domain[home[c]] += total[c];
+    }
+    if (n_combo > 0 && kXcds % n_combo == 0) {
+      // (few groups: each has its own share of the domains, which get its tiles in turn)
+      const int share = kXcds / n_combo;
       for (int c = 0; c < n_combo; ++c) {
         std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
         for (size_t i = 0; i < per_combo[c].size(); ++i)
-          out.queue[(c * share + static_cast<int>(i % share)) % kXcds].push_back(per_combo[c][i]);
+          out.queue[c * share + static_cast<int>(i % share)].push_back(per_combo[c][i]);
+      }
+    } else if (*std::max_element(domain.begin(), domain.end()) * kXcds <= sum + sum * 3 / 100) {
+      for (int c : order) out.queue[home[c]].insert(out.queue[home[c]].end(), per_combo[c].begin(), per_combo[c].end());
+    } else {
+      // ... unless that leaves some domain idle at the end (12 groups on 8 domains: a quarter of
+      // the chip): then the groups lie on a line that is cut into eight equal parts, and the tiles
+      // of a group that spans several domains are dealt to them, longest first, by what each lacks
+      int64_t begin = 0;
+      for (int c = 0; c < n_combo; ++c) {
+        int64_t lack[kXcds] = {};
+        for (int x = 0; x < kXcds; ++x)
+          lack[x] = std::min(begin + total[c], sum * (x + 1) / kXcds) - std::max(begin, sum * x / kXcds);
+        begin += total[c];
+        std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
+        for (const Item& it : per_combo[c]) {
+          const int x = static_cast<int>(std::max_element(lack, lack + kXcds) - lack);
+          lack[x] -= it.cost;
+          out.queue[x].push_back(it);
+        }
       }
     }
     for (auto& q : out.queue) std::stable_sort(q.begin(), q.end(), by_cost);
@@ -207,32 +300,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     }
     return worst;
   };
-  Layout chosen = lay_out(cap);
-  // Large problems are not cut by the rule above, but a few tiles may be so long that the
-  // launch ends with most compute units idle (one request of 75K tokens: the longest tile is
-  // two thirds of a compute unit's whole share).  Whether cutting those pays is decided by
-  // simulating the launch for a few piece sizes; the uncut launch is kept unless a cut one
-  // is predicted to finish at least 3 % earlier.
-  if (chosen.n_parts == 0) {
-    int64_t longest = 0;
-    for (int b = 0; b < B; ++b) {
-      const int64_t rows = static_cast<int64_t>(p.q_off[b + 1] - p.q_off[b]) * group;
-      if (rows > 0) longest = std::max(longest, (last_pos(b, rows) + 1 + kBlock - 1) / kBlock);
-    }
-    if (2 * longest > per_cu) {
-      const int64_t uncut = predicted_makespan(chosen);
-      int64_t best = uncut - uncut * 3 / 100;
-      for (const int64_t c : {per_cu * 7 / 10, per_cu * 6 / 10, per_cu / 2, per_cu * 4 / 10}) {
-        if (c < kMinPieceBlocks || c >= longest) continue;
-        Layout cand = lay_out(c);
-        const int64_t m = predicted_makespan(cand);
-        if (m < best) {
-          best = m;
-          chosen = std::move(cand);
-        }
-      }
-    }
-  }
+  Layout chosen = lay_out();
   // what the launch is predicted to leave idle: room for work that rides along in its tail
   p.est_makespan_blocks = predicted_makespan(chosen);
   p.est_idle_blocks = p.est_makespan_blocks * kComputeUnits - busy_blocks;
@@ -258,7 +326,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
 // kernel that walks a tile in list order changes the shift its queries are turned back by once per
 // chunk instance (softmax does not care about the order of the keys).  A tile visits the blocks
 // that start at or before its last row, a prefix of both parts; the pieces of a tile that was cut
-// along the keys share those blocks evenly, in list order.
+// along the keys share those blocks in proportion to their key ranges, in list order.
 void build_key_blocks(mpic_plan& p) {
   const int B = p.n_requests;
   p.key_order.clear();
@@ -268,20 +336,12 @@ void build_key_blocks(mpic_plan& p) {
     for (int32_t pos = p.ctx_off[b]; pos < p.ctx_off[b + 1]; ++pos)
       if (p.src_inst[pos] >= 0) p.key_order.push_back(pos);
   }
-  // the pieces of every cut tile: which one of how many, and where the tile ends
-  struct Piece {
-    int32_t index = 0, count = 1, n_keys = 0;
-  };
-  std::vector<Piece> pieces(p.n_parts);
-  for (const AttnMerge& m : p.merges)
-    for (int32_t i = 0; i < m.n_parts; ++i) {
-      pieces[m.first_part + i].index = i;
-      pieces[m.first_part + i].count = m.n_parts;
-    }
+  // where the tile that a piece belongs to ends
+  std::vector<int32_t> tile_end(p.n_parts);
   for (const AttnTile& t : p.tiles)
-    if (t.n_rows > 0 && t.part >= 0) pieces[t.part].n_keys = t.n_keys;
+    if (t.n_rows > 0 && t.part >= 0) tile_end[t.part] = t.n_keys;
   for (const AttnMerge& m : p.merges)  // (the last piece ends where the tile does)
-    for (int32_t i = 0; i + 1 < m.n_parts; ++i) pieces[m.first_part + i].n_keys = pieces[m.first_part + m.n_parts - 1].n_keys;
+    for (int32_t i = 0; i + 1 < m.n_parts; ++i) tile_end[m.first_part + i] = tile_end[m.first_part + m.n_parts - 1];
 
   for (int s = 0; s < kNumBlockSizes; ++s) {
     const int32_t bn = kBlockSizes[s];
@@ -314,18 +374,18 @@ void build_key_blocks(mpic_plan& p) {
         ranges.insert(ranges.end(), {0, 0, 0, 0});
         continue;
       }
-      const Piece pc = t.part >= 0 ? pieces[t.part] : Piece{0, 1, t.n_keys};
+      const int32_t end = t.part >= 0 ? tile_end[t.part] : t.n_keys;
       auto before_end = [&](int32_t lo, int32_t hi) {  // blocks of [lo, hi) that start below the tile's end
-        const KeyBlock* it = std::lower_bound(blocks.data() + lo, blocks.data() + hi, pc.n_keys,
+        const KeyBlock* it = std::lower_bound(blocks.data() + lo, blocks.data() + hi, end,
                                               [](const KeyBlock& k, int32_t v) { return k.pos0 < v; });
         return static_cast<int32_t>(it - (blocks.data() + lo));
       };
-      // no piece is empty: pieces own at least three 64-key blocks of positions on average, and a
-      // gathered block holds 96 keys at most.  Every row sees a key of the first piece, which starts
-      // with the request's first fresh row
+      // no piece is empty: a piece owns more than 192 keys' worth of positions, and a gathered block
+      // holds 96 keys at most.  Every row sees a key of the first piece, which starts with the
+      // request's first fresh row
       const int32_t nf = before_end(first[t.req], mid[t.req]), ns = before_end(mid[t.req], first[t.req + 1]);
-      const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * pc.index / pc.count);
-      const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * (pc.index + 1) / pc.count);
+      const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.key0 / end);
+      const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.n_keys / end);
       ranges.insert(ranges.end(), {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf});
     }
   }

@@ -360,3 +360,24 @@ def test_launch_estimate_is_the_list_scheduling_of_the_tile_order():
     reqs, _, _ = workloads.layout(1)
     plan = mpic.Plan(_ctx(sh.n_q_heads, sh.n_kv_heads, sh.head_dim, mpic.MPIC_F32, sh.rope_theta, 0), reqs, sh.default_k)
     assert plan.get("launch_estimate")[2] == 0 and plan.get("launch_estimate")[3] == 0
+
+
+@pytest.mark.parametrize("heads,requests", [((7, 1), 1), ((28, 4), 3), ((28, 4), 5), ((32, 8), 2), ((6, 3), 2), ((64, 8), 1)])
+@pytest.mark.parametrize("fresh,stored", [(40, 150), (700, 1500), (2100, 3300)])
+def test_cut_tiles_fill_the_domains(heads, requests, fresh, stored):
+    """Launches whose tiles are cut along the keys: every (row, head, key) once, no piece shorter than
+    four 64-key blocks (what the in-place kernel needs to give every piece a key block), and no L2
+    domain with much more work than the others, also where the (request, kv head) groups are not a
+    multiple of the domains."""
+    reqs = [[("chunk", 0, stored // 3, 0), ("text", fresh // 2), ("chunk", 1, stored, 32), ("text", fresh - fresh // 2 + b)]
+            for b in range(requests)]
+    plan = mpic.Plan(_ctx(*heads), reqs, 0)
+    want = build_plan(reqs, 0)
+    _check_tiles(plan, want, heads[0] // heads[1], heads[1])
+    tiles = plan.get("attn_tiles")
+    live = tiles[tiles[:, 3] > 0]
+    cut = live[live[:, 6] >= 0]
+    assert ((cut[:, 4] - cut[:, 5]) > 192).all()
+    work = [int((-(-(d[:, 4] - d[:, 5]) // 64) + 8).sum()) for d in (tiles[x::8][tiles[x::8][:, 3] > 0] for x in range(8))]
+    longest = int((live[:, 4] - live[:, 5]).max()) // 64 + 9
+    assert max(work) <= 1.15 * sum(work) / 8 + 2 * longest
