@@ -342,15 +342,17 @@ __global__ __launch_bounds__(THREADS) void decode_bf16_kernel(DecodeArgs a, Extr
   float* m_o = reinterpret_cast<float*>(lds);               // [WAVES][32 columns][D]
   float* m_m = m_o + WAVES * 32 * D;                        // [WAVES][32]
   float* m_l = m_m + WAVES * 32;                            // [WAVES][32]
+  if (valid) {  // (rows of 512 bytes conflict in the LDS banks: only the columns that are merged below)
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      f32x4 o;
+      for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = acc_o[db][q4 * 4 + e];
-      *reinterpret_cast<f32x4*>(m_o + (wave * 32 + col) * D + db * 32 + q4 * 8 + hi * 4) = o;
-    }
+        for (int e = 0; e < 4; ++e) o[e] = acc_o[db][q4 * 4 + e];
+        *reinterpret_cast<f32x4*>(m_o + (wave * 32 + col) * D + db * 32 + q4 * 8 + hi * 4) = o;
+      }
+  }
   if (hi == 0) {
     m_m[wave * 32 + col] = m_run;
     m_l[wave * 32 + col] = l_wave;
@@ -406,6 +408,16 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
   // keys of the request, or (lazy_rope, bf16) slots of its 32-key blocks
   const int n_ctx = a.blk_first ? (a.blk_first[b + 1] - a.blk_first[b]) * 32 : a.ctx_off[b + 1] - a.ctx_off[b];
   const int n_s = (n_ctx + a.keys_per_split - 1) / a.keys_per_split;
+  // The first log-sum-exps and partial outputs are fetched right here, before the weights are known and
+  // whether or not the request has that many splits (the others are not used): they and the tables
+  // arrive together instead of one after the other (with the narrower LDS merge of the main kernel
+  // 16.6 -> 13.6 us for a step over 2.6K tokens with 32 kv heads).
+  constexpr int kAhead = 8;
+  const float* po = a.ws_o + row * a.n_splits * kD + d;
+  const float lse0 = a.ws_lse[row * a.n_splits + min(d, a.n_splits - 1)];
+  float x0[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) x0[i] = po[static_cast<int64_t>(min(i, a.n_splits - 1)) * kD];
   float self = -INFINITY;
   float v_new = 0.f;
   if (a.new_k) {
@@ -426,13 +438,17 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
   }
   if (d < 64) {
     // lane l owns splits l, l + 64, ...
-    float m = self;
-    for (int s = d; s < n_s; s += 64) m = fmaxf(m, a.ws_lse[row * a.n_splits + s]);
+    float m = d < n_s ? fmaxf(self, lse0) : self;
+    for (int s = d + 64; s < n_s; s += 64) m = fmaxf(m, a.ws_lse[row * a.n_splits + s]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     float z = 0.f;
     if (m != -INFINITY) {
-      for (int s = d; s < n_s; s += 64) {
+      if (d < n_s) {
+        z = expf(lse0 - m);
+        wgt[d] = z;
+      }
+      for (int s = d + 64; s < n_s; s += 64) {
         const float w = expf(a.ws_lse[row * a.n_splits + s] - m);
         wgt[s] = w;
         z += w;
@@ -450,8 +466,10 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
   float z = stat[1];
   float o = 0.f;
   if (m != -INFINITY) {
-    const float* po = a.ws_o + row * a.n_splits * kD + d;
-    int s = 0;
+    int s = min(n_s, kAhead);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (i < s) o = fmaf(wgt[i], x0[i], o);
     for (; s + 8 <= n_s; s += 8) {
       float x[8];
 #pragma unroll
