@@ -325,7 +325,7 @@ int mpic_assemble_kv_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src*
  * A plan with no fresh row is a no-op that returns MPIC_OK.
  * Small and medium batches are cut along the keys as well as along the rows (see
  * MPIC_PLAN_ATTN_TILES); the partial results live in a workspace owned by the context,
- * allocated on first use and grown (with a device synchronisation) when a later call needs
+ * allocated by the first call that brings a plan to the GPU and grown by a plan that needs
  * more, so calls of one context that use it must not overlap on different streams.
  * Errors: MPIC_ERR_INVALID, MPIC_ERR_OOM (workspace), MPIC_ERR_HIP.
  */

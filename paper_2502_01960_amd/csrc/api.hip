@@ -29,14 +29,41 @@ namespace {
 
 constexpr size_t kTablePad = 128;
 
+// Workspace for the partial results of a plan's cut tiles.  It grows with the first call that brings
+// the plan to the GPU, at least twofold (so that what it replaces is never more than what it holds);
+// the attention calls themselves find it in place and can be captured.
+int ensure_attn_ws(mpic_ctx* ctx, const mpic_plan* p) {
+  const size_t need = static_cast<size_t>(p->n_parts) * kAttnTileRows * (ctx->cfg.head_dim + 1) * sizeof(float);
+  if (ctx->cfg.dtype != MPIC_BF16 || need <= ctx->attn_ws_bytes) return MPIC_OK;
+  if (ctx->attn_ws) ctx->attn_ws_old.reserve(ctx->attn_ws_old.size() + 1);
+  void* ws = nullptr;
+  size_t bytes = std::max(need, 2 * ctx->attn_ws_bytes);
+  if (hipMalloc(&ws, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    bytes = need;
+    if (hipMalloc(&ws, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(ctx, MPIC_ERR_OOM, "selective_attn: workspace allocation failed");
+    }
+  }
+  if (ctx->attn_ws) ctx->attn_ws_old.push_back(ctx->attn_ws);
+  ctx->attn_ws = ws;
+  ctx->attn_ws_bytes = bytes;
+  return MPIC_OK;
+}
+
 // Copy the integer maps, rotary tables and tile list to the GPU (once per plan): the tables
 // are packed into one host image that crosses the bus in a single copy into a single
 // allocation.  May throw std::bad_alloc (host image); the entry points catch it.
-int upload_plan(mpic_ctx* ctx, mpic_plan* p) {
+int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   if (p->dev.block) {
     if (p->dev.device != ctx->device) return fail(ctx, MPIC_ERR_INVALID, "plan lives on another GPU");
+    p->spare_blocks->used(&p->use, stream);
     return MPIC_OK;
   }
+  ctx->spare_blocks->mark(stream);
+  const int rc = ensure_attn_ws(ctx, p);
+  if (rc != MPIC_OK) return rc;
   const size_t n = p->n_ctx, nq = p->n_q, B = p->n_requests;
   // byte offset of every context row in 16-byte units (saves the attention kernel a
   // 64-bit multiply per staged row); fits 32 bits for context buffers below 64 GiB
@@ -108,12 +135,33 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p) {
   }
   image.resize(image.size() + 256, 0);
 
-  char* base = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&base), image.size()) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(ctx, MPIC_ERR_OOM, "device allocation of the plan failed");
+  // A plan is made for every request, so nothing here may wait for the requests before it: the block
+  // of an earlier plan is used again if one fits (no work reads it any more, see SpareBlocks), and
+  // the tables go up on a library stream.  hipFree and a copy on the default stream drained the GPU
+  // twice per request (four layers of a 2.6K-token request with its plan: 282 -> 193 us).
+  size_t bytes = 0;
+  char* base = static_cast<char*>(ctx->spare_blocks->take(image.size(), &bytes));
+  if (!base) {
+    bytes = (image.size() + 0xffff) / 0x10000 * 0x10000;  // plans of similar requests fit each other's blocks
+    if (hipMalloc(reinterpret_cast<void**>(&base), bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(ctx, MPIC_ERR_OOM, "device allocation of the plan failed");
+    }
   }
-  const hipError_t e = hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice);
+  // (the side stream is there already; chunks on their way over it must not delay the plan, and
+  // a stream of its own costs 80 us to create)
+  hipError_t e = hipSuccess;
+  hipStream_t up = ctx->upload_stream;
+  if (!up) {
+    up = ctx->side_stream;
+    if (hipStreamQuery(up) != hipSuccess) {
+      (void)hipGetLastError();
+      e = hipStreamCreateWithFlags(&ctx->upload_stream, hipStreamNonBlocking);
+      up = ctx->upload_stream;
+    }
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(base, image.data(), image.size(), hipMemcpyHostToDevice, up);
+  if (e == hipSuccess) e = hipStreamSynchronize(up);
   if (e != hipSuccess) {
     (void)hipFree(base);
     return fail_hip(ctx, e, "upload of the plan");
@@ -147,8 +195,11 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p) {
     }
   }
   d.block = base;
+  d.block_bytes = bytes;
   d.device = ctx->device;
   p->dev = d;
+  p->spare_blocks = ctx->spare_blocks;
+  p->spare_blocks->used(&p->use, stream);
   return MPIC_OK;
 }
 
@@ -215,8 +266,14 @@ extern "C" void mpic_destroy(mpic_ctx* ctx) {
     for (hipEvent_t ev : ctx->ev_copy) (void)hipEventDestroy(ev);
     for (void* buf : ctx->staging)
       if (buf) (void)hipFree(buf);
+    if (ctx->upload_stream) {
+      (void)hipStreamSynchronize(ctx->upload_stream);
+      (void)hipStreamDestroy(ctx->upload_stream);
+    }
+    ctx->spare_blocks->close([](void* p) { (void)hipFree(p); });
     if (ctx->decode_ws) (void)hipFree(ctx->decode_ws);
     if (ctx->attn_ws) (void)hipFree(ctx->attn_ws);
+    for (void* ws : ctx->attn_ws_old) (void)hipFree(ws);
     if (cur >= 0) (void)hipSetDevice(cur);
   }
   delete ctx;
@@ -224,7 +281,7 @@ extern "C" void mpic_destroy(mpic_ctx* ctx) {
 
 extern "C" void mpic_plan_destroy(mpic_plan* plan) {
   if (!plan) return;
-  if (plan->dev.block) {
+  if (plan->dev.block && !plan->spare_blocks->give(plan->dev.block, plan->dev.block_bytes, plan->use)) {
     int cur = -1;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(plan->dev.device);
@@ -278,7 +335,7 @@ int mpic::assemble_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* s
   if (any_mapped) ctx->background_seen = true;  // a launch that lasts as long as the transfer runs beside others
   int rc = mpic::bind_device(ctx);
   if (rc != MPIC_OK) return rc;
-  rc = mpic::upload_plan(ctx, plan);
+  rc = mpic::upload_plan(ctx, plan, static_cast<hipStream_t>(stream_));
   if (rc != MPIC_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   const mpic_config& c = ctx->cfg;
@@ -515,7 +572,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   }
   int rc = mpic::bind_device(ctx);
   if (rc != MPIC_OK) return rc;
-  rc = mpic::upload_plan(ctx, plan);
+  rc = mpic::upload_plan(ctx, plan, static_cast<hipStream_t>(stream_));
   if (rc != MPIC_OK) return rc;
   const mpic_config& c = ctx->cfg;
   mpic::AttnArgs a{};
@@ -538,19 +595,6 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   a.n_requests = plan->n_requests;
   if (c.dtype == MPIC_BF16 && plan->n_parts > 0) {
     const size_t slots = static_cast<size_t>(plan->n_parts) * mpic::kAttnTileRows;
-    const size_t need = slots * (c.head_dim + 1) * sizeof(float);
-    if (need > ctx->attn_ws_bytes) {
-      // growing the workspace is rare (first call / larger batch): drain what may still read it
-      MPIC_HIP(ctx, hipDeviceSynchronize());
-      if (ctx->attn_ws) MPIC_HIP(ctx, hipFree(ctx->attn_ws));
-      ctx->attn_ws = nullptr;
-      ctx->attn_ws_bytes = 0;
-      if (hipMalloc(&ctx->attn_ws, need) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(ctx, MPIC_ERR_OOM, "selective_attn: workspace allocation failed");
-      }
-      ctx->attn_ws_bytes = need;
-    }
     a.ws_o = static_cast<float*>(ctx->attn_ws);
     a.ws_lse = a.ws_o + slots * c.head_dim;
     a.merges = plan->dev.merges;
@@ -649,10 +693,11 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
                                          "e.g. mpic_assemble_kv, uploads it)");
     if (ctx->device != dev || plan->dev.device != dev)
       return fail(ctx, MPIC_ERR_INVALID, "decode_attn_static: context and plan live on another GPU than the current one");
+    plan->spare_blocks->used(&plan->use, static_cast<hipStream_t>(stream_));
   } else {
     rc = mpic::bind_device(ctx);
     if (rc != MPIC_OK) return rc;
-    rc = mpic::upload_plan(ctx, plan);
+    rc = mpic::upload_plan(ctx, plan, static_cast<hipStream_t>(stream_));
     if (rc != MPIC_OK) return rc;
   }
   const mpic_config& c = ctx->cfg;

@@ -524,8 +524,12 @@ extern "C" int mpic_create(mpic_ctx** out, const mpic_config* config) {
   } else {
     return MPIC_ERR_INVALID;
   }
-  mpic_ctx* ctx = new (std::nothrow) mpic_ctx();
-  if (!ctx) return MPIC_ERR_OOM;
+  mpic_ctx* ctx = nullptr;
+  try {
+    ctx = new mpic_ctx();
+  } catch (const std::bad_alloc&) {
+    return MPIC_ERR_OOM;
+  }
   ctx->cfg = c;
   ctx->group = c.n_q_heads / c.n_kv_heads;
   *out = ctx;
