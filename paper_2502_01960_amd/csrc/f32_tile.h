@@ -22,6 +22,13 @@
 //                               load of a value row -- straight from memory, without LDS.
 // The value rows of a block arrive while its keys are multiplied, the keys of the next block while
 // this one is normalised and multiplied with the values.
+//
+// Error against float64.  Most of it is the rounding of the logits, a sum of D terms: even and odd
+// chunks have an accumulator each.  With one for all of them the outputs had 0.95 to 1.23 times the error of
+// plain fp32 loops over the keys, with two 0.69 to 0.96 of it (contexts of 80 to 2.6K tokens, prefill
+// and decode; one image of 576 tokens with 32 heads, link + attend, 55.5 -> 56.9 us).  scale * log2(e) is held in two parts, since its
+// rounding shifts the exponents of all keys the same way, and the weights are summed in fours:
+// log-sum-exp of that image 1.07 -> 0.81 of the error of plain loops.
 #pragma once
 
 #include "common.h"
@@ -89,7 +96,17 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
   const int lane = tid & 63, col = lane & 31, hi = lane >> 5;
   char* area = lds + wave * G::kArea;
   const uint32_t area_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, area)));
-  const float c = scale * 1.4426950408889634f;
+  // weight of a raw logit t = s - reference <= 0: exp2(t * (c + c_lo)), c + c_lo = scale * log2(e).
+  // c lies below the product, so that c_lo is positive and t = -infinity gives -infinity in both terms.
+  float c = scale * 1.4426950216293335f, c_lo = fmaf(scale, 1.4426950216293335f, -c) + scale * 1.9259629891e-8f;
+  if (c_lo <= 0.f && c > 1e-36f) {
+    const float below = __uint_as_float(__float_as_uint(c) - 1);
+    c_lo += c - below;
+    c = below;
+  }
+  c = fmaxf(c, 1e-37f);  // (0 * -infinity is no number)
+  c_lo = fmaxf(c_lo, 1e-37f);
+  auto weight = [&](float t) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f(fmaf(t, c, t * c_lo)); };
   const int lo_pos = wave_min_i32(my_pos);
 
   // addresses of the key and value row that lane `lane % 32` stands for, and its rotary table row
@@ -166,7 +183,7 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
       }
       asm volatile("" ::: "memory");
     }
-    f32x16 s = f32x16{0};
+    f32x16 s = f32x16{0}, s_odd = f32x16{0};
     // (key operands are read two steps ahead; the scheduling barriers keep the compiler from reading
     // all of them first, which costs 64 registers and spills)
     auto key_chunk = [&](int j) __attribute__((always_inline)) {
@@ -179,9 +196,15 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
       const f32x4 k = kf[j & 1];
       if (j + 2 < G::kChunks / 2) kf[j & 1] = key_chunk(j + 2);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[4 * j + e], s, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) {
+        if (j & 1)
+          s_odd = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[4 * j + e], s_odd, 0, 0, 0);
+        else
+          s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[4 * j + e], s, 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
+    s += s_odd;
     // the values have arrived by now; settled before the next keys go out, so that the compiler's
     // waits for them never count those
 #pragma unroll
@@ -208,7 +231,7 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
     const float m_new = fmaxf(m_run, max_across_halves(m_blk));
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet: every weight below is exp2(-inf)
     if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_ref) * c);
+      const float alpha = weight(m_run - m_ref);
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < G::kBlocks; ++db) acc_o[db] *= alpha;
@@ -216,8 +239,8 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f((s[r] - m_ref) * c);
-      l_run += s[r];
+      s[r] = weight(s[r] - m_ref);
+      if (r % 4 == 3) l_run += (s[r - 3] + s[r - 2]) + (s[r - 1] + s[r]);
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
@@ -254,7 +277,7 @@ __device__ __forceinline__ void attend(const Rows& src, const float (&q)[D / 2],
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
     const float mw = m_of[w * kCols + mc];
-    const float wgt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - m_tot) * c);
+    const float wgt = mw == -INFINITY ? 0.f : weight(mw - m_tot);
     l_tot = fmaf(wgt, l_of[w * kCols + mc], l_tot);
 #pragma unroll
     for (int i = 0; i < G::kPerThread; ++i) o[i] = fmaf(wgt, part[(w * D + d0 + i) * kCols + mc], o[i]);
