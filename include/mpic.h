@@ -323,6 +323,11 @@ int mpic_assemble_kv_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src*
  *   out               device [n_fresh_rows][Hq][D], written
  *   lse               device float [n_fresh_rows][Hq], written; may be NULL
  * A plan with no fresh row is a no-op that returns MPIC_OK.
+ * Values that are not finite: F32 rows are only reached by keys and values they see.  In BF16 an
+ * infinity or NaN in a value row also reaches rows in front of it: 32 flattened rows are
+ * computed together, up to the key block (64 or 96 keys) that holds the last key any of them
+ * sees.  On lazy_rope contexts a block holds fresh rows, or stored rows of one chunk, that
+ * need not be neighbours.
  * Small and medium batches are cut along the keys as well as along the rows (see
  * MPIC_PLAN_ATTN_TILES); the partial results live in a workspace owned by the context,
  * allocated by the first call that brings a plan to the GPU and grown by a plan that needs

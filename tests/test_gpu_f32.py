@@ -120,3 +120,53 @@ def test_fp32_error_is_no_larger_than_that_of_plain_loops(heads, text, chunk):
         got, _ = p.gpu_decode(q, None, None)
         ref, _ = p.oracle_decode(K, V, q, None, None)
         assert rms(got, ref) <= rms(plain(q, np.array([len(K)])), ref)
+
+
+@pytest.mark.parametrize("heads", [(4, 4, 64), (6, 2, 128)])
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("source", ["fresh", "stored"])
+def test_fp32_rows_keep_clear_of_values_behind_them(heads, lazy, source):
+    """An infinity and a NaN in the value row of one position: the rows in front of it do not notice,
+    the others (and a decode step, whose last block repeats the last row as padding) notice in those
+    coordinates only; a NaN in its key row reaches none of the rows in front of it."""
+    requests = [[("text", 20), ("chunk", 0, 300, None), ("text", 3), ("chunk", 1, 77, None), ("text", 30)]]
+    p = _f32(requests, [300, 77], 7, *heads)
+    p.lazy = lazy
+    at, row = (409, int(np.flatnonzero(p.oplan["q_pos"] == 409)[0])) if source == "fresh" else (200, 180)
+    q, nk, nv = p.decode_inputs()
+
+    def run():
+        p.gpu_setup(False)
+        if lazy:
+            p.gpu_link_fresh_only()
+            p.gpu_attend_in_place()
+            decode = p.gpu_decode_in_place(q, None, None)[0]
+        else:
+            p.gpu_assemble()
+            p.gpu_attend()
+            decode = p.gpu_decode(q, None, None)[0]
+        torch.cuda.synchronize()
+        return p.out.to(torch.float64).cpu().numpy(), p.lse.to(torch.float64).cpu().numpy(), decode
+
+    K, V = p.oracle_link()
+    O_ref, L_ref = p.oracle_attend(K, V)
+    D_ref, _ = p.oracle_decode(K, V, q, None, None)
+    values = p.fresh_v if source == "fresh" else p.chunks[0][1]
+    keys = p.fresh_k if source == "fresh" else p.chunks[0][0]
+    before = p.oplan["q_pos"] < at
+    assert before.any() and not before.all()
+    values[row, :, 5], values[row, :, 40] = float("inf"), float("nan")
+    out, lse, decode = run()
+    assert np.abs(lse - L_ref).max() <= 1e-5 * np.abs(L_ref).max()
+    assert_f32_close(out[before], O_ref[before], "rows in front of the spoiled position")
+    assert np.isposinf(out[~before][..., 5]).all() and np.isnan(out[~before][..., 40]).all()
+    assert np.isposinf(decode[..., 5]).all() and np.isnan(decode[..., 40]).all()
+    rest = np.ones(heads[2], dtype=bool)
+    rest[[5, 40]] = False
+    assert_f32_close(out[~before][..., rest], O_ref[~before][..., rest], "other coordinates")
+    assert_f32_close(decode[..., rest], D_ref[..., rest], "other coordinates of the decode step")
+    keys[row, :, 7] = float("nan")
+    out, lse, decode = run()
+    assert_f32_close(out[before], O_ref[before], "rows in front of the spoiled key")
+    assert np.abs(lse - L_ref)[before].max() <= 1e-5 * np.abs(L_ref).max()
+    assert np.isnan(out[~before]).all() and np.isnan(lse[~before]).all() and np.isnan(decode).all()
