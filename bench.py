@@ -544,12 +544,9 @@ def main():
         ip_attn_ms = timed(attend_in_place, args.steps)
         ip_fresh_ms = timed(lambda s: mpic.mpic_assemble_kv_parts(ctx_lz.handle, plan_lz.handle, None, s["fk"], s["fv"], s["k_ctx"],
                                                                   s["v_ctx"], mpic.MPIC_PART_FRESH, stream), args.steps)
-        bn = args.attn_block_keys or 96
-        q_off, src_inst = plan_lz.get("q_off"), plan_lz.get("src_inst")
-        rows_of = list(np.diff(q_off)) + list(np.bincount(src_inst[src_inst >= 0]))  # fresh rows per request, stored rows per instance
-        n_slots = sum(-(-int(r) // bn) * bn for r in rows_of)
+        blocks = plan_lz.get("key_blocks_%d" % (args.attn_block_keys or 96))
         in_place = {"ms_per_step": round(ip_step_ms, 5), "attention_ms": round(ip_attn_ms, 5), "fresh_rows_ms": round(ip_fresh_ms, 5),
-                    "padding_keys_pct": round(100.0 * (n_slots / max(1, n_ctx) - 1.0), 3),
+                    "padding_keys_pct": round(100.0 * (len(blocks) * (args.attn_block_keys or 96) / max(1, n_ctx) - 1.0), 3),
                     "note": "lazy_rope context: fresh rows scattered into the context, stored rows read where their caches are "
                             "stored, queries turned back per chunk instance; same outputs as the linked step within the gates"}
 

@@ -133,21 +133,25 @@ enum {
                              /* (mpic_selective_attn_link_next); 1 if that is also predicted   */
                              /* to pay (the linking fits into the idle time, or the launch is  */
                              /* too short for a second stream to help)                         */
-  MPIC_PLAN_KEY_BLOCKS_32 = 16, /* lazy_rope contexts: [n_blocks][4] (first position, keys,    */
-  MPIC_PLAN_KEY_BLOCKS_64 = 17, /* chunk instance or -1 = fresh rows, request): the keys of    */
-  MPIC_PLAN_KEY_BLOCKS_96 = 18, /* every request cut into blocks of at most 32 / 64 / 96 keys  */
-                             /* that never straddle a change of source; request after request, */
-                             /* inside a request the blocks of fresh rows first, then those of */
-                             /* stored rows, each part in position order.  (A description of   */
-                             /* the sources by position, built when asked for: the kernels     */
-                             /* gather the keys of a source further, across such runs)         */
+  MPIC_PLAN_KEY_BLOCKS_32 = 16, /* lazy_rope contexts: [n_blocks][4] (position of the first    */
+  MPIC_PLAN_KEY_BLOCKS_64 = 17, /* key, keys, chunk instance or -1 = fresh rows, rank of the   */
+  MPIC_PLAN_KEY_BLOCKS_96 = 18, /* first key in its part): blocks of at most 32 / 64 / 96 keys */
+                             /* of one source, request after request, inside a request the     */
+                             /* blocks of its fresh part first, then those of its stored part. */
+                             /* A block holds the keys of ranks rank .. rank + keys - 1, which */
+                             /* need not be neighbours in the request.  The decode kernel      */
+                             /* walks the first list, the two shapes of the attention kernel   */
+                             /* the others                                                     */
   MPIC_PLAN_LAZY_TILES_64 = 19, /* lazy_rope contexts: [n_tiles][4] for every entry of         */
-  MPIC_PLAN_LAZY_TILES_96 = 20, /* MPIC_PLAN_ATTN_TILES the blocks in its range, as (f0, f1, s0,  */
+  MPIC_PLAN_LAZY_TILES_96 = 20, /* MPIC_PLAN_ATTN_TILES the blocks it visits, as (f0, f1, s0,  */
                              /* s1): fresh blocks f0..f1-1 and stored blocks s0..s1-1 of its   */
                              /* request, counted inside their parts                            */
   MPIC_PLAN_KEY_BLOCK_PARTS_32 = 21, /* lazy_rope contexts: [B][3] (first fresh block, first   */
   MPIC_PLAN_KEY_BLOCK_PARTS_64 = 22, /* stored block, end) of every request in the list above  */
   MPIC_PLAN_KEY_BLOCK_PARTS_96 = 23,
+  MPIC_PLAN_KEY_BLOCK_ORDER = 24, /* lazy_rope contexts: [N] for every request its keys by     */
+                             /* part and rank (fresh ones, then stored ones, each in position  */
+                             /* order), as ctx_off[request] + position                         */
   MPIC_PLAN_ATTN_TILES = 14  /* [n_tiles][8] launch order of the attention kernel: (request,   */
                              /* kv head, first flattened row, rows, end key, first key, slot   */
                              /* of the partial result or -1, 0); flattened row = (fresh row -  */

@@ -15,7 +15,7 @@ PLAN_FIELDS = dict(ctx_off=0, q_off=1, q_pos=2, q_req=3, slot_map=4, src_inst=5,
                    dst_slot=7, inst_src=8, inst_delta=9, inst_len=10, inst_k=11, inst_req=12,
                    runs=13, attn_tiles=14, launch_estimate=15, key_blocks_32=16, key_blocks_64=17,
                    key_blocks_96=18, lazy_tiles_64=19, lazy_tiles_96=20, key_block_parts_32=21,
-                   key_block_parts_64=22, key_block_parts_96=23)
+                   key_block_parts_64=22, key_block_parts_96=23, key_block_order=24)
 
 
 class MpicError(RuntimeError):

@@ -51,11 +51,6 @@ struct KeyBlock {
   int32_t inst;     // chunk instance that stores the keys (they lack its shift), -1 = fresh rows
   int32_t rank0;    // keys of the request's part (fresh, stored) in front of the block
 };
-// A run of consecutive positions with one source, cut to at most BN keys: what mpic_plan_get
-// tells about the sources of a request (MPIC_PLAN_KEY_BLOCKS_*); no kernel reads it.
-struct KeyRun {
-  int32_t pos0, n_valid, inst, req;
-};
 static_assert(sizeof(KeyBlock) == 16, "key block layout");
 constexpr int kNumBlockSizes = 3;
 constexpr int kBlockSizes[kNumBlockSizes] = {32, 64, 96};  // decode kernel, attention kernel shapes
@@ -253,12 +248,7 @@ struct mpic_plan {
   std::vector<int32_t> kblk_first[mpic::kNumBlockSizes];
   std::vector<int32_t> kblk_mid[mpic::kNumBlockSizes];    // [B] first stored block of every request (its fresh blocks come first)
   std::vector<int32_t> lazy_range[mpic::kNumBlockSizes];  // [n_tiles][4] fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
-  // the sources by position, for mpic_plan_get only: built when first asked for
-  std::mutex runs_mu;
-  bool runs_built = false;
-  std::vector<int32_t> run_blocks[mpic::kNumBlockSizes];  // [n][4] KeyRun
-  std::vector<int32_t> run_parts[mpic::kNumBlockSizes];   // [B][3] first fresh block, first stored block, end
-  std::vector<int32_t> run_range[mpic::kNumBlockSizes];   // [n_tiles][4] blocks of every tile
+  std::vector<int32_t> kblk_parts[mpic::kNumBlockSizes];  // [B][3] first fresh block, first stored block, end, for mpic_plan_get
   std::vector<int32_t> fresh_rot;            // contexts with fresh_pre_rope only
   std::vector<float> fresh_cos, fresh_sin;   // one row per distinct position id
   mpic::PlanDevice dev;

@@ -348,9 +348,11 @@ void build_key_blocks(mpic_plan& p) {
     auto& blocks = p.kblk[s];
     auto& first = p.kblk_first[s];
     auto& mid = p.kblk_mid[s];
+    auto& parts = p.kblk_parts[s];
     blocks.clear();
     first.assign(1, 0);
     mid.clear();
+    parts.clear();
     for (int b = 0; b < B; ++b) {
       const int32_t ctx0 = p.ctx_off[b], n = p.ctx_off[b + 1] - ctx0, n_fresh = p.q_off[b + 1] - p.q_off[b];
       const int32_t* order = p.key_order.data() + ctx0;
@@ -364,6 +366,7 @@ void build_key_blocks(mpic_plan& p) {
         i = end;
       }
       first.push_back(static_cast<int32_t>(blocks.size()));
+      parts.insert(parts.end(), {first[b], mid[b], first[b + 1]});
     }
     auto& ranges = p.lazy_range[s];
     ranges.clear();
@@ -387,66 +390,6 @@ void build_key_blocks(mpic_plan& p) {
       const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.key0 / end);
       const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.n_keys / end);
       ranges.insert(ranges.end(), {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf});
-    }
-  }
-}
-
-// What mpic_plan_get tells about the sources of a lazy_rope plan, by position (see KeyRun).  A run
-// ends where the source of the keys changes (next chunk instance, or stored rows <-> fresh rows),
-// where a tile that was cut along the keys starts a new piece, and after BN keys; the tiles are
-// restated as the runs inside their key range.
-void build_key_runs(mpic_plan& p) {
-  const int B = p.n_requests;
-  std::vector<std::vector<int32_t>> cuts(B);
-  for (const AttnTile& t : p.tiles)
-    if (t.n_rows > 0 && t.key0 > 0) cuts[t.req].push_back(t.key0);
-  for (auto& c : cuts) {
-    std::sort(c.begin(), c.end());
-    c.erase(std::unique(c.begin(), c.end()), c.end());
-  }
-  for (int s = 0; s < kNumBlockSizes; ++s) {
-    const int32_t bn = kBlockSizes[s];
-    std::vector<KeyRun> runs, fresh, stored;
-    auto& parts = p.run_parts[s];
-    parts.clear();
-    for (int b = 0; b < B; ++b) {
-      const int32_t ctx0 = p.ctx_off[b], n = p.ctx_off[b + 1] - ctx0;
-      fresh.clear();
-      stored.clear();
-      size_t next_cut = 0;
-      for (int32_t pos = 0; pos < n;) {
-        while (next_cut < cuts[b].size() && cuts[b][next_cut] <= pos) ++next_cut;
-        const int32_t limit = next_cut < cuts[b].size() ? std::min(n, cuts[b][next_cut]) : n;
-        const int32_t inst = p.src_inst[ctx0 + pos];
-        int32_t end = pos + 1;
-        while (end < limit && p.src_inst[ctx0 + end] == inst) ++end;
-        for (int32_t q = pos; q < end; q += bn) (inst < 0 ? fresh : stored).push_back(KeyRun{q, std::min(bn, end - q), inst, b});
-        pos = end;
-      }
-      const int32_t lo = static_cast<int32_t>(runs.size());
-      runs.insert(runs.end(), fresh.begin(), fresh.end());
-      const int32_t mid = static_cast<int32_t>(runs.size());
-      runs.insert(runs.end(), stored.begin(), stored.end());
-      parts.insert(parts.end(), {lo, mid, static_cast<int32_t>(runs.size())});
-    }
-    p.run_blocks[s].resize(runs.size() * 4);
-    if (!runs.empty()) std::memcpy(p.run_blocks[s].data(), runs.data(), runs.size() * sizeof(KeyRun));
-    auto& ranges = p.run_range[s];
-    ranges.clear();
-    if (bn == 32) continue;
-    auto below = [&](int32_t lo, int32_t hi, int32_t pos) {
-      const KeyRun* it = std::lower_bound(runs.data() + lo, runs.data() + hi, pos,
-                                          [](const KeyRun& k, int32_t v) { return k.pos0 < v; });
-      return static_cast<int32_t>(it - (runs.data() + lo));
-    };
-    for (const AttnTile& t : p.tiles) {
-      if (t.n_rows <= 0) {
-        ranges.insert(ranges.end(), {0, 0, 0, 0});
-        continue;
-      }
-      const int32_t* part = parts.data() + 3 * static_cast<size_t>(t.req);
-      ranges.insert(ranges.end(), {below(part[0], part[1], t.key0), below(part[0], part[1], t.n_keys),
-                                   below(part[1], part[2], t.key0), below(part[1], part[2], t.n_keys)});
     }
   }
 }
@@ -725,16 +668,6 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
 
 extern "C" int mpic_plan_get(const mpic_plan* plan, int32_t what, const int32_t** host_ptr, size_t* n) {
   if (!plan || !host_ptr || !n) return MPIC_ERR_INVALID;
-  if (what >= MPIC_PLAN_KEY_BLOCKS_32 && what <= MPIC_PLAN_KEY_BLOCK_PARTS_96 && plan->ctx->cfg.lazy_rope) {
-    mpic_plan* p = const_cast<mpic_plan*>(plan);
-    try {
-      std::lock_guard<std::mutex> lock(p->runs_mu);
-      if (!p->runs_built) mpic::build_key_runs(*p);
-      p->runs_built = true;
-    } catch (const std::bad_alloc&) {
-      return MPIC_ERR_OOM;
-    }
-  }
   const std::vector<int32_t>* v = nullptr;
   switch (what) {
     case MPIC_PLAN_CTX_OFF: v = &plan->ctx_off; break;
@@ -752,14 +685,20 @@ extern "C" int mpic_plan_get(const mpic_plan* plan, int32_t what, const int32_t*
     case MPIC_PLAN_INST_REQ: v = &plan->inst_req; break;
     case MPIC_PLAN_RUNS: v = &plan->runs; break;
     case MPIC_PLAN_LAUNCH_ESTIMATE: v = &plan->launch_est; break;
-    case MPIC_PLAN_KEY_BLOCKS_32: v = &plan->run_blocks[0]; break;
-    case MPIC_PLAN_KEY_BLOCKS_64: v = &plan->run_blocks[1]; break;
-    case MPIC_PLAN_KEY_BLOCKS_96: v = &plan->run_blocks[2]; break;
-    case MPIC_PLAN_LAZY_TILES_64: v = &plan->run_range[1]; break;
-    case MPIC_PLAN_LAZY_TILES_96: v = &plan->run_range[2]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_32: v = &plan->run_parts[0]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_64: v = &plan->run_parts[1]; break;
-    case MPIC_PLAN_KEY_BLOCK_PARTS_96: v = &plan->run_parts[2]; break;
+    case MPIC_PLAN_LAZY_TILES_64: v = &plan->lazy_range[1]; break;
+    case MPIC_PLAN_LAZY_TILES_96: v = &plan->lazy_range[2]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_32: v = &plan->kblk_parts[0]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_64: v = &plan->kblk_parts[1]; break;
+    case MPIC_PLAN_KEY_BLOCK_PARTS_96: v = &plan->kblk_parts[2]; break;
+    case MPIC_PLAN_KEY_BLOCK_ORDER: v = &plan->key_order; break;
+    case MPIC_PLAN_KEY_BLOCKS_32:
+    case MPIC_PLAN_KEY_BLOCKS_64:
+    case MPIC_PLAN_KEY_BLOCKS_96: {
+      const auto& blocks = plan->kblk[what - MPIC_PLAN_KEY_BLOCKS_32];
+      *host_ptr = reinterpret_cast<const int32_t*>(blocks.data());
+      *n = blocks.size() * 4;
+      return MPIC_OK;
+    }
     case MPIC_PLAN_ATTN_TILES:
       *host_ptr = reinterpret_cast<const int32_t*>(plan->tiles.data());
       *n = plan->tiles.size() * 8;

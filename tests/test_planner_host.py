@@ -143,13 +143,22 @@ def test_paged_plan_matches_oracle(reqs, default_k, ps, rnd):
 
 
 def _check_key_blocks(plan, want, group):
-    """lazy_rope plans: for every block size the blocks list the keys of every request, each position
-    exactly once: first the blocks of fresh rows, then the blocks of stored rows, each part in position
-    order; a block never straddles a change of source (one chunk instance, or fresh rows) and its stored
-    rows are consecutive rows of the cache; a piece of a tile that was cut along the keys owns whole
-    blocks; the two block ranges of a tile hold exactly the blocks that start inside its key range."""
-    ctx_off = want["ctx_off"]
+    """lazy_rope plans, the tables the in-place kernels walk.  The keys of a request by part and rank:
+    fresh ones, then stored ones, each in position order, every position once.  Blocks for every size:
+    each holds the next ranks of its part, of one source, and is full unless its source ends; what a row
+    sees of a block is its first (rank of the row - rank0) keys.  Tiles visit the blocks that start in
+    front of their last key, fresh ones and then stored ones; the pieces of a cut tile share them in that
+    order, every block once, none without a block, and the first one starts with the first fresh block,
+    of which every row sees a key."""
+    ctx_off, src_inst = want["ctx_off"], want["src_inst"]
+    order = plan.get("key_block_order")
+    assert len(order) == ctx_off[-1]
     tiles = plan.get("attn_tiles")
+    n_fresh = want["q_off"][1:] - want["q_off"][:-1]
+    for b in range(len(ctx_off) - 1):
+        at, inst = order[ctx_off[b]:ctx_off[b + 1]], src_inst[ctx_off[b]:ctx_off[b + 1]]
+        assert np.array_equal(at - ctx_off[b], np.concatenate([np.flatnonzero(inst < 0), np.flatnonzero(inst >= 0)]))
+        assert (inst < 0).sum() == n_fresh[b]
     for bn in (32, 64, 96):
         blocks = plan.get(f"key_blocks_{bn}")
         parts = plan.get(f"key_block_parts_{bn}")
@@ -158,41 +167,38 @@ def _check_key_blocks(plan, want, group):
         for b, (lo, mid, hi) in enumerate(parts.tolist()):
             assert lo == at_end and lo <= mid <= hi
             at_end = hi
-            n = ctx_off[b + 1] - ctx_off[b]
-            covered = np.zeros(n, dtype=np.int32)
-            for part, (x, y) in (("fresh", (lo, mid)), ("stored", (mid, hi))):
-                last = -1
-                for (pos0, n_valid, inst, req) in blocks[x:y].tolist():
-                    assert req == b and 1 <= n_valid <= bn
-                    assert (inst < 0) == (part == "fresh")
-                    assert pos0 > last, "each part lists its blocks in position order"
-                    last = pos0
-                    covered[pos0:pos0 + n_valid] += 1
-                    src = want["src_inst"][ctx_off[b] + pos0: ctx_off[b] + pos0 + n_valid]
-                    assert (src == inst).all(), "a block holds keys of one source only"
-                    if inst >= 0:
-                        rows = want["src_row"][ctx_off[b] + pos0: ctx_off[b] + pos0 + n_valid]
-                        assert (np.diff(rows) == 1).all()
-            assert (covered == 1).all(), "every position of the request in exactly one block"
+            fresh_end = ctx_off[b] + n_fresh[b]
+            for x, y, first, end in ((lo, mid, ctx_off[b], fresh_end), (mid, hi, fresh_end, ctx_off[b + 1])):
+                rank = 0
+                for (pos0, n_valid, inst, rank0) in blocks[x:y].tolist():
+                    assert rank0 == rank and 1 <= n_valid <= bn
+                    keys = order[first + rank:first + rank + n_valid]
+                    assert keys[0] == ctx_off[b] + pos0 and (src_inst[keys] == inst).all()
+                    rank += n_valid
+                    assert n_valid == bn or first + rank == end or src_inst[order[first + rank]] != inst
+                assert first + rank == end, "every key of the part in exactly one block"
         assert at_end == len(blocks)
         if bn == 32:
             continue
         ranges = plan.get(f"lazy_tiles_{bn}")
         assert len(ranges) == len(tiles)
-        for t, (f0, f1, s0, s1) in zip(tiles.tolist(), ranges.tolist()):
-            if t[3] == 0:
-                continue
-            b, key_end, key0 = t[0], t[4], t[5]
+        pieces = {}
+        for t, r in zip(tiles.tolist(), ranges.tolist()):
+            if t[3] > 0:
+                pieces.setdefault(tuple(t[:4]), []).append((t[5], t[4], r))
+        for (b, _, row0, n_rows), of in pieces.items():
+            of.sort()
             lo, mid, hi = parts[b].tolist()
-            mine = np.concatenate([blocks[lo + f0:lo + f1], blocks[mid + s0:mid + s1]])
-            rest = np.concatenate([blocks[lo:lo + f0], blocks[lo + f1:mid], blocks[mid:mid + s0], blocks[mid + s1:hi]])
-            assert len(mine) >= 1
-            assert ((mine[:, 0] >= key0) & (mine[:, 0] < key_end)).all(), "the tile's blocks start inside its key range"
-            assert not ((rest[:, 0] >= key0) & (rest[:, 0] < key_end)).any(), "no other block starts there"
-            assert mine[:, 0].min() == key0, "a tile (or piece) starts at a block start"
-            # no earlier block reaches into the range (a piece owns whole blocks)
-            before = rest[rest[:, 0] < key0]
-            assert (before[:, 0] + before[:, 1] <= key0).all()
+            last = of[-1][1] - 1           # position of the tile's last key, its last row's own
+            nf, ns = int((blocks[lo:mid, 0] <= last).sum()), int((blocks[mid:hi, 0] <= last).sum())
+            f, s = 0, 0
+            for _, _, (f0, f1, s0, s1) in of:
+                assert f0 == f and s0 == s and f1 >= f0 and s1 >= s0
+                assert f1 - f0 + s1 - s0 > 0, "no piece without a block"
+                assert s1 == s0 or f1 == nf, "fresh blocks first"
+                f, s = f1, s1
+            assert (f, s) == (nf, ns), "the pieces share the blocks of their tile"
+            assert of[0][2][:2] != [0, 0] and blocks[lo, 0] <= want["q_pos"][want["q_off"][b] + row0 // group]
 
 
 @pytest.mark.parametrize("cfg", [2, 3, 4, 5])
@@ -213,6 +219,7 @@ def test_key_blocks_of_lazy_plans_on_benchmark_layouts(cfg):
     plain = mpic.Plan(_ctx(sh.n_q_heads, sh.n_kv_heads, sh.head_dim, mpic.MPIC_BF16, sh.rope_theta, sh.page_size), reqs,
                       sh.default_k, tables, pool)
     assert len(plain.get("key_blocks_64")) == 0 and len(plain.get("lazy_tiles_96")) == 0
+    assert len(plain.get("key_block_order")) == 0
 
 
 @settings(max_examples=80, deadline=None)
@@ -224,6 +231,22 @@ def test_key_blocks_of_lazy_plans_on_random_layouts(reqs, default_k, heads):
     want = build_plan(reqs, default_k)
     got = mpic.Plan(ctx, reqs, default_k)
     _check_key_blocks(got, want, hq // hkv)
+
+
+@pytest.mark.parametrize("heads", [(7, 1), (28, 4), (32, 8), (8, 8)])
+@pytest.mark.parametrize("stored", [150, 1500, 5000])
+def test_key_blocks_of_cut_and_listed_lazy_plans(heads, stored):
+    """Long enough to be cut along the keys: a recompute set named token by token all over a chunk (its
+    stored rows fall apart into short runs), a recomputed chunk between stored ones, requests of unequal
+    length."""
+    rng = np.random.default_rng(stored)
+    pick = lambda n: tuple(sorted(rng.choice(stored, size=n, replace=False).tolist()))
+    reqs = [[("chunk", 0, stored, pick(stored // 20)), ("text", 1)],
+            [("chunk", 1, 97, (96,)), ("chunk", 0, stored, pick(stored // 3)), ("chunk", 1, 97, 97), ("chunk", 0, stored, 0), ("text", 5)],
+            [("chunk", 1, 97, 0)]]
+    got = mpic.Plan(mpic.Context(*heads, 128, mpic.MPIC_BF16, 1e4, 0, 0, 0, 1), reqs, 0)
+    _check_key_blocks(got, build_plan(reqs, 0), heads[0] // heads[1])
+    assert (got.get("attn_tiles")[:, 6] >= 0).any() or stored == 150
 
 
 def test_rope_tables_are_float64_accurate():
