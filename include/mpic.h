@@ -251,8 +251,12 @@ int mpic_plan_get_rope(const mpic_plan* plan, const float** cos_tab, const float
 int mpic_plan_get_fresh_rope(const mpic_plan* plan, const int32_t** table_row, const float** cos_tab,
                              const float** sin_tab, size_t* n_rows);
 
-/* Destroy a plan (device copies included).  The caller must have synchronised every
- * stream that still uses it.  NULL is allowed. */
+/* Destroy a plan.  NULL is allowed.  Work that earlier calls enqueued with the plan may still
+ * run; graphs that captured such calls must not be launched any more.  The context keeps up to
+ * four device blocks of destroyed plans (16 MB each at most) for its next plans, until it is
+ * destroyed or an allocation for a plan fails without them; such a plan goes without a wait.
+ * The blocks of other plans (larger ones, ones that were used under capture, on
+ * hipStreamPerThread or on more than three streams) are freed, which waits for the GPU. */
 void mpic_plan_destroy(mpic_plan* plan);
 
 /*

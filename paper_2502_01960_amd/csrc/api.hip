@@ -58,10 +58,9 @@ int ensure_attn_ws(mpic_ctx* ctx, const mpic_plan* p) {
 int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   if (p->dev.block) {
     if (p->dev.device != ctx->device) return fail(ctx, MPIC_ERR_INVALID, "plan lives on another GPU");
-    p->spare_blocks->used(&p->use, stream);
+    p->use.add(stream);
     return MPIC_OK;
   }
-  ctx->spare_blocks->mark(stream);
   const int rc = ensure_attn_ws(ctx, p);
   if (rc != MPIC_OK) return rc;
   const size_t n = p->n_ctx, nq = p->n_q, B = p->n_requests;
@@ -136,28 +135,42 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   image.resize(image.size() + 256, 0);
 
   // A plan is made for every request, so nothing here may wait for the requests before it: the block
-  // of an earlier plan is used again if one fits (no work reads it any more, see SpareBlocks), and
-  // the tables go up on a library stream.  hipFree and a copy on the default stream drained the GPU
-  // twice per request (four layers of a 2.6K-token request with its plan: 282 -> 193 us).
+  // of an earlier plan is used again if one fits (see plan_blocks.h), and the tables go up on a library
+  // stream unless the caller's is idle.  hipFree and a copy on the default stream drained the GPU twice
+  // per request (four layers of a 2.6K-token request with its plan, request after request: 282 -> 193 us);
+  // a request that finds the GPU idle is better off with the copy on its own stream, whose first launch
+  // then follows without a wait (the same with every request waited for: 328 us over the side stream,
+  // 288 over its own).
   size_t bytes = 0;
-  char* base = static_cast<char*>(ctx->spare_blocks->take(image.size(), &bytes));
+  char* base = static_cast<char*>(ctx->spare_blocks->take(image.size(), &bytes, stream));
   if (!base) {
-    bytes = (image.size() + 0xffff) / 0x10000 * 0x10000;  // plans of similar requests fit each other's blocks
-    if (hipMalloc(reinterpret_cast<void**>(&base), bytes) != hipSuccess) {
+    bytes = SpareBlocks::size_for(image.size());
+    auto allocate = [&]() {
+      if (hipMalloc(reinterpret_cast<void**>(&base), bytes) == hipSuccess) return true;
       (void)hipGetLastError();
-      return fail(ctx, MPIC_ERR_OOM, "device allocation of the plan failed");
+      return false;
+    };
+    bool ok = allocate();
+    if (!ok) {  // as little as the plan needs, and with nothing kept beside it
+      bytes = image.size();
+      ok = allocate() || (ctx->spare_blocks->trim([](void* kept) { (void)hipFree(kept); }) && allocate());
     }
+    if (!ok) return fail(ctx, MPIC_ERR_OOM, "device allocation of the plan failed");
   }
-  // (the side stream is there already; chunks on their way over it must not delay the plan, and
-  // a stream of its own costs 80 us to create)
   hipError_t e = hipSuccess;
-  hipStream_t up = ctx->upload_stream;
-  if (!up) {
-    up = ctx->side_stream;
-    if (hipStreamQuery(up) != hipSuccess) {
-      (void)hipGetLastError();
-      e = hipStreamCreateWithFlags(&ctx->upload_stream, hipStreamNonBlocking);
-      up = ctx->upload_stream;
+  hipStream_t up = stream;
+  if (!trackable(stream) || hipStreamQuery(stream) != hipSuccess) {
+    // (the side stream is there already; chunks on their way over it must not delay the plan, and
+    // a stream of its own costs 80 us to create)
+    (void)hipGetLastError();
+    up = ctx->upload_stream;
+    if (!up) {
+      up = ctx->side_stream;
+      if (hipStreamQuery(up) != hipSuccess) {
+        (void)hipGetLastError();
+        e = hipStreamCreateWithFlags(&ctx->upload_stream, hipStreamNonBlocking);
+        up = ctx->upload_stream;
+      }
     }
   }
   if (e == hipSuccess) e = hipMemcpyAsync(base, image.data(), image.size(), hipMemcpyHostToDevice, up);
@@ -199,7 +212,7 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   d.device = ctx->device;
   p->dev = d;
   p->spare_blocks = ctx->spare_blocks;
-  p->spare_blocks->used(&p->use, stream);
+  p->use.add(stream);
   return MPIC_OK;
 }
 
@@ -281,15 +294,22 @@ extern "C" void mpic_destroy(mpic_ctx* ctx) {
 
 extern "C" void mpic_plan_destroy(mpic_plan* plan) {
   if (!plan) return;
-  if (plan->dev.block && !plan->spare_blocks->give(plan->dev.block, plan->dev.block_bytes, plan->use)) {
+  if (plan->dev.block) {
     int cur = -1;
     (void)hipGetDevice(&cur);
-    (void)hipSetDevice(plan->dev.device);
-    (void)hipFree(plan->dev.block);
-    if (cur >= 0) (void)hipSetDevice(cur);
+    if (cur != plan->dev.device) (void)hipSetDevice(plan->dev.device);
+    void* replaced = nullptr;
+    if (!plan->spare_blocks->give(plan->dev.block, plan->dev.block_bytes, plan->use, &replaced)) (void)hipFree(plan->dev.block);
+    if (replaced) (void)hipFree(replaced);
+    if (cur >= 0 && cur != plan->dev.device) (void)hipSetDevice(cur);
   }
   delete plan;
 }
+
+#ifdef MPIC_PROBE_BUILD
+// How many plans of a context have used the block of an earlier one, for tests.
+extern "C" int64_t mpic_probe_blocks_handed_on(const mpic_ctx* ctx) { return ctx ? static_cast<int64_t>(ctx->spare_blocks->handed_out()) : -1; }
+#endif
 
 extern "C" int mpic_assemble_kv(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* srcs,
                                 int32_t n_srcs, const void* fresh_k, const void* fresh_v,
@@ -693,7 +713,7 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
                                          "e.g. mpic_assemble_kv, uploads it)");
     if (ctx->device != dev || plan->dev.device != dev)
       return fail(ctx, MPIC_ERR_INVALID, "decode_attn_static: context and plan live on another GPU than the current one");
-    plan->spare_blocks->used(&plan->use, static_cast<hipStream_t>(stream_));
+    plan->use.add(static_cast<hipStream_t>(stream_));
   } else {
     rc = mpic::bind_device(ctx);
     if (rc != MPIC_OK) return rc;

@@ -5,11 +5,11 @@
 
 #include <cstdint>
 #include <memory>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "mpic.h"
+#include "plan_blocks.h"
 
 namespace mpic {
 
@@ -83,100 +83,6 @@ struct PlanDevice {
   void* block = nullptr;  // the single allocation all of the above point into
   size_t block_bytes = 0;
   int device = -1;
-};
-
-// Where the work that reads a plan's tables was enqueued.
-struct PlanUse {
-  hipStream_t stream = nullptr;
-  uint64_t last = 0;     // number of the last use, counted over the context; 0 = none
-  bool one_stream = true;  // all of it on `stream`, none of it under capture
-};
-
-// Device blocks of destroyed plans, kept for the next plans of their context.  A block is kept only
-// when all work that reads it is known to be done: the first use of the next plan records a marker
-// on its stream, and the destruction of a plan that was used on that stream alone, before the
-// marker, waits for the marker -- for the plan's own work, that is, where hipFree waits for
-// everything on the GPU.  Plans hold the pool too: one that outlives its context gives its block
-// back to the runtime.
-class SpareBlocks {
- public:
-  // The smallest kept block of at least `bytes`, or null.
-  void* take(size_t bytes, size_t* have) {
-    std::lock_guard<std::mutex> lock(mu_);
-    int best = -1;
-    for (int i = 0; i < n_; ++i)
-      if (blocks_[i].bytes >= bytes && (best < 0 || blocks_[i].bytes < blocks_[best].bytes)) best = i;
-    if (best < 0) return nullptr;
-    const Block b = blocks_[best];
-    blocks_[best] = blocks_[--n_];
-    *have = b.bytes;
-    return b.ptr;
-  }
-  // One more use of a plan on `stream` (whose capture state is looked up here).
-  void used(PlanUse* u, hipStream_t stream) {
-    std::lock_guard<std::mutex> lock(mu_);
-    u->one_stream = u->one_stream && (u->last == 0 || u->stream == stream) && recordable(stream);
-    u->stream = stream;
-    u->last = ++n_uses_;
-  }
-  // Mark the end of everything enqueued on `stream` so far.
-  void mark(hipStream_t stream) {
-    std::lock_guard<std::mutex> lock(mu_);
-    marked_ = 0;
-    if (!recordable(stream)) return;
-    if (!marker_ && hipEventCreateWithFlags(&marker_, hipEventDisableTiming) != hipSuccess) marker_ = nullptr;
-    if (!marker_ || hipEventRecord(marker_, stream) != hipSuccess) {
-      (void)hipGetLastError();
-      return;
-    }
-    marked_ = n_uses_;
-    marked_stream_ = stream;
-  }
-  // False: not kept, the caller frees it.
-  bool give(void* ptr, size_t bytes, const PlanUse& u) {
-    std::lock_guard<std::mutex> lock(mu_);
-    if (closed_ || n_ == kMax || bytes > kMaxBytes) return false;
-    if (u.last > 0) {
-      if (!u.one_stream || u.last > marked_ || u.stream != marked_stream_) return false;
-      if (hipEventSynchronize(marker_) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-      }
-    }
-    blocks_[n_++] = Block{ptr, bytes};
-    return true;
-  }
-  template <typename Free>
-  void close(Free&& free) {
-    std::lock_guard<std::mutex> lock(mu_);
-    for (int i = 0; i < n_; ++i) free(blocks_[i].ptr);
-    n_ = 0;
-    closed_ = true;
-    if (marker_) (void)hipEventDestroy(marker_);
-    marker_ = nullptr;
-  }
-
- private:
-  static bool recordable(hipStream_t stream) {
-    if (stream == hipStreamPerThread) return false;  // one handle, a stream per thread
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st == hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
-  }
-  static constexpr int kMax = 4;
-  static constexpr size_t kMaxBytes = size_t{16} << 20;
-  struct Block {
-    void* ptr = nullptr;
-    size_t bytes = 0;
-  };
-  std::mutex mu_;
-  Block blocks_[kMax];
-  int n_ = 0;
-  bool closed_ = false;
-  uint64_t n_uses_ = 0, marked_ = 0;  // uses so far, uses before the marker (0 = no marker)
-  hipEvent_t marker_ = nullptr;
-  hipStream_t marked_stream_ = nullptr;
 };
 
 }  // namespace mpic

@@ -508,7 +508,10 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
 
   int rc = mpic::bind_device(ctx);
   if (rc != MPIC_OK) return rc;
-  if (!ctx->link_stream) MPIC_HIP(ctx, hipStreamCreateWithFlags(&ctx->link_stream, hipStreamNonBlocking));
+  if (!ctx->link_stream) {
+    MPIC_HIP(ctx, hipStreamCreateWithFlags(&ctx->link_stream, hipStreamNonBlocking));
+    ctx->spare_blocks->own(ctx->link_stream);
+  }
   while (ctx->ev_layer.size() < 2 * static_cast<size_t>(n_layers) + 1) {
     hipEvent_t ev;
     MPIC_HIP(ctx, hipEventCreateWithFlags(&ev, hipEventDisableTiming));

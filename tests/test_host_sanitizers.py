@@ -47,3 +47,19 @@ def test_store_and_layer_pipeline_under_sanitizers(tmp_path, sanitizer):
     r = subprocess.run([exe, str(disk)], capture_output=True, text=True, timeout=600, env=env)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "sanitized store run ok" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="needs g++ and the ROCm headers")
+def test_plan_blocks_are_reused_and_never_too_early(tmp_path):
+    """The pool of plan blocks with streams and events as stand-ins: the orders in which plans come
+    and go, plans that grow, streams that are gone, and random sequences."""
+    exe = str(tmp_path / "plan_blocks")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
+           os.path.join(ROOT, "tests", "native", "plan_blocks.cpp"), "-lpthread", "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, text=True, timeout=600)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", LD_PRELOAD="")
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600, env=env)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "plan blocks ok" in r.stdout

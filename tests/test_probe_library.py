@@ -16,7 +16,7 @@ PROBE_OPTION_ABLATE = 1000
 
 def test_product_library_has_no_probe_code():
     lib = ctypes.CDLL(mpic.lib_path())
-    for name in ("mpic_probe_mfma", "mpic_probe_read"):
+    for name in ("mpic_probe_mfma", "mpic_probe_read", "mpic_probe_blocks_handed_on"):
         assert not hasattr(lib, name), name
     ctx = mpic.Context(8, 2, 128, mpic.MPIC_BF16, 1e4)
     with pytest.raises(mpic.MpicError):
@@ -92,3 +92,66 @@ def test_probe_entry_points_run_and_mask_zero_is_the_product_kernel():
         plan.close()
         ctx.close()
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", ["destroyed_first", "next_first", "side_stream", "captured"])
+def test_plans_use_the_blocks_of_earlier_ones(order):
+    """Request after request on one context, each with a plan of its own: in the usual orders every plan
+    after the first few uses an earlier one's block, one whose plan was captured goes back to the
+    runtime, and the outputs are those of the first request, bit for bit."""
+    import torch
+    import workloads
+    if not os.path.exists(PROBE):
+        pytest.skip("probe library not built")
+    dev = torch.device("cuda:0")
+    spec = importlib.util.spec_from_file_location("mpic_probe_blocks_binding", os.path.join(ROOT, "paper_2502_01960_amd", "binding.py"))
+    pb = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(pb)
+    pb.lib_path = lambda: PROBE
+    sh = workloads.shape(3)
+    requests = [[("text", 40), ("chunk", 0, 300, None), ("text", 31)]]
+    n_ctx, k = 371, 16
+    ctx = pb.Context(sh.n_q_heads, sh.n_kv_heads, sh.head_dim, pb.MPIC_BF16, sh.rope_theta)
+    handed_on = pb.load_library().mpic_probe_blocks_handed_on
+    handed_on.restype, handed_on.argtypes = ctypes.c_int64, [ctypes.c_void_p]
+    srcs = [tuple(t.to(dev) for t in workloads.gen_chunk(sh, 0, 0, 300))]
+    q, fk, fv = (t.to(dev) for t in workloads.gen_fresh(sh, 0, 0, 40 + 31 + k))
+    streams = [torch.cuda.default_stream(), torch.cuda.Stream()]
+    n, last, first = 12, None, None
+    torch.cuda.synchronize()
+    for i in range(n):
+        if order == "destroyed_first" and last is not None:
+            torch.cuda.synchronize()
+            last.close()
+        plan = pb.Plan(ctx, requests, k)
+        stream = streams[1] if order == "side_stream" else streams[0]
+        kc, vc, out = (torch.zeros(s, dtype=torch.bfloat16, device=dev) for s in
+                       ((n_ctx, sh.n_kv_heads, sh.head_dim), (n_ctx, sh.n_kv_heads, sh.head_dim), tuple(q.shape)))
+        stream.wait_stream(streams[0])
+        with torch.cuda.stream(stream):
+            pb.mpic_assemble_kv(ctx.handle, plan.handle, srcs, fk, fv, kc, vc)
+            attend = lambda: pb.mpic_selective_attn(ctx.handle, plan.handle, q, kc, vc, sh.softmax_scale, out, None)
+            if order == "captured":
+                torch.cuda.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph):
+                    attend()
+                graph.replay()
+            else:
+                attend()
+        if order != "destroyed_first" and last is not None:
+            last.close()          # (its work is done or not)
+        last = plan
+        torch.cuda.synchronize()
+        if first is None:
+            first = out.clone()
+        assert torch.equal(out.view(torch.int16), first.view(torch.int16))
+    assert torch.isfinite(first.float()).all() and first.float().abs().max() > 0
+    reused = handed_on(ctx.handle)
+    if order == "captured":
+        assert reused == 0
+    else:
+        assert reused >= n - 3, reused
+    last.close()
+    ctx.close()
