@@ -337,9 +337,14 @@ int mpic_assemble_kv_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src*
  * sees.  On lazy_rope contexts a block holds fresh rows, or stored rows of one chunk, that
  * need not be neighbours.
  * Small and medium batches are cut along the keys as well as along the rows (see
- * MPIC_PLAN_ATTN_TILES); the partial results live in a workspace owned by the context,
- * allocated by the first call that brings a plan to the GPU and grown by a plan that needs
- * more, so calls of one context that use it must not overlap on different streams.
+ * MPIC_PLAN_ATTN_TILES); the partial results live in a workspace that the context keeps for
+ * the stream, grown by a plan that needs more (what it outgrew stays until mpic_destroy, for
+ * graphs that captured it, unless memory is short).  mpic_assemble_kv tries to provide it when
+ * it brings a plan to the GPU, so that the attention can be captured; if it cannot be had, only
+ * the attention call fails.  Calls of one context may overlap on up to four streams; on a fifth
+ * the call waits for the GPU to be idle.  A graph uses the workspace of the stream it was
+ * captured on, or the largest one if that stream had none, and must not run beside other
+ * calls that use it.
  * Errors: MPIC_ERR_INVALID, MPIC_ERR_OOM (workspace), MPIC_ERR_HIP.
  */
 int mpic_selective_attn(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q, int64_t n_fresh_rows,
@@ -416,7 +421,7 @@ int mpic_selective_attn_link_next(mpic_ctx* ctx, mpic_plan* plan, const void* fr
  *                     no new_k) gets zeros and lse = -infinity
  *   lse               device float [B][Hq], written; may be NULL
  * Partial results of the key splits live in a workspace owned by the context, allocated on
- * the first call and grown (with a device synchronisation) when a later call needs more;
+ * the first call and grown when a later call needs more (what it outgrew stays, as above);
  * calls on one context must therefore not overlap on different streams.
  * Errors: MPIC_ERR_INVALID, MPIC_ERR_OOM (workspace), MPIC_ERR_HIP.
  */
@@ -438,7 +443,7 @@ int mpic_decode_attn_in_place(mpic_ctx* ctx, mpic_plan* plan, const void* q, con
 /*
  * mpic_decode_attn for callers that cannot allocate: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
- * result, but the partial results of the key splits live in a file-scope device array of the
+ * result (F32: up to rounding if the splits do not fit the array, which then take one), but the partial results of the key splits live in a file-scope device array of the
  * library (8 MiB per GPU, held until the process ends) instead of the context's workspace,
  * and the call makes no hipMalloc, hipFree or other allocating call:
  *   - the context must be bound to the current GPU and the plan already uploaded to it, which

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <new>
 #include <string>
 
@@ -29,27 +30,76 @@ namespace {
 
 constexpr size_t kTablePad = 128;
 
-// Workspace for the partial results of a plan's cut tiles.  It grows with the first call that brings
-// the plan to the GPU, at least twofold (so that what it replaces is never more than what it holds);
-// the attention calls themselves find it in place and can be captured.
-int ensure_attn_ws(mpic_ctx* ctx, const mpic_plan* p) {
-  const size_t need = static_cast<size_t>(p->n_parts) * kAttnTileRows * (ctx->cfg.head_dim + 1) * sizeof(float);
-  if (ctx->cfg.dtype != MPIC_BF16 || need <= ctx->attn_ws_bytes) return MPIC_OK;
-  if (ctx->attn_ws) ctx->attn_ws_old.reserve(ctx->attn_ws_old.size() + 1);
-  void* ws = nullptr;
-  size_t bytes = std::max(need, 2 * ctx->attn_ws_bytes);
-  if (hipMalloc(&ws, bytes) != hipSuccess) {
+// Give `w` room for `need` bytes, at least twofold so that what is kept of the ones it outgrew is no more
+// than what it holds.  Work in flight and captured graphs may still use the old memory, which therefore
+// stays -- unless the new cannot be had beside it and is `needed`: then what the plans keep goes, and if
+// that does not help the old memory itself, once the GPU is idle.
+bool grow(mpic_ctx* ctx, Scratch* w, size_t need, bool needed = true) {
+  if (need <= w->bytes) return true;
+  if (w->ptr) ctx->replaced_scratch.reserve(ctx->replaced_scratch.size() + 1);
+  void* ptr = nullptr;
+  auto allocate = [&](size_t bytes) {
+    if (hipMalloc(&ptr, bytes) == hipSuccess) return bytes;
     (void)hipGetLastError();
-    bytes = need;
-    if (hipMalloc(&ws, bytes) != hipSuccess) {
+    return size_t{0};
+  };
+  size_t got = allocate(std::max(need, 2 * w->bytes));
+  if (!got && need < 2 * w->bytes) got = allocate(need);
+  if (!got && needed && ctx->spare_blocks->trim([](void* kept) { (void)hipFree(kept); })) got = allocate(need);
+  if (!got && needed && w->ptr) {
+    if (hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
-      return fail(ctx, MPIC_ERR_OOM, "selective_attn: workspace allocation failed");
+      return false;
+    }
+    (void)hipFree(w->ptr);
+    w->ptr = nullptr;
+    w->bytes = 0;
+    got = allocate(need);
+  }
+  if (!got) return false;
+  if (w->ptr) ctx->replaced_scratch.push_back(w->ptr);
+  w->ptr = ptr;
+  w->bytes = got;
+  return true;
+}
+
+size_t attn_ws_need(const mpic_ctx* ctx, const mpic_plan* p) {
+  return ctx->cfg.dtype == MPIC_BF16 ? static_cast<size_t>(p->n_parts) * kAttnTileRows * (ctx->cfg.head_dim + 1) * sizeof(float) : 0;
+}
+
+// The workspace of the stream's attention calls, or the largest that no stream has yet (null: none left).
+Scratch* find_attn_ws(mpic_ctx* ctx, hipStream_t stream) {
+  Scratch* w = nullptr;
+  for (Scratch& x : ctx->attn_ws) {
+    if (x.claimed && x.stream == stream) return &x;
+    if (!x.claimed && (!w || x.bytes > w->bytes)) w = &x;
+  }
+  return w;
+}
+
+// Workspace of the cut tiles of a plan for an attention call on `stream`, null if it cannot be had.  Every
+// stream has its own, so that calls on different streams do not meet in it: which plans are cut is the
+// planner's business, and no caller should have to order its streams for it.  With more streams than
+// workspaces one changes hands, once the GPU is idle.  A call that is being captured on a stream without
+// one uses the largest there is.
+Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
+  const size_t need = attn_ws_need(ctx, p);
+  Scratch* w = find_attn_ws(ctx, stream);
+  if (!(w && w->claimed)) {
+    if (!trackable(stream)) {
+      w = &*std::max_element(std::begin(ctx->attn_ws), std::end(ctx->attn_ws),
+                             [](const Scratch& x, const Scratch& y) { return x.bytes < y.bytes; });
+    } else {
+      if (!w) {
+        if (hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
+        w = &ctx->attn_ws[ctx->next_attn_ws];
+        ctx->next_attn_ws = (ctx->next_attn_ws + 1) % kAttnWorkspaces;
+      }
+      w->claimed = true;
+      w->stream = stream;
     }
   }
-  if (ctx->attn_ws) ctx->attn_ws_old.push_back(ctx->attn_ws);
-  ctx->attn_ws = ws;
-  ctx->attn_ws_bytes = bytes;
-  return MPIC_OK;
+  return grow(ctx, w, need) ? w : nullptr;
 }
 
 // Copy the integer maps, rotary tables and tile list to the GPU (once per plan): the tables
@@ -61,8 +111,6 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
     p->use.add(stream);
     return MPIC_OK;
   }
-  const int rc = ensure_attn_ws(ctx, p);
-  if (rc != MPIC_OK) return rc;
   const size_t n = p->n_ctx, nq = p->n_q, B = p->n_requests;
   // byte offset of every context row in 16-byte units (saves the attention kernel a
   // 64-bit multiply per staged row); fits 32 bits for context buffers below 64 GiB
@@ -284,9 +332,10 @@ extern "C" void mpic_destroy(mpic_ctx* ctx) {
       (void)hipStreamDestroy(ctx->upload_stream);
     }
     ctx->spare_blocks->close([](void* p) { (void)hipFree(p); });
-    if (ctx->decode_ws) (void)hipFree(ctx->decode_ws);
-    if (ctx->attn_ws) (void)hipFree(ctx->attn_ws);
-    for (void* ws : ctx->attn_ws_old) (void)hipFree(ws);
+    if (ctx->decode_ws.ptr) (void)hipFree(ctx->decode_ws.ptr);
+    for (const mpic::Scratch& w : ctx->attn_ws)
+      if (w.ptr) (void)hipFree(w.ptr);
+    for (void* p : ctx->replaced_scratch) (void)hipFree(p);
     if (cur >= 0) (void)hipSetDevice(cur);
   }
   delete ctx;
@@ -355,9 +404,14 @@ int mpic::assemble_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* s
   if (any_mapped) ctx->background_seen = true;  // a launch that lasts as long as the transfer runs beside others
   int rc = mpic::bind_device(ctx);
   if (rc != MPIC_OK) return rc;
-  rc = mpic::upload_plan(ctx, plan, static_cast<hipStream_t>(stream_));
-  if (rc != MPIC_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
+  const bool first_use = !plan->dev.block;
+  rc = mpic::upload_plan(ctx, plan, stream);
+  if (rc != MPIC_OK) return rc;
+  // The attention call that most likely follows on this stream can be captured if its workspace is there.
+  // Nothing is lost if it cannot be had yet.
+  if (first_use && stream != ctx->link_stream)
+    if (mpic::Scratch* w = mpic::find_attn_ws(ctx, stream)) (void)mpic::grow(ctx, w, mpic::attn_ws_need(ctx, plan), false);
   const mpic_config& c = ctx->cfg;
   const size_t elem = c.dtype == MPIC_F32 ? 4 : 2;
   const size_t row_bytes = static_cast<size_t>(c.n_kv_heads) * c.head_dim * elem;
@@ -615,7 +669,9 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   a.n_requests = plan->n_requests;
   if (c.dtype == MPIC_BF16 && plan->n_parts > 0) {
     const size_t slots = static_cast<size_t>(plan->n_parts) * mpic::kAttnTileRows;
-    a.ws_o = static_cast<float*>(ctx->attn_ws);
+    const mpic::Scratch* w = mpic::attn_workspace(ctx, plan, static_cast<hipStream_t>(stream_));
+    if (!w) return fail(ctx, MPIC_ERR_OOM, "selective_attn: workspace allocation failed");
+    a.ws_o = static_cast<float*>(w->ptr);
     a.ws_lse = a.ws_o + slots * c.head_dim;
     a.merges = plan->dev.merges;
     a.n_merges = static_cast<int32_t>(plan->merges.size());
@@ -756,17 +812,9 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
     if (need > have)
       return fail(ctx, MPIC_ERR_UNSUPPORTED, "decode_attn_static: the partial results of this batch (" + std::to_string(need) +
                                              " bytes) exceed the static scratch array (" + std::to_string(have) + " bytes)");
-  } else if (need > ctx->decode_ws_bytes) {
-    // growing the workspace is rare (first call / larger batch): drain what may still read it
-    MPIC_HIP(ctx, hipDeviceSynchronize());
-    if (ctx->decode_ws) MPIC_HIP(ctx, hipFree(ctx->decode_ws));
-    ctx->decode_ws = nullptr;
-    ctx->decode_ws_bytes = 0;
-    if (hipMalloc(&ctx->decode_ws, need) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(ctx, MPIC_ERR_OOM, "decode_attn: workspace allocation failed");
-    }
-    ctx->decode_ws_bytes = need;
+  } else {
+    if (!mpic::grow(ctx, &ctx->decode_ws, need)) return fail(ctx, MPIC_ERR_OOM, "decode_attn: workspace allocation failed");
+    ws = static_cast<float*>(ctx->decode_ws.ptr);
   }
   mpic::DecodeArgs a{};
   a.ctx_off = plan->dev.ctx_off;
@@ -779,7 +827,6 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
   a.v_ctx = v_ctx;
   a.out = out;
   a.lse = lse;
-  if (!static_scratch) ws = static_cast<float*>(ctx->decode_ws);
   a.ws_o = ws;
   a.ws_lse = a.ws_o + rows * n_splits * c.head_dim;
   a.scale = static_cast<float>(softmax_scale);

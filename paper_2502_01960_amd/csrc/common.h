@@ -85,6 +85,15 @@ struct PlanDevice {
   int device = -1;
 };
 
+// Device memory for partial results, grown on demand.
+struct Scratch {
+  void* ptr = nullptr;
+  size_t bytes = 0;
+  bool claimed = false;  // by the work of `stream`
+  hipStream_t stream = nullptr;
+};
+constexpr int kAttnWorkspaces = 4;
+
 }  // namespace mpic
 
 struct mpic_ctx {
@@ -113,14 +122,12 @@ struct mpic_ctx {
   int32_t attn_block_keys = 0;
   int32_t attn_ablate = 0;  // probe builds only, see kAblate*
   bool background_seen = false;
-  // partial results of the decode step (one per key split), grown on demand
-  void* decode_ws = nullptr;
-  size_t decode_ws_bytes = 0;
-  // partial results of prefill tiles that were cut along the keys, grown when a plan needs more.
-  // Smaller ones it replaced stay until the end: captured graphs may still point to them.
-  void* attn_ws = nullptr;
-  size_t attn_ws_bytes = 0;
-  std::vector<void*> attn_ws_old;
+  // partial results of the decode step (one per key split), and of prefill tiles that were cut along
+  // the keys (one workspace per stream that attends, see attn_workspace)
+  mpic::Scratch decode_ws;
+  mpic::Scratch attn_ws[mpic::kAttnWorkspaces];
+  int32_t next_attn_ws = 0;            // the one that changes hands next
+  std::vector<void*> replaced_scratch;  // smaller ones that were outgrown: captured graphs may still point to them
   // plan tables: blocks kept for reuse, and the stream that uploads them (see upload_plan)
   std::shared_ptr<mpic::SpareBlocks> spare_blocks = std::make_shared<mpic::SpareBlocks>();
   hipStream_t upload_stream = nullptr;

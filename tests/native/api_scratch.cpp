@@ -1,0 +1,182 @@
+// Host-only exercise of the scratch memory behind the entry points (built by
+// tests/test_host_sanitizers.py with g++ from plan.cpp, api.hip and the stand-ins below): who
+// allocates it, what happens when it cannot be had, which calls share it.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <vector>
+
+#include "common.h"
+
+// ---- stand-ins for the HIP runtime: host memory, a limit on it, streams that may be captured ----
+namespace {
+size_t in_use = 0, limit = SIZE_MAX;
+std::map<void*, size_t> sizes;
+int n_syncs = 0;
+struct Stream { bool capturing = false; };
+bool capturing_any = false;
+Stream null_stream;
+Stream* of(hipStream_t s) { return s ? reinterpret_cast<Stream*>(s) : &null_stream; }
+}  // namespace
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  if (capturing_any) return hipErrorStreamCaptureUnsupported;
+  if (in_use + n > limit) return hipErrorOutOfMemory;
+  *p = std::malloc(n ? n : 1);
+  sizes[*p] = n;
+  in_use += n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  in_use -= sizes.at(p);
+  sizes.erase(p);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = reinterpret_cast<hipEvent_t>(new int(0)); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<int*>(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = reinterpret_cast<hipStream_t>(new Stream()); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { delete of(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned int) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  *st = of(s)->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipDeviceSynchronize(void) { ++n_syncs; return capturing_any ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stub"; }
+}
+
+namespace mpic {
+AttnArgs last_attn;
+DecodeArgs last_decode;
+hipError_t launch_assemble(int, const AssembleArgs&, const AssembleSrcTable&, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_bf16(const AttnArgs& a, const AssembleArgs*, const AssembleSrcTable*, const LazyRefs*, hipStream_t) {
+  last_attn = a;
+  return hipSuccess;
+}
+hipError_t launch_attn_f32(const AttnArgs& a, int64_t, const LazyRefs*, hipStream_t) { last_attn = a; return hipSuccess; }
+hipError_t launch_decode(int, const DecodeArgs& a, const LazyRefs*, hipStream_t) { last_decode = a; return hipSuccess; }
+hipError_t decode_static_scratch(float**, size_t*) { return hipErrorInvalidDevice; }
+}  // namespace mpic
+
+#define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); std::exit(1); } } while (0)
+
+namespace {
+alignas(16) char any[16];  // stands for every data buffer: the launches are stand-ins
+mpic_ctx* context(int dtype) {
+  mpic_config cfg{};
+  cfg.n_q_heads = 8;
+  cfg.n_kv_heads = 8;
+  cfg.head_dim = 128;
+  cfg.dtype = dtype;
+  cfg.rope_theta = 1e4;
+  mpic_ctx* ctx = nullptr;
+  CHECK(mpic_create(&ctx, &cfg) == MPIC_OK);
+  return ctx;
+}
+mpic_plan* plan_of(mpic_ctx* ctx, int len) {  // one request of text
+  const int32_t seg_off[2] = {0, 1};
+  mpic_segment seg{};
+  seg.len = len;
+  mpic_plan* p = nullptr;
+  CHECK(mpic_plan_create(ctx, 1, seg_off, &seg, 0, nullptr, nullptr, 0, &p) == MPIC_OK);
+  return p;
+}
+int assemble(mpic_ctx* c, mpic_plan* p, Stream* s) {
+  return mpic_assemble_kv(c, p, nullptr, 0, any, any, p->n_q, any, any, p->n_ctx, s);
+}
+int attend(mpic_ctx* c, mpic_plan* p, Stream* s) {
+  return mpic_selective_attn(c, p, any, p->n_q, any, any, p->n_ctx, 0.1, any, nullptr, s);
+}
+int decode(mpic_ctx* c, mpic_plan* p, Stream* s) {
+  return mpic_decode_attn(c, p, any, nullptr, nullptr, any, any, p->n_ctx, 0.1, any, nullptr, s);
+}
+size_t ws_of(const mpic_plan* p) { return static_cast<size_t>(p->n_parts) * mpic::kAttnTileRows * 129 * sizeof(float); }
+void capture(Stream* s, bool on) { s->capturing = capturing_any = on; }
+}  // namespace
+
+int main() {
+  const size_t mb = size_t{1} << 20;
+  Stream s[7];
+  {  // without room for the workspace a plan can be linked and decoded; only its attention fails
+    mpic_ctx* c = context(MPIC_BF16);
+    mpic_plan* p = plan_of(c, 3000);
+    CHECK(p->n_parts > 0 && ws_of(p) > 4 * mb);
+    limit = in_use + 2 * mb;
+    CHECK(assemble(c, p, &s[0]) == MPIC_OK);
+    CHECK(decode(c, p, &s[0]) == MPIC_OK);
+    CHECK(attend(c, p, &s[0]) == MPIC_ERR_OOM);
+    limit = SIZE_MAX;
+    CHECK(attend(c, p, &s[0]) == MPIC_OK);
+    // a larger plan finds room for its workspace only if the old one goes, once the GPU is idle
+    mpic_plan* q = plan_of(c, 9000);
+    CHECK(ws_of(q) > ws_of(p));
+    limit = in_use + ws_of(q) - ws_of(p) + mb;
+    const int syncs = n_syncs;
+    CHECK(assemble(c, q, &s[0]) == MPIC_OK && n_syncs == syncs);
+    CHECK(attend(c, q, &s[0]) == MPIC_OK && n_syncs == syncs + 1);
+    limit = SIZE_MAX;
+    mpic_plan_destroy(p);
+    mpic_plan_destroy(q);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  {  // streams do not meet in a workspace, capture finds the one that linking left; what is outgrown stays
+    mpic_ctx* c = context(MPIC_BF16);
+    mpic_plan* p = plan_of(c, 3000);
+    CHECK(assemble(c, p, &s[0]) == MPIC_OK);
+    capture(&s[5], true);
+    CHECK(attend(c, p, &s[5]) == MPIC_OK);
+    capture(&s[5], false);
+    const float* captured = mpic::last_attn.ws_o;
+    CHECK(attend(c, p, &s[0]) == MPIC_OK && mpic::last_attn.ws_o == captured);
+    std::vector<const float*> of_stream;
+    const int syncs = n_syncs;
+    for (int i = 0; i < 4; ++i) {
+      CHECK(attend(c, p, &s[i]) == MPIC_OK);
+      for (const float* w : of_stream) CHECK(mpic::last_attn.ws_o != w);
+      of_stream.push_back(mpic::last_attn.ws_o);
+    }
+    for (int i = 0; i < 4; ++i) CHECK(attend(c, p, &s[i]) == MPIC_OK && mpic::last_attn.ws_o == of_stream[i]);
+    CHECK(n_syncs == syncs);
+    CHECK(attend(c, p, &s[4]) == MPIC_OK && n_syncs == syncs + 1);  // a fifth stream
+    mpic_plan* q = plan_of(c, 9000);
+    CHECK(assemble(c, q, &s[3]) == MPIC_OK);
+    capture(&s[3], true);
+    CHECK(attend(c, q, &s[3]) == MPIC_OK && mpic::last_attn.ws_o != of_stream[3]);
+    capture(&s[3], false);
+    CHECK(sizes.count(const_cast<float*>(of_stream[3])) == 1);
+    mpic_plan_destroy(q);
+    mpic_plan_destroy(p);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  {  // fp32: no workspace for the attention; decode steps of one batch size stay valid as contexts grow
+    mpic_ctx* c = context(MPIC_F32);
+    mpic_plan *p = plan_of(c, 200), *q = plan_of(c, 5000);
+    CHECK(assemble(c, p, &s[0]) == MPIC_OK && assemble(c, q, &s[0]) == MPIC_OK);
+    CHECK(attend(c, q, &s[0]) == MPIC_OK);
+    for (const mpic::Scratch& w : c->attn_ws) CHECK(!w.ptr);
+    CHECK(decode(c, p, &s[0]) == MPIC_OK && mpic::last_decode.n_splits == 1);
+    float* const first = mpic::last_decode.ws_o;  // as a captured step holds it
+    const int syncs = n_syncs;
+    CHECK(decode(c, q, &s[0]) == MPIC_OK && mpic::last_decode.n_splits > 1 && mpic::last_decode.ws_o != first);
+    CHECK(sizes.count(first) == 1 && n_syncs == syncs);
+    mpic_plan_destroy(p);
+    mpic_plan_destroy(q);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  std::puts("scratch ok");
+  return 0;
+}

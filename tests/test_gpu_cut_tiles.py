@@ -60,3 +60,32 @@ def test_blocks_of_destroyed_plans(side):
             for a, b in zip(got, first[j]):
                 assert torch.equal(a.view(torch.int16), b.view(torch.int16)), i
     last.close()
+
+
+def test_cut_tiles_on_two_streams_at_once():
+    """Attention calls of one context that overlap on two streams do not meet in a workspace: every call
+    gives the bits it gives alone."""
+    probs = [_custom(reqs, 2, [333, 1500], 0) for reqs in LAYOUTS]
+    for p in probs:
+        p.gpu_setup(False)
+    ctx = probs[0].ctx
+    plans = [mpic.Plan(ctx, p.requests, p.k) for p in probs]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    want = []
+    for p, plan in zip(probs, plans):
+        assert (plan.get("attn_tiles")[:, 6] >= 0).any()
+        mpic.mpic_assemble_kv(ctx.handle, plan.handle, p.srcs, p.d_fk, p.d_fv, p.k_ctx, p.v_ctx)
+        mpic.mpic_selective_attn(ctx.handle, plan.handle, p.d_q, p.k_ctx, p.v_ctx, p.sh.softmax_scale, p.out, None)
+        torch.cuda.synchronize()
+        want.append(p.out.clone())
+    outs = [[torch.zeros_like(p.out) for _ in range(25)] for p in probs]
+    torch.cuda.synchronize()
+    for i in range(25):
+        for p, plan, out, s in zip(probs, plans, outs, streams):
+            mpic.mpic_selective_attn(ctx.handle, plan.handle, p.d_q, p.k_ctx, p.v_ctx, p.sh.softmax_scale, out[i], None, s.cuda_stream)
+    torch.cuda.synchronize()
+    for w, of in zip(want, outs):
+        for out in of:
+            assert torch.equal(out.view(torch.int16), w.view(torch.int16))
+    for plan in plans:
+        plan.close()
