@@ -813,6 +813,14 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
       return fail(ctx, MPIC_ERR_UNSUPPORTED, "decode_attn_static: the partial results of this batch (" + std::to_string(need) +
                                              " bytes) exceed the static scratch array (" + std::to_string(have) + " bytes)");
   } else {
+    // A captured fp32 step whose splits find no room runs unsplit in what is there (nothing can be
+    // allocated under capture, and one split per row is what an earlier step over as many rows has left).
+    const size_t unsplit = rows * (c.head_dim + 1) * sizeof(float);
+    if (need > ctx->decode_ws.bytes && c.dtype == MPIC_F32 && unsplit <= ctx->decode_ws.bytes && !mpic::trackable(stream)) {
+      n_splits = 1;
+      keys_per_split = max_ctx;
+      need = unsplit;
+    }
     if (!mpic::grow(ctx, &ctx->decode_ws, need)) return fail(ctx, MPIC_ERR_OOM, "decode_attn: workspace allocation failed");
     ws = static_cast<float*>(ctx->decode_ws.ptr);
   }

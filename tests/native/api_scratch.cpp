@@ -169,6 +169,10 @@ int main() {
     for (const mpic::Scratch& w : c->attn_ws) CHECK(!w.ptr);
     CHECK(decode(c, p, &s[0]) == MPIC_OK && mpic::last_decode.n_splits == 1);
     float* const first = mpic::last_decode.ws_o;  // as a captured step holds it
+    capture(&s[1], true);
+    CHECK(decode(c, q, &s[1]) == MPIC_OK && mpic::last_decode.n_splits == 1 && mpic::last_decode.keys_per_split == 5000);
+    CHECK(mpic::last_decode.ws_o == first);
+    capture(&s[1], false);
     const int syncs = n_syncs;
     CHECK(decode(c, q, &s[0]) == MPIC_OK && mpic::last_decode.n_splits > 1 && mpic::last_decode.ws_o != first);
     CHECK(sizes.count(first) == 1 && n_syncs == syncs);
