@@ -412,7 +412,7 @@ def main():
                 attend(s)
 
     # Which of the two schedules is the step: the planner's estimate decides, as it does inside
-    # mpic_prefill_layers (is the linking predicted to fit into what the attention launch leaves idle?)
+    # mpic_prefill_layers (is the attention launch predicted to leave anything idle?)
     fuse = bool(plan.get("launch_estimate")[3])
     # (The event-timed kernel loops come first, after an untimed stretch of load: the whole-step timing below
     # should not pay for the clock ramp of a GPU that was idle with its first steps.)

@@ -131,8 +131,8 @@ enum {
                              /* the chip), both in 64-key blocks of one tile; 1 if a launch    */
                              /* can carry the linking of the next layer                        */
                              /* (mpic_selective_attn_link_next); 1 if that is also predicted   */
-                             /* to pay (the linking fits into the idle time, or the launch is  */
-                             /* too short for a second stream to help)                         */
+                             /* to pay (the launch leaves something idle, or is too short for  */
+                             /* a second stream to help)                                       */
   MPIC_PLAN_KEY_BLOCKS_32 = 16, /* lazy_rope contexts: [n_blocks][4] (position of the first    */
   MPIC_PLAN_KEY_BLOCKS_64 = 17, /* key, keys, chunk instance or -1 = fresh rows, rank of the   */
   MPIC_PLAN_KEY_BLOCKS_96 = 18, /* first key in its part): blocks of at most 32 / 64 / 96 keys */
@@ -386,7 +386,7 @@ int mpic_selective_attn_in_place(mpic_ctx* ctx, mpic_plan* plan, const void* fre
  * The fused launch needs bf16, device-resident sources, at most 128 chunk instances in
  * the plan and Hkv * D / 16 dividing 512; otherwise (and when the recompute set is empty)
  * the call does the same work with a launch of its own after the attention.  Whether
- * fusing pays depends on how much of the chip the attention tiles leave idle at the end:
+ * fusing pays depends on whether the attention tiles leave any of the chip idle at the end:
  * MPIC_PLAN_LAUNCH_ESTIMATE holds the planner's prediction (a batch whose tiles fill the
  * chip evenly is better served by MPIC_PART_CACHED | MPIC_PART_BACKGROUND on a second
  * stream).  The fresh rows of the next layer are not touched: link them

@@ -352,18 +352,21 @@ inline bool can_link_in_attention(const mpic_ctx* ctx, const mpic_plan* plan) {
   return ctx->cfg.dtype == MPIC_BF16 && plan->inst_src.size() <= static_cast<size_t>(kMaxInstPerLaunch) &&
          !plan->tiles.empty() && pairs_per_row <= 512 && 512 % pairs_per_row == 0;
 }
-// ... and does it pay?  Yes when the linking is predicted to fit into the time the launch leaves
-// idle (a 64-key block of a 256-row tile takes about 2.1 us; a linking launch of its own moves
-// about 6 TB/s), and for short launches in any case: there the events of a two-stream schedule
-// cost more than the linking itself (2.6K-token request: 59 us per layer against 100 us).
-inline bool link_fits_attention_tail(const mpic_ctx* ctx, const mpic_plan* plan) {
-  int64_t rows = 0;
-  for (int32_t r : plan->inst_cached) rows += r;
-  const double row_bytes = static_cast<double>(ctx->cfg.n_kv_heads) * ctx->cfg.head_dim * (ctx->cfg.dtype == MPIC_F32 ? 4 : 2);
-  const double link_us = 4.0 * static_cast<double>(rows) * row_bytes / 6.0e6;
-  const double idle_us = static_cast<double>(plan->est_idle_blocks) * 2.1 / 256.0;
-  const double launch_us = static_cast<double>(plan->est_makespan_blocks) * 2.1;
-  return link_us <= idle_us || launch_us < 500.0;
+// ... and does it pay?  Yes unless the tiles are predicted to fill a long launch to its very end.  The
+// other schedule, linking on a second stream, runs the first layer's linking in a small grid with
+// nothing beside it and holds the attention to its 64-key shape.  Where anything is left idle, the
+// fused launch took 0.84 to 0.99 of the time of the two streams over 3 layers (53 batches of
+// 0.5 to 5 ms a layer) and 0.94 to 1.00 over 10; what a further layer takes is within 3 % either way,
+// less for 9 of 16.  (Asking whether the whole linking fits into the idle time sent batches to the
+// second stream that are fused better: 7 requests of 7K tokens, three layers, 2180 us against 2414.)
+// With nothing left idle a further layer is 2 % faster on two streams, 2108 against 2144 us for 8
+// requests of 16 chunks.  Launches of less than half a millisecond are fused in any case: there the
+// events cost more than the linking itself (2.6K-token request: 59 us per layer against 100 us).
+inline bool link_fits_attention_tail(const mpic_ctx*, const mpic_plan* plan) {
+  bool any_stored = false;
+  for (int32_t r : plan->inst_cached) any_stored = any_stored || r > 0;
+  const double launch_us = static_cast<double>(plan->est_makespan_blocks) * 2.1;  // a 64-key block of a 256-row tile
+  return plan->est_idle_blocks > 0 || launch_us < 500.0 || !any_stored;
 }
 
 }  // namespace mpic

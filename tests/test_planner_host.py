@@ -385,6 +385,20 @@ def test_launch_estimate_is_the_list_scheduling_of_the_tile_order():
     assert plan.get("launch_estimate")[2] == 0 and plan.get("launch_estimate")[3] == 0
 
 
+@pytest.mark.parametrize("batch,chunks,length,text,tail", [(7, 15, 439, 27, 98), (3, 11, 204, 64, 30), (5, 5, 629, 400, 0)])
+def test_linking_rides_in_launches_that_leave_anything_idle(batch, chunks, length, text, tail):
+    """Tiles cut evenly leave little idle at the end of a launch, less than linking would take on its own,
+    and the fused schedule is still the faster one; only where nothing is left is it not."""
+    reqs = [[s for c in range(chunks) for s in (("text", text), ("chunk", b * chunks + c, length, 64))] + [("text", text), ("text", tail)]
+            for b in range(batch)]
+    plan = mpic.Plan(_ctx(32, 8), reqs, 64)
+    est = plan.get("launch_estimate").tolist()
+    stored = batch * chunks * (length - 64)
+    assert est[2:] == [1, int(est[1] > 0 or est[0] * 2.1 < 500)]
+    if batch == 7:
+        assert est[0] * 2.1 > 500 and 0 < est[1] * 2.1 / 256 < 4 * stored * 8 * 128 * 2 / 6e6 and est[3] == 1
+
+
 @pytest.mark.parametrize("heads,requests", [((7, 1), 1), ((28, 4), 3), ((28, 4), 5), ((32, 8), 2), ((6, 3), 2), ((64, 8), 1)])
 @pytest.mark.parametrize("fresh,stored", [(40, 150), (700, 1500), (2100, 3300)])
 def test_cut_tiles_fill_the_domains(heads, requests, fresh, stored):
