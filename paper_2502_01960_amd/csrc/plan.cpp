@@ -58,12 +58,13 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   constexpr int64_t kBlock = 64;          // keys per block of the attention kernel
   constexpr int64_t kMinPieceBlocks = 4;
   // Fixed costs in blocks (1.3 us each with one workgroup per compute unit): of a tile, of a piece
-  // (its partial result is written and read again) and of the merge launch.  Measured over ten
-  // batches with every cap from 4 blocks up: the launches chosen with 12 or 20 for a piece differ by
-  // 3 % at most.  Pieces of one size for a whole launch that had to fit one or two rounds over the
-  // chip left it half idle: one request of 2177 rows with 87-block tiles 94 -> 66 us, 8 requests of
-  // 13K tokens 235 -> 198 us, 2 lazy requests of 5K tokens 136 -> 126 us.
-  constexpr int64_t kTileCost = 6, kPieceCost = 16, kMergeCost = 4;
+  // (its partial result is written and read again) and of the merge launch.  Measured over two sets
+  // of 104 batches of 3 to 300 GFLOP against pieces of one size for a whole launch that had to fit
+  // one or two rounds over the chip (attention and merge, both sides in turn): with 10 for a piece
+  // 0.86 and 0.84 of that time, 9 and 10 batches more than 3 % above it, 1.08 and 1.12 at most; with 16,
+  // 0.87 and 0.85, 12 and 16 batches, 1.22 and 1.20; 8 and 12 are within 1 % of 10.  One request
+  // of 2177 rows with 87-block tiles 91 -> 70 us, 8 requests of 13K tokens 197 -> 179 us.
+  constexpr int64_t kTileCost = 6, kPieceCost = 10, kMergeCost = 4;
   constexpr int64_t kUnit = 10;
   const int B = p.n_requests;
   const int n_combo = B * n_kv_heads;
