@@ -140,7 +140,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
       cut = cut || parts > 1;
       for (int64_t i = 0; i < parts; ++i) {
         const int64_t cost = duration(t, (piece_begin(t.blocks, c, parts, i + 1) - piece_begin(t.blocks, c, parts, i)) * kBlock, parts);
-        for (int64_t h = 0; h < heads; ++h) costs.push_back(cost);
+        costs.push_back(cost);  // (once for all heads)
         sum += cost * heads;
       }
     }
@@ -150,12 +150,21 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     if (costs.empty() || costs.front() + merge >= best) return best;
     load.assign(per_head_cus, 0);
     int64_t end = 0;
-    for (const int64_t cost : costs) {
-      std::pop_heap(load.begin(), load.end(), std::greater<int64_t>());
-      load.back() += cost;
-      end = std::max(end, load.back());
-      std::push_heap(load.begin(), load.end(), std::greater<int64_t>());
-    }
+    for (const int64_t cost : costs)
+      for (int64_t h = 0; h < heads; ++h) {
+        // the lightest unit takes the piece and sinks to its place in the heap
+        const int64_t now = load.front() + cost;
+        size_t at = 0;
+        for (size_t kid = 1; kid < load.size(); kid = 2 * at + 1) {
+          if (kid + 1 < load.size() && load[kid + 1] < load[kid]) ++kid;
+          if (load[kid] >= now) break;
+          load[at] = load[kid];
+          at = kid;
+        }
+        load[at] = now;
+        end = std::max(end, now);
+        if (end + merge >= best) return best;
+      }
     return end + merge;
   };
   auto choose_cut = [&]() {
@@ -192,103 +201,101 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     int32_t n_parts = 0;
   };
   auto by_cost = [](const Item& a, const Item& b) { return a.cost > b.cost; };
-  auto lay_out = [&]() {
-    Layout out;
-    std::vector<std::vector<Item>> per_combo(n_combo);
-    for (const RowTile& rt : row_tiles) {
-      const int b = rt.b;
-      const int64_t row = rt.row, n = rt.n;
-      const int64_t parts = n_pieces(rt.blocks, cut);
-      for (int64_t i = 0; i < parts; ++i) {
-        const int64_t key0 = piece_begin(rt.blocks, cut, parts, i) * kBlock;
-        const int64_t key1 = std::min<int64_t>(rt.n_keys, piece_begin(rt.blocks, cut, parts, i + 1) * kBlock);
-        const int64_t cost = duration(rt, key1 - key0, parts);
-        for (int g = 0; g < n_kv_heads; ++g) {
-          Item it{};
-          it.t.req = b;
-          it.t.kv_head = g;
-          it.t.row0 = static_cast<int32_t>(row);
-          it.t.n_rows = static_cast<int32_t>(n);
-          it.t.n_keys = static_cast<int32_t>(key1);
-          it.t.key0 = static_cast<int32_t>(key0);
-          it.t.part = -1;  // set below for the pieces of a cut tile
-          it.cost = cost;
-          per_combo[b * n_kv_heads + g].push_back(it);
-        }
-      }
-      if (parts > 1) {
-        for (int g = 0; g < n_kv_heads; ++g) {
-          AttnMerge m{};
-          m.req = b;
-          m.kv_head = g;
-          m.row0 = static_cast<int32_t>(row);
-          m.n_rows = static_cast<int32_t>(n);
-          m.first_part = out.n_parts;
-          m.n_parts = static_cast<int32_t>(parts);
-          out.n_parts += static_cast<int32_t>(parts);
-          out.merges.push_back(m);
-          // the pieces of this (tile, g) were pushed last into their group, in key order
-          auto& v = per_combo[b * n_kv_heads + g];
-          for (int64_t i = 0; i < parts; ++i) v[v.size() - parts + i].t.part = m.first_part + static_cast<int32_t>(i);
-        }
+  Layout chosen;
+  std::vector<std::vector<Item>> per_combo(n_combo);
+  for (const RowTile& rt : row_tiles) {
+    const int b = rt.b;
+    const int64_t row = rt.row, n = rt.n;
+    const int64_t parts = n_pieces(rt.blocks, cut);
+    for (int64_t i = 0; i < parts; ++i) {
+      const int64_t key0 = piece_begin(rt.blocks, cut, parts, i) * kBlock;
+      const int64_t key1 = std::min<int64_t>(rt.n_keys, piece_begin(rt.blocks, cut, parts, i + 1) * kBlock);
+      const int64_t cost = duration(rt, key1 - key0, parts);
+      for (int g = 0; g < n_kv_heads; ++g) {
+        Item it{};
+        it.t.req = b;
+        it.t.kv_head = g;
+        it.t.row0 = static_cast<int32_t>(row);
+        it.t.n_rows = static_cast<int32_t>(n);
+        it.t.n_keys = static_cast<int32_t>(key1);
+        it.t.key0 = static_cast<int32_t>(key0);
+        it.t.part = -1;  // set below for the pieces of a cut tile
+        it.cost = cost;
+        per_combo[b * n_kv_heads + g].push_back(it);
       }
     }
-    out.queue.assign(kXcds, {});
-    std::vector<int64_t> total(n_combo, 0);
-    int64_t sum = 0;
+    if (parts > 1) {
+      for (int g = 0; g < n_kv_heads; ++g) {
+        AttnMerge m{};
+        m.req = b;
+        m.kv_head = g;
+        m.row0 = static_cast<int32_t>(row);
+        m.n_rows = static_cast<int32_t>(n);
+        m.first_part = chosen.n_parts;
+        m.n_parts = static_cast<int32_t>(parts);
+        chosen.n_parts += static_cast<int32_t>(parts);
+        chosen.merges.push_back(m);
+        // the pieces of this (tile, g) were pushed last into their group, in key order
+        auto& v = per_combo[b * n_kv_heads + g];
+        for (int64_t i = 0; i < parts; ++i) v[v.size() - parts + i].t.part = m.first_part + static_cast<int32_t>(i);
+      }
+    }
+  }
+  chosen.queue.assign(kXcds, {});
+  std::vector<int64_t> total(n_combo, 0);
+  int64_t sum = 0;
+  for (int c = 0; c < n_combo; ++c) {
+    for (const Item& it : per_combo[c]) total[c] += it.cost;
+    sum += total[c];
+  }
+  // whole (request, kv head) groups go to the currently lightest domain, heaviest first ...
+  std::vector<int> order(n_combo), home(n_combo);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return total[a] > total[b]; });
+  std::vector<int64_t> domain(kXcds, 0);
+  for (int c : order) {
+    home[c] = static_cast<int>(std::min_element(domain.begin(), domain.end()) - domain.begin());
+    domain[home[c]] += total[c];
+  }
+  if (n_combo > 0 && kXcds % n_combo == 0) {
+    // (few groups: each has its own share of the domains, which get its tiles in turn)
+    const int share = kXcds / n_combo;
     for (int c = 0; c < n_combo; ++c) {
-      for (const Item& it : per_combo[c]) total[c] += it.cost;
-      sum += total[c];
+      std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
+      for (size_t i = 0; i < per_combo[c].size(); ++i)
+        chosen.queue[c * share + static_cast<int>(i % share)].push_back(per_combo[c][i]);
     }
-    // whole (request, kv head) groups go to the currently lightest domain, heaviest first ...
-    std::vector<int> order(n_combo), home(n_combo);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return total[a] > total[b]; });
-    std::vector<int64_t> domain(kXcds, 0);
-    for (int c : order) {
-      home[c] = static_cast<int>(std::min_element(domain.begin(), domain.end()) - domain.begin());
-      domain[home[c]] += total[c];
-    }
-    if (n_combo > 0 && kXcds % n_combo == 0) {
-      // (few groups: each has its own share of the domains, which get its tiles in turn)
-      const int share = kXcds / n_combo;
-      for (int c = 0; c < n_combo; ++c) {
-        std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
-        for (size_t i = 0; i < per_combo[c].size(); ++i)
-          out.queue[c * share + static_cast<int>(i % share)].push_back(per_combo[c][i]);
-      }
-    } else if (*std::max_element(domain.begin(), domain.end()) * kXcds <= sum + sum * 3 / 100) {
-      for (int c : order) out.queue[home[c]].insert(out.queue[home[c]].end(), per_combo[c].begin(), per_combo[c].end());
-    } else {
-      // ... unless that leaves some domain idle at the end (12 groups on 8 domains: a quarter of
-      // the chip): then the groups lie on a line that is cut into eight equal parts, and the tiles
-      // of a group that spans several domains are dealt to them, longest first, by what each lacks
-      int64_t begin = 0;
-      for (int c = 0; c < n_combo; ++c) {
-        int64_t lack[kXcds] = {};
-        for (int x = 0; x < kXcds; ++x)
-          lack[x] = std::min(begin + total[c], sum * (x + 1) / kXcds) - std::max(begin, sum * x / kXcds);
-        begin += total[c];
-        std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
-        for (const Item& it : per_combo[c]) {
-          const int x = static_cast<int>(std::max_element(lack, lack + kXcds) - lack);
-          lack[x] -= it.cost;
-          out.queue[x].push_back(it);
-        }
+  } else if (*std::max_element(domain.begin(), domain.end()) * kXcds <= sum + sum * 3 / 100) {
+    for (int c : order) chosen.queue[home[c]].insert(chosen.queue[home[c]].end(), per_combo[c].begin(), per_combo[c].end());
+  } else {
+    // ... unless that leaves some domain idle at the end (12 groups on 8 domains: a quarter of
+    // the chip): then the groups lie on a line that is cut into eight equal parts, and the tiles
+    // of a group that spans several domains are dealt to them, longest first, by what each lacks
+    int64_t begin = 0;
+    for (int c = 0; c < n_combo; ++c) {
+      int64_t lack[kXcds] = {};
+      for (int x = 0; x < kXcds; ++x)
+        lack[x] = std::min(begin + total[c], sum * (x + 1) / kXcds) - std::max(begin, sum * x / kXcds);
+      begin += total[c];
+      std::stable_sort(per_combo[c].begin(), per_combo[c].end(), by_cost);
+      for (const Item& it : per_combo[c]) {
+        const int x = static_cast<int>(std::max_element(lack, lack + kXcds) - lack);
+        lack[x] -= it.cost;
+        chosen.queue[x].push_back(it);
       }
     }
-    for (auto& q : out.queue) std::stable_sort(q.begin(), q.end(), by_cost);
-    return out;
-  };
-  // Predicted duration of a launch, in blocks: every L2 domain hands its tiles in order to
-  // whichever of its compute units is free first; a piece of a cut tile costs three blocks
-  // more than its keys (prologue, partial result, share of the merge).
-  int64_t busy_blocks = 0;  // compute-unit time the tiles of the last simulated layout take, in blocks
-  auto predicted_makespan = [&](const Layout& l) {
+  }
+  for (auto& q : chosen.queue) std::stable_sort(q.begin(), q.end(), by_cost);
+  // Predicted duration of the launch, in blocks: every L2 domain hands its tiles in order to whichever
+  // of its compute units is free first; a tile costs two blocks more than its keys, a piece of a cut
+  // one five.  (Smaller fixed costs than `duration` has, which are relative to the time of a block in
+  // small launches: what hangs on the estimate is whether it leaves anything idle and whether it
+  // comes to half a millisecond.)
+  int64_t busy_blocks = 0;  // compute-unit time the tiles take, in blocks
+  auto predicted_makespan = [&]() {
     int64_t worst = 0;
-    busy_blocks = 0;
     auto heavier = std::greater<int64_t>();
-    for (const auto& q : l.queue) {
+    for (const auto& q : chosen.queue) {
       std::vector<int64_t> load(kComputeUnits / kXcds, 0);  // min-heap of compute unit loads
       for (const Item& it : q) {
         std::pop_heap(load.begin(), load.end(), heavier);
@@ -301,9 +308,8 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     }
     return worst;
   };
-  Layout chosen = lay_out();
   // what the launch is predicted to leave idle: room for work that rides along in its tail
-  p.est_makespan_blocks = predicted_makespan(chosen);
+  p.est_makespan_blocks = predicted_makespan();
   p.est_idle_blocks = p.est_makespan_blocks * kComputeUnits - busy_blocks;
   p.merges = std::move(chosen.merges);
   p.n_parts = chosen.n_parts;
