@@ -410,7 +410,7 @@ int mpic::assemble_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* s
   if (rc != MPIC_OK) return rc;
   // The attention call that most likely follows on this stream can be captured if its workspace is there.
   // Nothing is lost if it cannot be had yet.
-  if (first_use && stream != ctx->link_stream)
+  if (first_use && !(ctx->link_stream && stream == ctx->link_stream))
     if (mpic::Scratch* w = mpic::find_attn_ws(ctx, stream)) (void)mpic::grow(ctx, w, mpic::attn_ws_need(ctx, plan), false);
   const mpic_config& c = ctx->cfg;
   const size_t elem = c.dtype == MPIC_F32 ? 4 : 2;

@@ -131,6 +131,17 @@ int main() {
     mpic_destroy(c);
     CHECK(in_use == 0);
   }
+  {  // linking on the default stream leaves a workspace too
+    mpic_ctx* c = context(MPIC_BF16);
+    mpic_plan* p = plan_of(c, 3000);
+    CHECK(assemble(c, p, nullptr) == MPIC_OK);
+    capture(&s[5], true);
+    CHECK(attend(c, p, &s[5]) == MPIC_OK);
+    capture(&s[5], false);
+    mpic_plan_destroy(p);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
   {  // streams do not meet in a workspace, capture finds the one that linking left; what is outgrown stays
     mpic_ctx* c = context(MPIC_BF16);
     mpic_plan* p = plan_of(c, 3000);
