@@ -156,7 +156,7 @@ int main() {
       wait(&null_stream);
       rt.destroy(&p);
     }
-    CHECK(n > 140 && rt.mallocs <= 9 && rt.frees <= 9);
+    CHECK(n > 140 && rt.mallocs <= 17 && rt.frees <= 17);
     const int mallocs = rt.mallocs, frees = rt.frees;
     for (int i = 0; i < 100; ++i) {
       Plan p = rt.first_use((size_t{11} << 20) + 1000 * i, &null_stream);
@@ -182,6 +182,10 @@ int main() {
       rt.destroy(&p);
     }
     CHECK(rt.mallocs == mallocs + 1 && rt.frees == 1 && !bad_handle);
+  }
+  for (size_t need = 1; need <= mpic::SpareBlocks::kMaxBytes; need += need / 7 + 1) {
+    const size_t size = mpic::SpareBlocks::size_for(need);
+    CHECK(size >= need && size <= mpic::SpareBlocks::kMaxBytes && (size <= need / 2 * 3 + 2 || size == size_t{64} << 10));
   }
   {  // not followed: under capture, on the per-thread stream, on too many streams, too large, pool closed
     Runtime rt;
