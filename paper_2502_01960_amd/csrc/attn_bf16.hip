@@ -64,7 +64,11 @@ struct Geo {
   __device__ static int v_slot_off(int t) { return (t % V_SLOTS) * TILE_BYTES; }
   __device__ static int k_slot_off(int t) { return V_SLOTS * TILE_BYTES + (t % K_SLOTS) * TILE_BYTES; }
 };
-constexpr int kLinkRounds = 2;  // trips of the linking loop per trailing workgroup
+// Trips of the linking loop per trailing workgroup.  With two, the trailing workgroups of a launch of one
+// round, which each take a whole compute unit, outlast its tiles where few units are left for them: of 104
+// batches of up to 100 GFLOP, 25 took up to 30 % more than with tiles cut into fewer pieces, with one 14
+// (request of 3.2K tokens 30.5 -> 27 us, one of 2.7K 41 -> 36 us; the 18K-token batch of 4 the same 1085 us).
+constexpr int kLinkRounds = 1;
 constexpr int kLinkDepth = 2;   // items a thread of a trailing workgroup keeps in flight
 constexpr float kSumLimit = 4096.0f;  // lazy rescale: a lane's share of a block's row sum may reach this
 static_assert(WAVES * ROWS_PER_WAVE == kAttnTileRows, "tile size and kernel shape must agree");
@@ -895,7 +899,7 @@ hipError_t launch_shape(const AttnArgs& a, const AssembleArgs* next, const Assem
     ln.args = *next;
     ln.tab = *next_tab;
     // kLinkRounds trips of the loop per workgroup: short enough to fill the gaps the last
-    // attention tiles leave
+    // attention tiles leave, and the few compute units that a launch of one round leaves
     const int64_t rows_per_pass = THREADS / (next->n_kv_heads * (next->head_dim / 2 / 8));
     const int64_t rows_per_wg = kLinkRounds * kLinkDepth * rows_per_pass;
     ln.n_wgs = static_cast<int32_t>(std::max<int64_t>(1, (n_pos + rows_per_wg - 1) / rows_per_wg));
