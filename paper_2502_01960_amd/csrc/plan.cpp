@@ -57,14 +57,15 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   };
   constexpr int64_t kBlock = 64;          // keys per block of the attention kernel
   constexpr int64_t kMinPieceBlocks = 4;
-  // Fixed costs in blocks (1.3 us each with one workgroup per compute unit): of a tile, of a piece
-  // (its partial result is written and read again) and of the merge launch.  Measured over two sets
-  // of 104 batches of 3 to 300 GFLOP against pieces of one size for a whole launch that had to fit
-  // one or two rounds over the chip (attention and merge, both sides in turn): with 10 for a piece
-  // 0.86 and 0.84 of that time, 9 and 10 batches more than 3 % above it, 1.08 and 1.12 at most; with 16,
-  // 0.87 and 0.85, 12 and 16 batches, 1.22 and 1.20; 8 and 12 are within 1 % of 10.  One request
-  // of 2177 rows with 87-block tiles 91 -> 70 us, 8 requests of 13K tokens 197 -> 179 us.
-  constexpr int64_t kTileCost = 6, kPieceCost = 10, kMergeCost = 4;
+  // Fixed costs in blocks (1.3 us each with one workgroup per compute unit): of a tile, of a piece, of
+  // the merge launch, and the rows of partial results that are written and read again in the time of
+  // one block (11 MB, 8.5 TB/s).  Measured over three sets of 104 batches of 0.1 to 300 GFLOP against
+  // pieces of one size for a whole launch that had to fit one or two rounds over the chip (attention
+  // and merge, both sides in turn): 0.84, 0.85 and 0.88 of that time, 33 of the 312 batches more than
+  // 3 % above it, most of them launches of less than 20 us.  With 10 blocks for a piece whatever its
+  // rows and 4 for the merge launch: 0.85, 0.87 and 0.89, 45 batches; with 16 for a piece up to 22 %
+  // more.  One request of 2177 rows with 87-block tiles 91 -> 70 us, 8 requests of 13K tokens 197 -> 179 us.
+  constexpr int64_t kTileCost = 6, kPieceCost = 5, kMergeCost = 2, kPartRowsPerBlock = 10667;
   constexpr int64_t kUnit = 10;
   const int B = p.n_requests;
   const int n_combo = B * n_kv_heads;
@@ -133,18 +134,17 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   std::vector<int64_t> costs, load;
   auto simulate = [&](const Cut& c, int64_t best) {
     costs.clear();
-    int64_t sum = 0;
-    bool cut = false;
+    int64_t sum = 0, part_rows = 0;
     for (const RowTile& t : row_tiles) {
       const int64_t parts = n_pieces(t.blocks, c);
-      cut = cut || parts > 1;
+      if (parts > 1) part_rows += parts * t.n * n_kv_heads;
       for (int64_t i = 0; i < parts; ++i) {
         const int64_t cost = duration(t, (piece_begin(t.blocks, c, parts, i + 1) - piece_begin(t.blocks, c, parts, i)) * kBlock, parts);
         costs.push_back(cost);  // (once for all heads)
         sum += cost * heads;
       }
     }
-    const int64_t merge = cut ? kMergeCost * kUnit : 0;
+    const int64_t merge = part_rows > 0 ? kMergeCost * kUnit + part_rows * kUnit / kPartRowsPerBlock : 0;
     if (sum / per_head_cus + merge >= best) return best;  // cannot be better
     std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
     if (costs.empty() || costs.front() + merge >= best) return best;
