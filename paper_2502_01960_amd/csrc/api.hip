@@ -795,6 +795,10 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
     int64_t kps = (max_ctx + want - 1) / want;
     const int64_t unit = c.dtype == MPIC_F32 ? mpic::kDecodeBlockKeysF32 : mpic::kDecodeBlockKeys;
     kps = (kps + unit - 1) / unit * unit;
+    // Short contexts stay in one piece: the merge launch takes 2.3 us, every further 128 keys of a
+    // workgroup 1.1 to 1.4 us (28 heads over 4: 256 keys 8.4 -> 7.2 us, 384 8.4 -> 8.3, 512 8.5 -> 9.3;
+    // 10 key blocks of a lazy_rope context 9.4 -> 10.6).
+    if (c.dtype == MPIC_BF16 && max_ctx <= mpic::kDecodeUnsplitKeys) kps = max_ctx;
     keys_per_split = static_cast<int32_t>(kps);
     n_splits = static_cast<int32_t>((max_ctx + kps - 1) / kps);  // <= 256, the merge kernel holds up to 1024 weights
   }

@@ -309,6 +309,7 @@ hipError_t launch_attn_bf16(const AttnArgs& a, const AssembleArgs* next, const A
 // Keys of a decode split are a multiple of this (four wavefronts x 32-key blocks).
 constexpr int kDecodeBlockKeys = 128;
 constexpr int kDecodeBlockKeysF32 = 256;  // (eight wavefronts)
+constexpr int kDecodeUnsplitKeys = 256;   // bf16 contexts up to here are not split
 struct DecodeArgs {
   const int32_t* ctx_off;
   const int32_t* dst_slot;

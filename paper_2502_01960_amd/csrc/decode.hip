@@ -14,9 +14,12 @@
 // the loop: a wavefront only reads what it loaded itself).  The query heads of the kv
 // group are the columns of a 32-column matrix-core tile (S^T = K.Q^T, O^T = V^T.P^T, the
 // transposed formulation of the prefill kernel: softmax statistics are per-lane
-// scalars).  The four wavefronts merge their partial results through LDS and write one
-// (O, log-sum-exp) partial per split; a second small kernel merges the splits and adds
-// the new token itself.
+// scalars).  The four wavefronts merge their partial results through LDS.  Where the keys are
+// not split, the workgroup adds the new token itself and writes the output; otherwise it writes one
+// (O, log-sum-exp) partial per split, and a second small kernel merges the splits and adds the new
+// token.  (Merging in the workgroup that arrives last, with partial results that go past the L2s and a
+// counter, takes longer than that launch: 14.2 us against 13.5 for 2.6K tokens with 32 kv heads, 36.5
+// against 33.1 for the 18K-token batch of 4.)
 #include <type_traits>
 
 #include "common.h"
@@ -37,10 +40,11 @@ constexpr int STAGES = 2;                        // blocks in flight per wavefro
 constexpr int WAVE_LDS = STAGES * STAGE_BYTES;
 constexpr int LDS_BYTES = WAVES * WAVE_LDS;
 constexpr int LOADS_PER_BLOCK = 16;              // direct loads per wavefront and block
+constexpr int FINISH_AT = WAVES * 32 * D + 2 * WAVES * 32;  // LDS of the rows of an unsplit step, in floats: behind the merge area
 constexpr float kSlack = 8.0f;                   // lazy-rescale threshold, log2 units
 static_assert(kDecodeBlockKeys % BN == 0, "a split is a whole number of key blocks");
 static_assert(LDS_BYTES <= 160 * 1024 && LOADS_PER_BLOCK * (STAGES - 1) <= 63, "LDS size / load counter range");
-static_assert(WAVES * 32 * D * 4 + 2 * WAVES * 32 * 4 <= LDS_BYTES, "merge area must fit the staging area");
+static_assert((FINISH_AT + 32 * D + 32) * 4 <= LDS_BYTES, "merge area and finished rows must fit the staging area");
 
 // wait until at most `blocks` blocks of loads are outstanding; the empty asm keeps the
 // compiler from moving an LDS read above the wait
@@ -58,6 +62,57 @@ __device__ inline void wait_loads(int blocks) {
 }
 static_assert(LOADS_PER_BLOCK == 16, "wait_loads spells the count out");
 
+// The end of an unsplit step: the context's share of output rows h0 .. h0 + n_cols - 1 of request b
+// (normalised, [n_cols][kD], and its log-sum-exp, both in LDS; any_key = false: the request has no
+// context) and the new token's own term give the rows.  Called by the whole workgroup, once its LDS
+// writes are visible.  Saves the merge launch, 2.3 us (28 heads over 4, 64 keys 8.0 -> 6.1 us; fp32 with 4
+// heads, 250 keys 12.5 -> 10.4).
+template <typename T, int kD, int kThreads>
+__device__ inline void finish_rows(const DecodeArgs& a, int b, int g, int h0, int n_cols, bool any_key, const float* part_o,
+                                   const float* part_lse) {
+  constexpr int kLanes = kD / 4;  // threads per output row
+  typedef T t4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, d0 = tid % kLanes * 4;
+  const int64_t kv = (static_cast<int64_t>(b) * a.n_kv_heads + g) * kD + d0;
+  f32x4 k = f32x4{0}, v = f32x4{0};
+  if (a.new_k) {
+    k = __builtin_convertvector(*reinterpret_cast<const t4*>(static_cast<const T*>(a.new_k) + kv), f32x4);
+    v = __builtin_convertvector(*reinterpret_cast<const t4*>(static_cast<const T*>(a.new_v) + kv), f32x4);
+  }
+  for (int c = tid / kLanes; c < n_cols; c += kThreads / kLanes) {
+    const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + h0 + c;
+    float self = -INFINITY;
+    if (a.new_k) {
+      const f32x4 q = __builtin_convertvector(*reinterpret_cast<const t4*>(static_cast<const T*>(a.q) + row * kD + d0), f32x4);
+      self = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) self = fmaf(q[e], k[e], self);
+#pragma unroll
+      for (int off = kLanes / 2; off > 0; off >>= 1) self += __shfl_xor(self, off);
+      self *= a.scale;
+    }
+    const float lse = any_key ? part_lse[c] : -INFINITY;
+    const float m = fmaxf(lse, self);
+    f32x4 o = f32x4{0};
+    float z = 0.f;
+    if (m != -INFINITY) {
+      if (any_key) {
+        z = expf(lse - m);
+        o = *reinterpret_cast<const f32x4*>(part_o + c * kD + d0) * z;
+      }
+      if (a.new_k) {
+        const float w = expf(self - m);
+        z += w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(w, v[e], o[e]);
+      }
+      o /= z;
+    }
+    *reinterpret_cast<t4*>(static_cast<T*>(a.out) + row * kD + d0) = __builtin_convertvector(o, t4);
+    if (a.lse && d0 == 0) a.lse[row] = m == -INFINITY ? -INFINITY : m + logf(z);
+  }
+}
+
 // Extra = LazyRefs (lazy_rope contexts): the wavefronts walk the request's 32-key blocks of the
 // plan (KeyBlock: one source and one missing shift per block, slots past n_valid are padding),
 // stage each block from its source's base address, and turn the query back by the block's shift
@@ -66,7 +121,9 @@ static_assert(LOADS_PER_BLOCK == 16, "wait_loads spells the count out");
 struct NoLazy {};
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
-template <typename Extra>
+// kUnsplit: a.n_splits is 1 and the kernel writes the output rows (a kernel of its own, since the longer code
+// costs the split steps 0.3 us).
+template <typename Extra, bool kUnsplit>
 __global__ __launch_bounds__(THREADS) void decode_bf16_kernel(DecodeArgs a, Extra extra) {
   constexpr bool kLazy = std::is_same<Extra, LazyRefs>::value;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -89,7 +146,12 @@ __global__ __launch_bounds__(THREADS) void decode_bf16_kernel(DecodeArgs a, Extr
     vb0 = extra.first[b] + split * (a.keys_per_split / BN);
   }
   const int key0 = split * a.keys_per_split;
-  if (key0 >= n_ctx) return;  // this request has fewer splits (the whole workgroup leaves)
+  const int n_cols = min(32, group - cb * 32);
+  float* const fin = reinterpret_cast<float*>(lds) + FINISH_AT;
+  if (key0 >= n_ctx) {  // this request has fewer splits (the whole workgroup leaves), or no context
+    if constexpr (kUnsplit) finish_rows<__bf16, D, THREADS>(a, b, g, g * group + cb * 32, n_cols, false, fin, fin);
+    return;
+  }
   const int n_keys = min(n_ctx, key0 + a.keys_per_split) - key0;
   const int n_blk = (n_keys + BN - 1) / BN;
 
@@ -376,16 +438,30 @@ __global__ __launch_bounds__(THREADS) void decode_bf16_kernel(DecodeArgs a, Extr
       }
       const float inv = 1.f / l_tot;  // a split holds at least one key, so l_tot > 0
       const int64_t part = (static_cast<int64_t>(b) * a.n_q_heads + g * group + hg) * a.n_splits + split;
-      float* po = a.ws_o + part * D + d0;
+      const float lse = m_tot * a.scale + logf(l_tot);
 #pragma unroll
       for (int i = 0; i < 16; i += 4) {
         f32x4 acc = f32x4{0};
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) acc += wgt[w] * *reinterpret_cast<const f32x4*>(m_o + (w * 32 + c) * D + d0 + i);
-        *reinterpret_cast<f32x4*>(po + i) = acc * inv;
+        if constexpr (kUnsplit) {
+          *reinterpret_cast<f32x4*>(fin + c * D + d0 + i) = acc * inv;
+        } else {
+          *reinterpret_cast<f32x4*>(a.ws_o + part * D + d0 + i) = acc * inv;
+        }
       }
-      if ((tid & 7) == 0) a.ws_lse[part] = m_tot * a.scale + logf(l_tot);
+      if ((tid & 7) == 0) {
+        if constexpr (kUnsplit) {
+          fin[32 * D + c] = lse;
+        } else {
+          a.ws_lse[part] = lse;
+        }
+      }
     }
+  }
+  if constexpr (kUnsplit) {
+    __syncthreads();
+    finish_rows<__bf16, D, THREADS>(a, b, g, g * group + cb * 32, n_cols, true, fin, fin + 32 * D);
   }
 }
 
@@ -492,7 +568,7 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
 // fp32 path: the query heads of a kv group are the columns of one fp32 tile (f32_tile.h), a
 // workgroup owns one split of the keys.  kLazy (lazy_rope contexts): stored keys are turned to
 // their position as they are read, in fp32; refs.by_ref: stored rows are read in their caches.
-template <int kD, bool kLazy>
+template <int kD, bool kLazy, bool kUnsplit>
 __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(DecodeArgs a, LazyRefs refs) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int lane = threadIdx.x & 63, col = lane & 31, hi = lane >> 5;
@@ -505,7 +581,11 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
   const int b = blockIdx.x / a.n_splits;
   const int n_ctx = a.ctx_off[b + 1] - a.ctx_off[b];
   const int key0 = split * a.keys_per_split;
-  if (key0 >= n_ctx) return;  // this request has fewer splits
+  float* const fin = reinterpret_cast<float*>(lds);
+  if (key0 >= n_ctx) {  // this request has fewer splits, or no context
+    if constexpr (kUnsplit) finish_rows<float, kD, f32tile::kThreads>(a, b, g, h0, n_cols, false, fin, fin);
+    return;
+  }
   const int key1 = min(n_ctx, key0 + a.keys_per_split);
   float q[kD / 2];
   const int64_t row0 = static_cast<int64_t>(b) * a.n_q_heads + h0;
@@ -526,32 +606,54 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
   }
   f32tile::attend<kD, kLazy>(src, q, key1 - 1, key0, key1, a.scale, lds,
                              [&](int c, int d0, const float(&o)[f32tile::Geo<kD>::kPerThread], float m, float l) {
+    if constexpr (kUnsplit) __syncthreads();  // (every thread is here once: what lies in LDS has been read)
     if (c >= n_cols) return;
     const int64_t part = (row0 + c) * a.n_splits + split;
-    const float inv = 1.f / l;
-    float* po = a.ws_o + part * kD + d0;
+    const float inv = 1.f / l, lse = m * a.scale + logf(l);
 #pragma unroll
-    for (int i = 0; i < f32tile::Geo<kD>::kPerThread; i += 4)
-      *reinterpret_cast<f32x4*>(po + i) = f32x4{o[i], o[i + 1], o[i + 2], o[i + 3]} * inv;
-    if (d0 == 0) a.ws_lse[part] = m * a.scale + logf(l);
+    for (int i = 0; i < f32tile::Geo<kD>::kPerThread; i += 4) {
+      const f32x4 x = f32x4{o[i], o[i + 1], o[i + 2], o[i + 3]} * inv;
+      if constexpr (kUnsplit) {
+        *reinterpret_cast<f32x4*>(fin + c * kD + d0 + i) = x;
+      } else {
+        *reinterpret_cast<f32x4*>(a.ws_o + part * kD + d0 + i) = x;
+      }
+    }
+    if (d0 != 0) return;
+    if constexpr (kUnsplit) {
+      fin[f32tile::kCols * kD + c] = lse;
+    } else {
+      a.ws_lse[part] = lse;
+    }
   });
+  if constexpr (kUnsplit) {
+    __syncthreads();
+    finish_rows<float, kD, f32tile::kThreads>(a, b, g, h0, n_cols, true, fin, fin + f32tile::kCols * kD);
+  }
+}
+
+template <int kD, bool kLazy, bool kUnsplit>
+hipError_t launch_f32_kernel(const DecodeArgs& a, const LazyRefs& refs, int dev, hipStream_t stream) {
+  constexpr int kLds = f32tile::Geo<kD>::kLdsBytes;
+  static LdsOptIn opt_in;
+  const hipError_t e = opt_in.ensure(dev, [] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(decode_f32_kernel<kD, kLazy, kUnsplit>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  });
+  if (e != hipSuccess) return e;
+  const int group = a.n_q_heads / a.n_kv_heads;
+  const dim3 grid(static_cast<unsigned>(a.n_splits) * a.n_requests, a.n_kv_heads * ((group + f32tile::kCols - 1) / f32tile::kCols));
+  hipLaunchKernelGGL((decode_f32_kernel<kD, kLazy, kUnsplit>), grid, dim3(f32tile::kThreads), kLds, stream, a, refs);
+  return hipSuccess;
 }
 
 template <int kD, bool kLazy>
 hipError_t launch_f32(const DecodeArgs& a, const LazyRefs& refs, int dev, hipStream_t stream) {
-  if (a.max_ctx > 0) {
-    constexpr int kLds = f32tile::Geo<kD>::kLdsBytes;
-    static LdsOptIn opt_in;
-    const hipError_t e = opt_in.ensure(dev, [] {
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(decode_f32_kernel<kD, kLazy>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    });
-    if (e != hipSuccess) return e;
-    const int group = a.n_q_heads / a.n_kv_heads;
-    const dim3 grid(static_cast<unsigned>(a.n_splits) * a.n_requests, a.n_kv_heads * ((group + f32tile::kCols - 1) / f32tile::kCols));
-    hipLaunchKernelGGL((decode_f32_kernel<kD, kLazy>), grid, dim3(f32tile::kThreads), kLds, stream, a, refs);
-  }
-  const unsigned rows = static_cast<unsigned>(a.n_requests) * a.n_q_heads;
-  hipLaunchKernelGGL((decode_merge_kernel<float, kD>), dim3(rows), dim3(kD), 0, stream, a);
+  const hipError_t e = a.n_splits == 1 ? launch_f32_kernel<kD, kLazy, true>(a, refs, dev, stream)
+                                       : launch_f32_kernel<kD, kLazy, false>(a, refs, dev, stream);
+  if (e != hipSuccess) return e;
+  if (a.n_splits > 1)
+    hipLaunchKernelGGL((decode_merge_kernel<float, kD>), dim3(static_cast<unsigned>(a.n_requests) * a.n_q_heads), dim3(kD), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -597,22 +699,29 @@ hipError_t launch_decode(int dtype, const DecodeArgs& a, const LazyRefs* lazy, h
   }
   static LdsOptIn opt_in;
   e = opt_in.ensure(dev, [] {
-    const hipError_t e0 = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_bf16_kernel<NoLazy>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (e0 != hipSuccess) return e0;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(decode_bf16_kernel<LazyRefs>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    for (const void* kernel : {reinterpret_cast<const void*>(decode_bf16_kernel<NoLazy, false>), reinterpret_cast<const void*>(decode_bf16_kernel<NoLazy, true>),
+                               reinterpret_cast<const void*>(decode_bf16_kernel<LazyRefs, false>), reinterpret_cast<const void*>(decode_bf16_kernel<LazyRefs, true>)}) {
+      const hipError_t e0 = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+      if (e0 != hipSuccess) return e0;
+    }
+    return hipSuccess;
   });
   if (e != hipSuccess) return e;
   const int group = a.n_q_heads / a.n_kv_heads;
   const dim3 grid(a.n_splits, a.n_kv_heads * ((group + 31) / 32), a.n_requests);
-  if (a.max_ctx > 0) {
-    if (lazy)
-      hipLaunchKernelGGL(decode_bf16_kernel<LazyRefs>, grid, dim3(THREADS), LDS_BYTES, stream, a, *lazy);
+  if (lazy) {
+    if (a.n_splits == 1)
+      hipLaunchKernelGGL((decode_bf16_kernel<LazyRefs, true>), grid, dim3(THREADS), LDS_BYTES, stream, a, *lazy);
     else
-      hipLaunchKernelGGL(decode_bf16_kernel<NoLazy>, grid, dim3(THREADS), LDS_BYTES, stream, a, NoLazy{});
+      hipLaunchKernelGGL((decode_bf16_kernel<LazyRefs, false>), grid, dim3(THREADS), LDS_BYTES, stream, a, *lazy);
+  } else {
+    if (a.n_splits == 1)
+      hipLaunchKernelGGL((decode_bf16_kernel<NoLazy, true>), grid, dim3(THREADS), LDS_BYTES, stream, a, NoLazy{});
+    else
+      hipLaunchKernelGGL((decode_bf16_kernel<NoLazy, false>), grid, dim3(THREADS), LDS_BYTES, stream, a, NoLazy{});
   }
-  hipLaunchKernelGGL((decode_merge_kernel<__bf16, 128>), dim3(static_cast<unsigned>(rows)), dim3(128), 0, stream, a);
+  if (a.n_splits > 1)
+    hipLaunchKernelGGL((decode_merge_kernel<__bf16, 128>), dim3(static_cast<unsigned>(rows)), dim3(128), 0, stream, a);
   return hipGetLastError();
 }
 
