@@ -64,7 +64,9 @@ bool grow(mpic_ctx* ctx, Scratch* w, size_t need, bool needed = true) {
 }
 
 size_t attn_ws_need(const mpic_ctx* ctx, const mpic_plan* p) {
-  return ctx->cfg.dtype == MPIC_BF16 ? static_cast<size_t>(p->n_parts) * kAttnTileRows * (ctx->cfg.head_dim + 1) * sizeof(float) : 0;
+  const size_t rows = ctx->cfg.dtype == MPIC_BF16 ? static_cast<size_t>(p->n_parts) * kAttnTileRows
+                                                  : static_cast<size_t>(p->n_parts_f32) * ctx->cfg.n_kv_heads * kAttnTileRowsF32;
+  return rows * (ctx->cfg.head_dim + 1) * sizeof(float);
 }
 
 // The workspace of the stream's attention calls, or the largest that no stream has yet (null: none left).
@@ -77,6 +79,11 @@ Scratch* find_attn_ws(mpic_ctx* ctx, hipStream_t stream) {
   return w;
 }
 
+Scratch* largest_attn_ws(mpic_ctx* ctx) {
+  return &*std::max_element(std::begin(ctx->attn_ws), std::end(ctx->attn_ws),
+                            [](const Scratch& x, const Scratch& y) { return x.bytes < y.bytes; });
+}
+
 // Workspace of the cut tiles of a plan for an attention call on `stream`, null if it cannot be had.  Every
 // stream has its own, so that calls on different streams do not meet in it: which plans are cut is the
 // planner's business, and no caller should have to order its streams for it.  With more streams than
@@ -87,8 +94,7 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
   Scratch* w = find_attn_ws(ctx, stream);
   if (!(w && w->claimed)) {
     if (!trackable(stream)) {
-      w = &*std::max_element(std::begin(ctx->attn_ws), std::end(ctx->attn_ws),
-                             [](const Scratch& x, const Scratch& y) { return x.bytes < y.bytes; });
+      w = largest_attn_ws(ctx);
     } else {
       if (!w) {
         if (hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
@@ -100,6 +106,20 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
     }
   }
   return grow(ctx, w, need) ? w : nullptr;
+}
+
+// The same for a launch that can also do without (fp32): null if no workspace is free or has the room, and
+// nothing waits or goes to make some.
+Scratch* spare_attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
+  const size_t need = attn_ws_need(ctx, p);
+  Scratch* w = find_attn_ws(ctx, stream);
+  if (!(w && w->claimed) && !trackable(stream)) w = largest_attn_ws(ctx);
+  if (!w || (need > w->bytes && !trackable(stream))) return nullptr;  // (nothing can be allocated under capture)
+  if (!trackable(stream)) return w;
+  if (!grow(ctx, w, need, false)) return nullptr;
+  w->claimed = true;
+  w->stream = stream;
+  return w;
 }
 
 // Copy the integer maps, rotary tables and tile list to the GPU (once per plan): the tables
@@ -149,7 +169,10 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   const size_t o_fresh_cos = put(p->fresh_cos.data(), p->fresh_cos.size() * 4);
   const size_t o_fresh_sin = put(p->fresh_sin.data(), p->fresh_sin.size() * 4);
   const size_t o_tiles = put(p->tiles.data(), p->tiles.size() * sizeof(AttnTile));
-  const size_t o_merges = put(p->merges.data(), p->merges.size() * sizeof(AttnMerge));
+  const std::vector<AttnMerge>& merges = ctx->cfg.dtype == MPIC_F32 ? p->merges_f32 : p->merges;
+  const size_t o_merges = put(merges.data(), merges.size() * sizeof(AttnMerge));
+  const size_t o_tiles_f32 = put(p->tiles_f32.data(), p->tiles_f32.size() * sizeof(AttnPieceF32));
+  const size_t o_pieces_f32 = put(p->pieces_f32.data(), p->pieces_f32.size() * sizeof(AttnPieceF32));
   // lazy_rope contexts: key blocks, their row-offset tables in both views, tiles in block indices
   size_t o_kblk[kNumBlockSizes] = {}, o_first[kNumBlockSizes] = {}, o_mid[kNumBlockSizes] = {}, o_vctx[kNumBlockSizes] = {},
          o_vref[kNumBlockSizes] = {}, o_range[kNumBlockSizes] = {};
@@ -245,6 +268,8 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   }
   d.tiles = reinterpret_cast<AttnTile*>(base + o_tiles);
   d.merges = reinterpret_cast<AttnMerge*>(base + o_merges);
+  d.tiles_f32 = reinterpret_cast<AttnPieceF32*>(base + o_tiles_f32);
+  d.pieces_f32 = reinterpret_cast<AttnPieceF32*>(base + o_pieces_f32);
   if (lazy) {
     for (int s = 0; s < kNumBlockSizes; ++s) {
       d.kblk[s] = reinterpret_cast<KeyBlock*>(base + o_kblk[s]);
@@ -682,10 +707,19 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   a.q_sin = plan->dev.fresh_sin;
   a.interleaved = c.rope_interleaved;
   a.ablate = ctx->attn_ablate;
-  int64_t n_tiles_f32 = 0;
-  if (c.dtype == MPIC_F32)
-    for (int b = 0; b < plan->n_requests; ++b)
-      n_tiles_f32 += ((plan->q_off[b + 1] - plan->q_off[b]) * static_cast<int64_t>(ctx->group) + mpic::kAttnTileRowsF32 - 1) / mpic::kAttnTileRowsF32;
+  int64_t n_pieces_f32 = 0;
+  if (c.dtype == MPIC_F32) {
+    // (tiles that are to be cut stay whole where there is no room for their partial results)
+    const mpic::Scratch* w = plan->n_parts_f32 > 0 ? mpic::spare_attn_workspace(ctx, plan, static_cast<hipStream_t>(stream_)) : nullptr;
+    a.pieces_f32 = w ? plan->dev.pieces_f32 : plan->dev.tiles_f32;
+    n_pieces_f32 = static_cast<int64_t>(w ? plan->pieces_f32.size() : plan->tiles_f32.size());
+    if (w) {
+      a.ws_o = static_cast<float*>(w->ptr);
+      a.ws_lse = a.ws_o + static_cast<size_t>(plan->n_parts_f32) * c.n_kv_heads * mpic::kAttnTileRowsF32 * c.head_dim;
+      a.merges = plan->dev.merges;
+      a.n_merges = static_cast<int32_t>(plan->merges_f32.size());
+    }
+  }
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   if (lazy) {
     mpic::LazyRefs lr;
@@ -696,7 +730,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
       a.src_row = plan->dev.src_row;
       a.rope_cos = plan->dev.rope_cos;
       a.rope_sin = plan->dev.rope_sin;
-      MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_tiles_f32, &lr, stream));
+      MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_pieces_f32, &lr, stream));
     } else {
       MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, &lr, stream));
     }
@@ -731,7 +765,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     return MPIC_OK;
   }
   if (c.dtype == MPIC_F32) {
-    MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_tiles_f32, nullptr, stream));
+    MPIC_HIP(ctx, mpic::launch_attn_f32(a, n_pieces_f32, nullptr, stream));
   } else {
     MPIC_HIP(ctx, mpic::launch_attn_bf16(a, nullptr, nullptr, nullptr, stream));
   }

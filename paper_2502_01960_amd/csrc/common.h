@@ -30,9 +30,19 @@ static_assert(sizeof(AttnTile) == 32, "tile layout is part of the ABI");
 struct AttnMerge {
   int32_t req, kv_head, row0, n_rows;
   int32_t first_part, n_parts;  // partial slots first_part .. first_part + n_parts - 1, in key order
-  int32_t pad[2];
+  int32_t pad[2];  // (fp32: first fresh row of the request)
 };
 static_assert(sizeof(AttnMerge) == 32, "merge item layout");
+
+// Work item of the fp32 attention kernel, the same for every kv head: rows row0 .. row0 + n_rows - 1 (flattened as
+// above) of a request against its keys key0 .. key1 - 1.  Everything the kernel needs to find its rows stands
+// here, so that one load precedes those of the queries and the row offsets.
+struct AttnPieceF32 {
+  int32_t req, row0, n_rows, key0, key1;
+  int32_t part;        // -1: the rows see no other keys; >= 0: number of the partial result
+  int32_t q_off, ctx_off;  // first fresh row and first position of the request
+};
+static_assert(sizeof(AttnPieceF32) == 32, "piece layout");
 
 // Contexts with lazy_rope: the keys of a request, gathered into blocks of one source each (a chunk
 // instance, or the fresh rows).  All keys of a block lack the same position shift, so a kernel can
@@ -73,6 +83,8 @@ struct PlanDevice {
   float* fresh_sin = nullptr;
   AttnTile* tiles = nullptr;
   AttnMerge* merges = nullptr;
+  AttnPieceF32* tiles_f32 = nullptr;   // fp32 contexts: whole tiles, and the launch with tiles cut along the keys
+  AttnPieceF32* pieces_f32 = nullptr;
   // lazy_rope contexts, one set per block size (kBlockSizes)
   KeyBlock* kblk[kNumBlockSizes] = {};
   int32_t* kblk_first[kNumBlockSizes] = {};   // [B+1] first block of each request
@@ -148,6 +160,11 @@ struct mpic_plan {
   std::vector<mpic::AttnTile> tiles;
   std::vector<mpic::AttnMerge> merges;  // tiles cut along the keys
   int32_t n_parts = 0;                  // partial-result slots those tiles use
+  // fp32 contexts: tiles of one kv head; the same with the long ones cut along the keys (empty: none is worth it),
+  // what that leaves to be merged (kv_head unused) and the partial results of one kv head
+  std::vector<mpic::AttnPieceF32> tiles_f32, pieces_f32;
+  std::vector<mpic::AttnMerge> merges_f32;
+  int32_t n_parts_f32 = 0;
   // the planner's simulation of the attention launch, in 64-key blocks of one tile: when the
   // last workgroup ends, and the compute-unit time left idle until then (summed over the chip)
   int64_t est_makespan_blocks = 0;
@@ -253,7 +270,10 @@ struct AttnArgs {
   int32_t n_q_heads, n_kv_heads, head_dim;
   int32_t n_requests;
   float* ws_o;    // [n_parts][kAttnTileRows * D] normalised partial outputs of cut tiles, in register order
+                  // (fp32: [n_parts][Hkv][kAttnTileRowsF32][D])
   float* ws_lse;  // [n_parts][kAttnTileRows] their log-sum-exp (-inf: the row saw no key of the piece)
+                  // (fp32: [n_parts][Hkv][kAttnTileRowsF32])
+  const AttnPieceF32* pieces_f32;
   const AttnMerge* merges;
   int32_t n_merges;
   int32_t block_keys;    // keys per LDS block of the bf16 kernel: 64 or 96
@@ -341,9 +361,9 @@ hipError_t launch_decode(int dtype, const DecodeArgs& a, const LazyRefs* lazy, h
 // Device address and size of the file-scope scratch array of the decode kernels on the
 // current GPU (looked up once per device; allocates nothing).
 hipError_t decode_static_scratch(float** ptr, size_t* bytes);
-// n_tiles: tiles of kAttnTileRowsF32 flattened rows of all requests, per kv head.  `lazy` non-null
-// (lazy_rope contexts): stored keys are turned to their position as they are read.
-hipError_t launch_attn_f32(const AttnArgs& a, int64_t n_tiles, const LazyRefs* lazy, hipStream_t stream);
+// n_pieces: entries of a.pieces_f32, per kv head.  `lazy` non-null (lazy_rope contexts): stored keys are turned
+// to their position as they are read.
+hipError_t launch_attn_f32(const AttnArgs& a, int64_t n_pieces, const LazyRefs* lazy, hipStream_t stream);
 
 
 // Can the attention launch of this plan carry the linking of the next layer (device-resident

@@ -571,7 +571,6 @@ __global__ __launch_bounds__(kD) void decode_merge_kernel(DecodeArgs a) {
 template <int kD, bool kLazy, bool kUnsplit>
 __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(DecodeArgs a, LazyRefs refs) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int lane = threadIdx.x & 63, col = lane & 31, hi = lane >> 5;
   const int group = a.n_q_heads / a.n_kv_heads;
   const int col_blocks = (group + f32tile::kCols - 1) / f32tile::kCols;
   const int split = blockIdx.x % a.n_splits;
@@ -587,9 +586,7 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
     return;
   }
   const int key1 = min(n_ctx, key0 + a.keys_per_split);
-  float q[kD / 2];
   const int64_t row0 = static_cast<int64_t>(b) * a.n_q_heads + h0;
-  f32tile::load_query<kD>(static_cast<const float*>(a.q) + (row0 + min(col, n_cols - 1)) * kD, hi, q);
   f32tile::Rows src{};
   src.off16 = a.kv_off16 + a.ctx_off[b];
   src.k = static_cast<const char*>(a.k_ctx) + static_cast<int64_t>(g) * kD * 4;
@@ -604,7 +601,8 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
     src.row_bytes = static_cast<int64_t>(a.n_kv_heads) * kD * 4;
     src.interleaved = a.interleaved;
   }
-  f32tile::attend<kD, kLazy>(src, q, key1 - 1, key0, key1, a.scale, lds,
+  f32tile::attend<kD, kLazy>(src, [&](int c) { return static_cast<const char*>(a.q) + (row0 + min(c, n_cols - 1)) * (kD * 4); },
+                             [](float(&)[kD / 2]) {}, key1 - 1, key0, key1, a.scale, lds,
                              [&](int c, int d0, const float(&o)[f32tile::Geo<kD>::kPerThread], float m, float l) {
     if constexpr (kUnsplit) __syncthreads();  // (every thread is here once: what lies in LDS has been read)
     if (c >= n_cols) return;

@@ -328,6 +328,99 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
   while (!p.tiles.empty() && p.tiles.back().n_rows == 0) p.tiles.pop_back();
 }
 
+// Work items of the fp32 attention: tiles of 32 flattened rows, longest first, and where that leaves compute
+// units idle the same launch with the long tiles cut along the keys into even pieces, whose partial results a
+// second launch merges.
+//
+// How long the pieces are is decided by list scheduling over the compute units that one kv head has to itself, a
+// workgroup at a time on each.  Costs in units of 0.85 us: a wavefront multiplies a block of 32 keys in 3.4 us (heads
+// of 64: 1.7) and shares its SIMD with one other, every block it takes costs latencies besides, and so do a
+// workgroup and the merge launch.  Fitted to a sweep of the piece length over nine requests of 300 to 2.5K tokens (both
+// head sizes), where the choice is within 5 % of the best length.  Attention and merge, uncut and cut: 149 rows over 693
+// keys with 32 heads 38.3 -> 26.5 us, 76 over 360 22.5 -> 16.3, 4 heads of 64 over 2.6K keys 64.5 -> 18.4; batches that fill
+// the chip stay whole (396 rows over 1.9K keys with 32 heads 95 us, cut at best 105).
+void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
+  p.tiles_f32.clear();
+  p.pieces_f32.clear();
+  p.merges_f32.clear();
+  p.n_parts_f32 = 0;
+  constexpr int64_t kKeys = 32, kWaves = 8, kSimds = 4;
+  std::vector<AttnPieceF32>& tiles = p.tiles_f32;
+  for (int b = 0; b < p.n_requests; ++b) {
+    const int64_t rows = static_cast<int64_t>(p.q_off[b + 1] - p.q_off[b]) * group;
+    for (int64_t row = 0; row < rows; row += kAttnTileRowsF32) {
+      const int64_t n = std::min<int64_t>(kAttnTileRowsF32, rows - row);
+      const int32_t last = p.q_pos[p.q_off[b] + (row + n - 1) / group];
+      tiles.push_back(AttnPieceF32{b, static_cast<int32_t>(row), static_cast<int32_t>(n), 0, last + 1, -1, p.q_off[b], p.ctx_off[b]});
+    }
+  }
+  auto longer = [](const AttnPieceF32& x, const AttnPieceF32& y) { return x.key1 - x.key0 > y.key1 - y.key0; };
+  std::stable_sort(tiles.begin(), tiles.end(), longer);
+  auto blocks_of = [](const AttnPieceF32& t) { return (t.key1 - t.key0 + kKeys - 1) / kKeys; };
+  const int64_t longest = tiles.empty() ? 0 : blocks_of(tiles.front());
+  if (longest <= kWaves) return;
+  int64_t heads = n_kv_heads, cus = kComputeUnits;
+  while (heads % 2 == 0 && cus > kSimds) heads /= 2, cus /= 2;
+  auto cost = [&](int64_t blocks) {
+    const int64_t on_simd = (blocks + kSimds - 1) / kSimds, rounds = (blocks + kWaves - 1) / kWaves;
+    return head_dim == 64 ? 3 + 2 * on_simd + 3 * rounds : 4 + 4 * on_simd + 5 * rounds;
+  };
+  constexpr int64_t kMergeCost = 3;
+  const int64_t part_rows_per_unit = int64_t{425000} / head_dim;  // (8 bytes a coordinate, 4 TB/s)
+  std::vector<int64_t> load;
+  auto simulate = [&](int64_t cap, int64_t best) {
+    int64_t sum = 0, n_parts = 0;
+    for (const AttnPieceF32& t : tiles) {
+      const int64_t blocks = blocks_of(t), parts = (blocks + cap - 1) / cap;
+      sum += (parts - blocks % parts) * cost(blocks / parts) + blocks % parts * cost(blocks / parts + 1);
+      if (parts > 1) n_parts += parts;
+    }
+    const int64_t merge = n_parts > 0 ? kMergeCost + n_parts * kAttnTileRowsF32 * n_kv_heads / part_rows_per_unit : 0;
+    if (sum * heads / cus + merge >= best) return best;  // cannot be better
+    load.assign(cus, 0);                                 // min-heap
+    const auto heavier = std::greater<int64_t>();
+    int64_t end = 0;
+    for (const AttnPieceF32& t : tiles) {
+      const int64_t blocks = blocks_of(t), parts = (blocks + cap - 1) / cap;
+      for (int64_t i = 0; i < parts * heads; ++i) {
+        std::pop_heap(load.begin(), load.end(), heavier);
+        load.back() += cost(blocks / parts + (i % parts < blocks % parts));
+        end = std::max(end, load.back());
+        std::push_heap(load.begin(), load.end(), heavier);
+        if (end + merge >= best) return best;
+      }
+    }
+    return end + merge;
+  };
+  int64_t total = 0;
+  for (const AttnPieceF32& t : tiles) total += blocks_of(t);
+  if (total * heads >= 4 * longest * cus) return;  // several rounds of the longest tile: even enough
+  int64_t cut = longest, best = simulate(longest, INT64_MAX);
+  best -= best * 5 / 100;  // a cut launch has to be worth its partial results
+  for (int64_t cap = kSimds; cap < longest; cap += std::max<int64_t>(1, cap / 5)) {
+    const int64_t end = simulate(cap, best);
+    if (end < best) {
+      best = end;
+      cut = cap;
+    }
+  }
+  if (cut == longest) return;
+  for (const AttnPieceF32& t : tiles) {
+    const int64_t blocks = blocks_of(t), parts = (blocks + cut - 1) / cut;
+    if (parts > 1) {
+      p.merges_f32.push_back(AttnMerge{t.req, 0, t.row0, t.n_rows, p.n_parts_f32, static_cast<int32_t>(parts), {t.q_off, 0}});
+    }
+    for (int64_t i = 0; i < parts; ++i) {
+      AttnPieceF32 x = t;
+      x.key0 = static_cast<int32_t>(blocks * i / parts * kKeys);
+      x.key1 = std::min(t.key1, static_cast<int32_t>(blocks * (i + 1) / parts * kKeys));
+      if (parts > 1) x.part = p.n_parts_f32++;
+      p.pieces_f32.push_back(x);
+    }
+  }
+  std::stable_sort(p.pieces_f32.begin(), p.pieces_f32.end(), longer);
+}
+
 // Key blocks of a lazy_rope plan (see KeyBlock), as the kernels walk them.  The list of a request
 // holds its fresh blocks first and its stored blocks after them, each part in position order: a
 // kernel that walks a tile in list order changes the shift its queries are turned back by once per
@@ -658,6 +751,7 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
       }
     if (ctx->cfg.fresh_pre_rope) mpic::build_fresh_rope(*p, ctx->cfg);
     mpic::build_tiles(*p, ctx->group, ctx->cfg.n_kv_heads);
+    if (ctx->cfg.dtype == MPIC_F32) mpic::build_pieces_f32(*p, ctx->group, ctx->cfg.n_kv_heads, ctx->cfg.head_dim);
     if (ctx->cfg.lazy_rope) mpic::build_key_blocks(*p);
     {
       auto clamp = [](int64_t x) { return static_cast<int32_t>(std::min<int64_t>(x, INT32_MAX)); };

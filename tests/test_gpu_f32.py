@@ -60,6 +60,31 @@ def test_fp32_tiles(layout, heads):
     _check_decode(p, False, (K, V))
 
 
+# tiles cut along the keys (more than 8 blocks of 32): one block more than stays whole, a ragged last piece, rows at
+# both ends of the context in one tile (the early ones see nothing of the later pieces), a short request beside
+_CUT_LAYOUTS = {
+    "one_more": ([[("chunk", 0, 256, 0), ("text", 1)]], [256], 0),
+    "ragged": ([[("text", 7), ("chunk", 0, 700, None), ("text", 11)]], [700], 9),
+    "both_ends": ([[("text", 9), ("chunk", 0, 1003, 0), ("text", 5)], [("text", 3)]], [1003], 0),
+}
+
+
+@pytest.mark.parametrize("heads", [(4, 4, 64), (6, 2, 128), (40, 1, 64)])
+@pytest.mark.parametrize("layout", sorted(_CUT_LAYOUTS))
+def test_fp32_tiles_cut_along_the_keys(layout, heads):
+    requests, src_len, k = _CUT_LAYOUTS[layout]
+    p = _f32(requests, src_len, k, *heads)
+    p.gpu_setup(False)
+    p.gpu_assemble()
+    p.gpu_attend()
+    torch.cuda.synchronize()
+    K, V = p.oracle_link()
+    O_ref, L_ref = p.oracle_attend(K, V)
+    assert_f32_close(p.out.to(torch.float64).cpu().numpy(), O_ref, "attention output")
+    assert np.abs(p.lse.to(torch.float64).cpu().numpy() - L_ref).max() <= 1e-5 * max(1.0, np.abs(L_ref).max())
+    _run_lazy(_f32(requests, src_len, k, *heads, pre_rope=True))
+
+
 @pytest.mark.parametrize("heads", [(4, 4, 64), (6, 2, 128)])
 @pytest.mark.parametrize("interleaved,pre_rope", [(False, False), (True, True)])
 def test_fp32_tiles_turn_stored_keys_as_they_read_them(heads, interleaved, pre_rope):
