@@ -756,6 +756,15 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     la.head_dim = c.head_dim;
     la.interleaved = c.rope_interleaved;
     la.skip_fresh = 1;
+    if (next->fresh_k) {
+      la.skip_fresh = 0;
+      la.fresh_k = next->fresh_k;
+      la.fresh_v = next->fresh_v;
+      la.fresh_rot = plan->dev.fresh_rot;
+      la.fresh_cos = plan->dev.fresh_cos;
+      la.fresh_sin = plan->dev.fresh_sin;
+      *next->took_fresh = true;
+    }
     mpic::AssembleSrcTable tab{};
     for (size_t i = 0; i < plan->inst_src.size(); ++i) {
       tab.k[i] = next->srcs[plan->inst_src[i]].k;
@@ -957,7 +966,7 @@ extern "C" int mpic_selective_attn_link_next(mpic_ctx* ctx, mpic_plan* plan, con
                                              int64_t n_ctx_slots, double softmax_scale, void* out, float* lse,
                                              const mpic_chunk_src* next_srcs, int32_t n_srcs, void* next_k_ctx,
                                              void* next_v_ctx, void* stream) {
-  const mpic::NextLink next{next_srcs, n_srcs, next_k_ctx, next_v_ctx};
+  const mpic::NextLink next{next_srcs, n_srcs, next_k_ctx, next_v_ctx, nullptr, nullptr, nullptr};
   MPIC_GUARDED(ctx, mpic::attend(ctx, plan, fresh_q, n_fresh_rows, k_ctx, v_ctx, n_ctx_slots, softmax_scale,
                                  out, lse, stream, &next))
 }

@@ -208,6 +208,10 @@ struct NextLink {
   int32_t n_srcs;
   void* k_ctx;
   void* v_ctx;
+  // its fresh rows too (all null: they are left alone); *took_fresh says whether they were
+  const void* fresh_k;
+  const void* fresh_v;
+  bool* took_fresh;
 };
 // refs non-null (lazy_rope contexts): stored rows are read in place in these chunk caches.
 struct SrcRefs {

@@ -660,31 +660,45 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
     return MPIC_OK;
   }
   if (rows_stored == 0 && mpic::can_link_in_attention(ctx, plan) && mpic::link_fits_attention_tail(ctx, plan)) {
+    // The fresh rows of layer l+1 go along where nothing that layer l reads or writes is among the buffers
+    // concerned: a scatter of its own costs 4 us a layer (four layers of a 2.7K-token request 183 -> 165 us).
     std::vector<mpic_chunk_src> next_srcs(std::max(n_srcs, 0));
-    const size_t ctx_bytes = static_cast<size_t>(n_ctx_slots) * st->row_bytes;
-    auto overlap = [&](const void* x, const void* y) {
-      const char* a0 = static_cast<const char*>(x);
-      const char* b0 = static_cast<const char*>(y);
-      return a0 < b0 + ctx_bytes && b0 < a0 + ctx_bytes;
+    struct Span {
+      const void* at;
+      size_t bytes;
     };
-    bool linked = false;  // stored rows of the current layer are already in place
+    auto overlap = [](const Span& x, const Span& y) {
+      const char *a0 = static_cast<const char*>(x.at), *b0 = static_cast<const char*>(y.at);
+      return a0 && b0 && a0 < b0 + y.bytes && b0 < a0 + x.bytes;
+    };
+    const size_t ctx_bytes = static_cast<size_t>(n_ctx_slots) * st->row_bytes;
+    const size_t fresh_bytes = static_cast<size_t>(n_fresh_rows) * st->row_bytes, q_bytes = fresh_bytes * ctx->group;
+    const size_t lse_bytes = static_cast<size_t>(n_fresh_rows) * ctx->cfg.n_q_heads * sizeof(float);
+    bool linked = false, scattered = false;  // stored / fresh rows of the current layer are already in place
     for (int32_t l = 0; l < n_layers; ++l) {
-      if (!linked) {
-        fill_srcs(l, srcs);
-        rc = mpic::assemble_parts(ctx, plan, srcs.data(), n_srcs, nullptr, nullptr, 0, k_ctx[l], v_ctx[l], n_ctx_slots,
-                                  MPIC_PART_CACHED, stream);
+      if (!linked) fill_srcs(l, srcs);
+      if (!linked || !scattered) {
+        rc = mpic::assemble_parts(ctx, plan, linked ? nullptr : srcs.data(), linked ? 0 : n_srcs, fresh_k[l], fresh_v[l], n_fresh_rows,
+                                  k_ctx[l], v_ctx[l], n_ctx_slots, linked ? MPIC_PART_FRESH : MPIC_PART_CACHED | MPIC_PART_FRESH, stream);
         if (rc != MPIC_OK) return rc;
       }
-      rc = mpic::assemble_parts(ctx, plan, nullptr, 0, fresh_k[l], fresh_v[l], n_fresh_rows, k_ctx[l], v_ctx[l],
-                                n_ctx_slots, MPIC_PART_FRESH, stream);
-      if (rc != MPIC_OK) return rc;
-      linked = l + 1 < n_layers && !overlap(k_ctx[l + 1], k_ctx[l]) && !overlap(k_ctx[l + 1], v_ctx[l]) &&
-               !overlap(v_ctx[l + 1], k_ctx[l]) && !overlap(v_ctx[l + 1], v_ctx[l]);
-      mpic::NextLink next{next_srcs.data(), n_srcs, nullptr, nullptr};
+      linked = l + 1 < n_layers;
+      for (const void* next : {l + 1 < n_layers ? k_ctx[l + 1] : nullptr, l + 1 < n_layers ? v_ctx[l + 1] : nullptr})
+        for (const void* now : {k_ctx[l], v_ctx[l]}) linked = linked && !overlap({next, ctx_bytes}, {now, ctx_bytes});
+      scattered = false;
+      mpic::NextLink next{next_srcs.data(), n_srcs, nullptr, nullptr, nullptr, nullptr, &scattered};
       if (linked) {
         fill_srcs(l + 1, next_srcs);
         next.k_ctx = k_ctx[l + 1];
         next.v_ctx = v_ctx[l + 1];
+        const Span in_k{fresh_k[l + 1], fresh_bytes}, in_v{fresh_v[l + 1], fresh_bytes}, to_k{next.k_ctx, ctx_bytes}, to_v{next.v_ctx, ctx_bytes};
+        const Span q{fresh_q[l], q_bytes}, o{out[l], q_bytes}, e{lse ? lse[l] : nullptr, lse_bytes};
+        bool apart = !overlap(in_k, to_k) && !overlap(in_k, to_v) && !overlap(in_v, to_k) && !overlap(in_v, to_v);
+        for (const Span& x : {o, e}) apart = apart && !overlap(x, in_k) && !overlap(x, in_v) && !overlap(x, to_k) && !overlap(x, to_v);
+        if (apart && !overlap(q, to_k) && !overlap(q, to_v)) {
+          next.fresh_k = fresh_k[l + 1];
+          next.fresh_v = fresh_v[l + 1];
+        }
       }
       rc = mpic::attend(ctx, plan, fresh_q[l], n_fresh_rows, k_ctx[l], v_ctx[l], n_ctx_slots, softmax_scale, out[l],
                         lse ? lse[l] : nullptr, stream, linked ? &next : nullptr, ctx->attn_block_keys ? 0 : 96);
