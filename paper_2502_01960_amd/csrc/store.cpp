@@ -706,6 +706,21 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
     }
     return MPIC_OK;
   }
+  // fp32: no attention launch carries linking, and two streams with events and a linking launch held to a
+  // small grid cost more than linking a layer when its turn comes: 26 requests of 100 to 1500 tokens, 2 to 4
+  // layers, 0.45 to 0.77 of the time (two layers of 1023 tokens with 32 heads 302 -> 152 us).
+  if (rows_stored == 0 && ctx->cfg.dtype == MPIC_F32) {
+    for (int32_t l = 0; l < n_layers; ++l) {
+      fill_srcs(l, srcs);
+      rc = mpic::assemble_parts(ctx, plan, srcs.data(), n_srcs, fresh_k[l], fresh_v[l], n_fresh_rows, k_ctx[l], v_ctx[l],
+                                n_ctx_slots, MPIC_PART_CACHED | MPIC_PART_FRESH, stream);
+      if (rc != MPIC_OK) return rc;
+      rc = mpic::attend(ctx, plan, fresh_q[l], n_fresh_rows, k_ctx[l], v_ctx[l], n_ctx_slots, softmax_scale, out[l],
+                        lse ? lse[l] : nullptr, stream, nullptr);
+      if (rc != MPIC_OK) return rc;
+    }
+    return MPIC_OK;
+  }
   std::unordered_map<const void*, int32_t> last_reader;  // context buffer -> layer whose attention read it last
   for (int32_t l = 0; l < n_layers; ++l) {
     if (n_disk > 0) {
