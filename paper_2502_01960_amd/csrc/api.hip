@@ -175,7 +175,7 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   const size_t o_pieces_f32 = put(p->pieces_f32.data(), p->pieces_f32.size() * sizeof(AttnPieceF32));
   // lazy_rope contexts: key blocks, their row-offset tables in both views, tiles in block indices
   size_t o_kblk[kNumBlockSizes] = {}, o_first[kNumBlockSizes] = {}, o_mid[kNumBlockSizes] = {}, o_vctx[kNumBlockSizes] = {},
-         o_vref[kNumBlockSizes] = {}, o_range[kNumBlockSizes] = {};
+         o_vref[kNumBlockSizes] = {}, o_range[kNumBlockSizes] = {}, o_half = 0;
   const bool lazy = ctx->cfg.lazy_rope != 0;
   if (lazy) {
     for (int s = 0; s < kNumBlockSizes; ++s) {
@@ -202,6 +202,7 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
       o_mid[s] = put(p->kblk_mid[s].data(), p->kblk_mid[s].size() * 4);
       o_range[s] = put(p->lazy_range[s].data(), p->lazy_range[s].size() * 4);
     }
+    o_half = put(p->lazy_half.data(), p->lazy_half.size() * 4);
   }
   image.resize(image.size() + 256, 0);
 
@@ -279,6 +280,7 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
       d.kblk_mid[s] = reinterpret_cast<int32_t*>(base + o_mid[s]);
       d.lazy_range[s] = reinterpret_cast<int32_t*>(base + o_range[s]);
     }
+    d.lazy_half = reinterpret_cast<int32_t*>(base + o_half);
   }
   d.block = base;
   d.block_bytes = bytes;
@@ -301,6 +303,7 @@ int fill_lazy_refs(mpic_ctx* ctx, const mpic_plan* plan, int bn, const SrcRefs* 
   r.first = plan->dev.kblk_first[s];
   r.mid = plan->dev.kblk_mid[s];
   r.range = plan->dev.lazy_range[s];
+  r.half = plan->dev.lazy_half;
   r.voff = refs ? plan->dev.voff_ref[s] : plan->dev.voff_ctx[s];
   r.rope_cos = plan->dev.rope_cos;
   r.rope_sin = plan->dev.rope_sin;
@@ -702,6 +705,10 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     a.n_merges = static_cast<int32_t>(plan->merges.size());
   }
   a.block_keys = block_keys ? block_keys : ctx->attn_block_keys ? ctx->attn_block_keys : ctx->background_seen ? 64 : 96;
+  if (lazy && !block_keys && !ctx->attn_block_keys && !ctx->background_seen && plan->n_blocks <= mpic::kHalfTileBlocks) {
+    a.half_tiles = 1;
+    a.block_keys = mpic::kHalfTileBlock;
+  }
   a.q_rot = plan->dev.fresh_rot;
   a.q_cos = plan->dev.fresh_cos;
   a.q_sin = plan->dev.fresh_sin;

@@ -36,26 +36,35 @@ namespace mpic {
 namespace {
 
 constexpr int D = 128;   // head dim
-constexpr int WAVES = 8;
 constexpr int ROWS_PER_WAVE = 32;
-constexpr int THREADS = WAVES * 64;
 constexpr int ROW_BYTES = D * 2;  // one staged key or value row
 
-// Keys per LDS block and what follows from it.  Two shapes are built:
+// Keys per LDS block, wavefronts per workgroup and what follows from them.  Three shapes are built, two of eight
+// wavefronts and one of four:
 //   64 keys: K and V rings of four slots (128 KB), loads two blocks ahead, 202 registers -- leaves
 //            room on every SIMD for a wave of another kernel (linking on a second stream);
 //   96 keys: K ring of two slots, V ring of three (120 KB), loads one block ahead, 238 registers --
 //            a third fewer barriers and phase changes per key, 1 to 2.6 % faster alone, but nothing
-//            fits beside it (two-stream step of 8 requests x 16 chunks: 2.19 -> 2.32 ms).
-template <int kBlockKeys>
+//            fits beside it (two-stream step of 8 requests x 16 chunks: 2.19 -> 2.32 ms);
+//   64 keys, four wavefronts: half a tile, K ring of two slots, V ring of three (80 KB), 244 registers, so that
+//            two workgroups share a compute unit and one computes while the other starts, turns its queries
+//            or stores; and a half walks only the blocks its own rows reach.  Twice the K/V stream per flop makes it 14 %
+//            slower where tiles are long.  Built for caches read in place only: there the kernel of eight
+//            wavefronts spills, and short launches are 4 to 22 % faster in halves (launch_attn_bf16 has the rule), while
+//            those over linked contexts are 0.92 to 1.14 of the time, 1.04 on average.
+template <int kBlockKeys, int kWaves>
 struct Geo {
-  static_assert(kBlockKeys == 64 || kBlockKeys == 96, "block shapes with a ring layout");
+  static_assert((kBlockKeys == 64 && kWaves == 4) || (kWaves == 8 && (kBlockKeys == 64 || kBlockKeys == 96)),
+                "shapes with a ring layout");
   static constexpr int BN = kBlockKeys;
+  static constexpr int WAVES = kWaves;
+  static constexpr int THREADS = kWaves * 64;
+  static constexpr bool DEEP = kBlockKeys == 64 && kWaves == 8;
   static constexpr int KB = BN / 32;                 // 32-key matrix tiles per block
   static constexpr int TILE_BYTES = BN * ROW_BYTES;  // one staged K (or V) block
-  static constexpr int K_SLOTS = BN == 64 ? 4 : 2;
-  static constexpr int V_SLOTS = BN == 64 ? 4 : 3;
-  static constexpr int AHEAD = BN == 64 ? 2 : 1;     // blocks the loads run ahead of their first use
+  static constexpr int K_SLOTS = DEEP ? 4 : 2;
+  static constexpr int V_SLOTS = DEEP ? 4 : 3;
+  static constexpr int AHEAD = DEEP ? 2 : 1;         // blocks the loads run ahead of their first use
   static constexpr int LDS_BYTES = (K_SLOTS + V_SLOTS) * TILE_BYTES;
   static constexpr int ROWS_LOADED_PER_WAVE = BN / WAVES;               // rows of K (and of V) a wave stages per block
   static constexpr int LOADS_PER_STAGE = 2 * ROWS_LOADED_PER_WAVE / 4;  // direct loads each wave issues per block
@@ -71,7 +80,8 @@ struct Geo {
 constexpr int kLinkRounds = 1;
 constexpr int kLinkDepth = 2;   // items a thread of a trailing workgroup keeps in flight
 constexpr float kSumLimit = 4096.0f;  // lazy rescale: a lane's share of a block's row sum may reach this
-static_assert(WAVES * ROWS_PER_WAVE == kAttnTileRows, "tile size and kernel shape must agree");
+constexpr int kHalves = 2;      // workgroups of four wavefronts per tile
+static_assert(8 * ROWS_PER_WAVE == kAttnTileRows && kHalves * 4 * ROWS_PER_WAVE == kAttnTileRows, "tile size and kernel shapes must agree");
 
 // Staged rows are 256 bytes = 16 columns of 16 bytes, unpadded (a direct global->LDS
 // load writes 64 lanes x 16 bytes contiguously).  Bank conflicts are avoided by
@@ -93,6 +103,7 @@ struct LinkNext {
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
+template <int THREADS>
 __device__ inline void link_share(const LinkNext& ln, int j) {
   const link::Shape sh = link::shape_of<__bf16>(ln.args);
   // workgroup j links rows [lo, hi) of the range; a thread keeps its unit pair and walks down
@@ -129,9 +140,11 @@ __device__ inline void link_share(const LinkNext& ln, int j) {
   }
 }
 
-template <int kBlockKeys, typename Extra, int kAblate = 0>
-__global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra extra) {
-  using G = Geo<kBlockKeys>;
+template <int kBlockKeys, int kWaves, typename Extra, int kAblate = 0>
+__global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, Extra extra) {
+  using G = Geo<kBlockKeys, kWaves>;
+  constexpr bool kHalf = kWaves == 4;  // (see Geo)
+  static_assert(!kHalf || std::is_same<Extra, LazyRefs>::value, "only caches in place are attended in half tiles");
   constexpr int BN = G::BN, KB = G::KB, TILE_BYTES = G::TILE_BYTES, AHEAD = G::AHEAD;
   constexpr int ROWS_LOADED_PER_WAVE = G::ROWS_LOADED_PER_WAVE, LOADS_PER_STAGE = G::LOADS_PER_STAGE;
   auto k_slot_off = [](int t) { return G::k_slot_off(t); };
@@ -140,12 +153,17 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
 
   if constexpr (std::is_same<Extra, LinkNext>::value) {
     if (static_cast<int>(blockIdx.x) >= a.n_tiles) {
-      link_share(extra, static_cast<int>(blockIdx.x) - a.n_tiles);
+      link_share<G::THREADS>(extra, static_cast<int>(blockIdx.x) - a.n_tiles);
       return;
     }
   }
-  const AttnTile tile = a.tiles[blockIdx.x];
-  if (tile.n_rows <= 0) return;  // padding entry of the launch order
+  // both halves of a tile on the L2 domain that the launch order gives it
+  const int tile_no = kHalf ? static_cast<int>(blockIdx.x / (8 * kHalves) * 8 + blockIdx.x % 8) : static_cast<int>(blockIdx.x);
+  const int half = kHalf ? static_cast<int>(blockIdx.x / 8 % kHalves) : 0;
+  if (kHalf && tile_no >= a.n_tiles) return;
+  const AttnTile tile = a.tiles[tile_no];
+  const int first_row = half * kWaves * ROWS_PER_WAVE;
+  if (tile.n_rows <= first_row) return;  // padding entry of the launch order, or a tile without a second half
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
@@ -163,7 +181,8 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
   // batch's block list (its request's fresh part and stored part); step t of the walk is block bid(t)
   int fb = 0, nf = 0, sb = 0, ns = 0;
   if constexpr (kLazy) {
-    const i32x4 rg = *(const __attribute__((address_space(4))) i32x4*)(extra.range + 4 * static_cast<int64_t>(blockIdx.x));
+    const int32_t* ranges = kHalf ? extra.half + 4 * (kHalves * static_cast<int64_t>(tile_no) + half) : extra.range + 4 * static_cast<int64_t>(tile_no);
+    const i32x4 rg = *(const __attribute__((address_space(4))) i32x4*)ranges;
     fb = extra.first[b] + rg[0];
     nf = rg[1] - rg[0];
     sb = extra.mid[b] + rg[2];
@@ -178,7 +197,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, lds)));
 
   // ---- this lane's query ----
-  const int local = wave * ROWS_PER_WAVE + col;
+  const int local = first_row + wave * ROWS_PER_WAVE + col;
   const bool valid = local < tile.n_rows;
   const int flat = tile.row0 + (valid ? local : 0);
   // lazy: keys of the fresh part this row sees (it is one of them); of the stored part it sees the rest
@@ -360,8 +379,12 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
     } else if constexpr (kLoadPairs == 3) {
       load3x2_to_lds_16B(static_cast<const char*>(gk[0]), static_cast<const char*>(gk[1]), static_cast<const char*>(gk[2]),
                          static_cast<const char*>(gv[0]), static_cast<const char*>(gv[1]), static_cast<const char*>(gv[2]), dk, dv);
+    } else if constexpr (kLoadPairs == 4) {
+      load4x2_to_lds_16B(static_cast<const char*>(gk[0]), static_cast<const char*>(gk[1]), static_cast<const char*>(gk[2]),
+                         static_cast<const char*>(gk[3]), static_cast<const char*>(gv[0]), static_cast<const char*>(gv[1]),
+                         static_cast<const char*>(gv[2]), static_cast<const char*>(gv[3]), dk, dv);
     } else {
-      static_assert(kLoadPairs == 2 || kLoadPairs == 3, "rows staged per wavefront and block");
+      static_assert(kLoadPairs >= 2 && kLoadPairs <= 4, "rows staged per wavefront and block");
       static_assert(4 * ROW_BYTES == 1024, "the loaders step 1024 bytes from one load to the next");
       load2x2_to_lds_16B(static_cast<const char*>(gk[0]), static_cast<const char*>(gk[1]), static_cast<const char*>(gv[0]),
                          static_cast<const char*>(gv[1]), dk, dv);
@@ -661,7 +684,28 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
     }
     __builtin_amdgcn_s_setprio(0);
   };
-  if constexpr (kLazy) {
+  if constexpr (kHalf) {
+    // Four wavefronts, one on every SIMD, beside those of another workgroup, which fill each other's gaps.  All run in step: a
+    // barrier per block, behind which block t is complete and the slots of K of block t - 1 and V of block
+    // t - 2 have been read.
+    bool prev_needed = false;
+    KeyBlock cur = desc_of(0), nxt = desc_of(1);
+    for (int t = 0; t <= n_iter; ++t) {
+      const bool needed = t < n_iter && cur.pos0 <= wave_hi_pos;
+      even_sync(t);
+      matrix_part(t, needed, prev_needed, cur.inst);
+      ro = fetch_rows(t + AHEAD + 1);
+      const KeyBlock nxt2 = desc_of(t + 2);
+      if (t + 1 < n_iter && nxt.pos0 <= wave_hi_pos && nxt.inst != q_inst) fetch_q();
+      if (needed) {
+        kd = cur;
+        softmax_block(t);
+      }
+      prev_needed = needed;
+      cur = nxt;
+      nxt = nxt2;
+    }
+  } else if constexpr (kLazy) {
     // the same two loops over the tile's key blocks: a block is needed while its first position
     // is within the wave's reach.  Descriptors are fetched two steps ahead at the start of the
     // softmax phase, like the row offsets, so that nothing waits for a scalar load.  When the
@@ -748,7 +792,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(AttnArgs a, Extra
     const bool seen = sees();
     const float inv_p = seen ? 1.f / l_tot : 0.f;
     const int64_t slot = static_cast<int64_t>(tile.part) * kAttnTileRows + local;
-    float* po = a.ws_o + static_cast<int64_t>(tile.part) * kAttnTileRows * D + (wave * 16 * 64 + lane) * 4;
+    float* po = a.ws_o + static_cast<int64_t>(tile.part) * kAttnTileRows * D + ((half * kWaves + wave) * 16 * 64 + lane) * 4;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -845,16 +889,17 @@ inline int64_t n_pos_of(const AssembleArgs* next) { return next ? next->pos_end 
 template <int kBlockKeys>
 hipError_t launch_shape(const AttnArgs& a, const AssembleArgs* next, const AssembleSrcTable* next_tab,
                         const LazyRefs* lazy, int dev, hipStream_t stream) {
-  using G = Geo<kBlockKeys>;
+  using G = Geo<kBlockKeys, 8>;
+  constexpr int THREADS = G::THREADS;
   static LdsOptIn opt_in;  // one per kernel shape
   const hipError_t eo = opt_in.ensure(dev, [] {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, NoLink>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, 8, NoLink>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, LinkNext>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, 8, LinkNext>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, LazyRefs>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, 8, LazyRefs>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES);
   });
   if (eo != hipSuccess) return eo;
@@ -864,11 +909,11 @@ hipError_t launch_shape(const AttnArgs& a, const AssembleArgs* next, const Assem
       constexpr int kM = decltype(mask)::value;
       static LdsOptIn probe_opt_in;
       const hipError_t e = probe_opt_in.ensure(dev, [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, NoLink, kM>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kBlockKeys, 8, NoLink, kM>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES);
       });
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, NoLink, kM>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
+      hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, 8, NoLink, kM>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
                          NoLink{});
       return hipSuccess;
     };
@@ -889,7 +934,7 @@ hipError_t launch_shape(const AttnArgs& a, const AssembleArgs* next, const Assem
   }
 #endif
   if (lazy) {
-    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, LazyRefs>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
+    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, 8, LazyRefs>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
                        *lazy);
     return hipSuccess;
   }
@@ -903,12 +948,25 @@ hipError_t launch_shape(const AttnArgs& a, const AssembleArgs* next, const Assem
     const int64_t rows_per_pass = THREADS / (next->n_kv_heads * (next->head_dim / 2 / 8));
     const int64_t rows_per_wg = kLinkRounds * kLinkDepth * rows_per_pass;
     ln.n_wgs = static_cast<int32_t>(std::max<int64_t>(1, (n_pos + rows_per_wg - 1) / rows_per_wg));
-    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, LinkNext>), dim3(a.n_tiles + ln.n_wgs), dim3(THREADS), G::LDS_BYTES,
+    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, 8, LinkNext>), dim3(a.n_tiles + ln.n_wgs), dim3(THREADS), G::LDS_BYTES,
                        stream, a, ln);
   } else {
-    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, NoLink>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
+    hipLaunchKernelGGL((attn_bf16_kernel<kBlockKeys, 8, NoLink>), dim3(a.n_tiles), dim3(THREADS), G::LDS_BYTES, stream, a,
                        NoLink{});
   }
+  return hipSuccess;
+}
+
+hipError_t launch_halves(const AttnArgs& a, const LazyRefs& lazy, int dev, hipStream_t stream) {
+  using G = Geo<kHalfTileBlock, 4>;
+  static LdsOptIn opt_in;
+  const hipError_t e = opt_in.ensure(dev, [] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bf16_kernel<kHalfTileBlock, 4, LazyRefs>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES);
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bf16_kernel<kHalfTileBlock, 4, LazyRefs>), dim3((a.n_tiles + 7) / 8 * 8 * kHalves), dim3(G::THREADS),
+                     G::LDS_BYTES, stream, a, lazy);
   return hipSuccess;
 }
 
@@ -920,8 +978,9 @@ hipError_t launch_attn_bf16(const AttnArgs& a, const AssembleArgs* next, const A
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  e = a.block_keys == 96 ? launch_shape<96>(a, next, next_tab, lazy, dev, stream)
-                         : launch_shape<64>(a, next, next_tab, lazy, dev, stream);
+  e = a.half_tiles && lazy ? launch_halves(a, *lazy, dev, stream)
+      : a.block_keys == 96 ? launch_shape<96>(a, next, next_tab, lazy, dev, stream)
+                           : launch_shape<64>(a, next, next_tab, lazy, dev, stream);
   if (e != hipSuccess) return e;
   if (a.n_merges > 0)
     hipLaunchKernelGGL(attn_merge_kernel, dim3(a.n_merges, kAttnTileRows / 8), dim3(256), 0, stream, a);

@@ -64,6 +64,7 @@ struct KeyBlock {
 static_assert(sizeof(KeyBlock) == 16, "key block layout");
 constexpr int kNumBlockSizes = 3;
 constexpr int kBlockSizes[kNumBlockSizes] = {32, 64, 96};  // decode kernel, attention kernel shapes
+constexpr int kHalfTileBlock = 64;  // keys per block where two workgroups share a tile of the attention kernel
 inline int block_size_index(int bn) { return bn == 32 ? 0 : bn == 64 ? 1 : 2; }
 
 // Device-resident copy of a plan.
@@ -92,6 +93,7 @@ struct PlanDevice {
   uint32_t* voff_ref[kNumBlockSizes] = {};    // the same with stored rows addressed inside their source
   int32_t* kblk_mid[kNumBlockSizes] = {};     // [B] first stored block of each request
   int32_t* lazy_range[kNumBlockSizes] = {};   // [n_tiles][4] block ranges of every tile: fresh [f0, f1), stored [s0, s1)
+  int32_t* lazy_half = nullptr;               // [n_tiles][2][4] the same of its halves of rows (blocks of kHalfTileBlock keys)
   void* block = nullptr;  // the single allocation all of the above point into
   size_t block_bytes = 0;
   int device = -1;
@@ -169,6 +171,7 @@ struct mpic_plan {
   // last workgroup ends, and the compute-unit time left idle until then (summed over the chip)
   int64_t est_makespan_blocks = 0;
   int64_t est_idle_blocks = 0;
+  int64_t n_blocks = 0;  // 64-key blocks of all tiles
   std::vector<int32_t> launch_est;  // MPIC_PLAN_LAUNCH_ESTIMATE
   std::vector<float> rope_cos, rope_sin;
   // contexts with lazy_rope only: key blocks per block size, first block of every request,
@@ -178,6 +181,7 @@ struct mpic_plan {
   std::vector<int32_t> kblk_first[mpic::kNumBlockSizes];
   std::vector<int32_t> kblk_mid[mpic::kNumBlockSizes];    // [B] first stored block of every request (its fresh blocks come first)
   std::vector<int32_t> lazy_range[mpic::kNumBlockSizes];  // [n_tiles][4] fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
+  std::vector<int32_t> lazy_half;  // [n_tiles][2][4] the same for the halves of every tile (kHalfTileBlock)
   std::vector<int32_t> kblk_parts[mpic::kNumBlockSizes];  // [B][3] first fresh block, first stored block, end, for mpic_plan_get
   std::vector<int32_t> fresh_rot;            // contexts with fresh_pre_rope only
   std::vector<float> fresh_cos, fresh_sin;   // one row per distinct position id
@@ -281,6 +285,7 @@ struct AttnArgs {
   const AttnMerge* merges;
   int32_t n_merges;
   int32_t block_keys;    // keys per LDS block of the bf16 kernel: 64 or 96
+  int32_t half_tiles;    // 1 (caches read in place): two workgroups of four wavefronts per tile, kHalfTileBlock keys per block
   const int32_t* q_rot;  // non-null: queries are rotated with row q_rot[r] of q_cos / q_sin on load
   const float* q_cos;
   const float* q_sin;
@@ -304,6 +309,10 @@ enum { kAblateLoads = 1,     // K/V blocks are staged only until every ring slot
        kAblateNoLoadWaits = 32,    // no wait for staged blocks inside the loop (only with kAblateLdsReads)
        kAblateAddressesOnly = 64 };// the addresses of the direct loads are formed, the loads are not issued
 constexpr int kProbeOptionAblate = 1000;  // mpic_set_option of the probe library: value = mask of kAblate*
+// Launches over caches read in place of up to this many 64-key blocks per compute unit run in half tiles: of 51 drawn batches
+// below it 46 took 0.78 to 0.99 of the time of the 96-key shape (0.91 on average, 1.11 at most), of 19 above it 15
+// were 0 to 14 % slower.
+constexpr int64_t kHalfTileBlocks = 180 * 256;
 // Contexts with lazy_rope: stored keys are never turned to their global position.  The kernel
 // walks the request's key blocks (KeyBlock: all keys of a block come from one source and lack
 // the same shift) and turns its *queries* back by that shift whenever the
@@ -315,6 +324,7 @@ struct LazyRefs {
   const int32_t* first;    // [B+1] first block of every request (its fresh blocks, then its stored blocks)
   const int32_t* mid;      // [B] first stored block of every request
   const int32_t* range;    // [n_tiles][4] attention kernel: fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
+  const int32_t* half;     // [n_tiles][2][4] the same of its halves of rows
   const uint32_t* voff;    // [n_blocks][BN] row offsets (16-byte units) from the block's base
   const float* rope_cos;   // [n_inst][D/2] cos / sin of every instance's shift
   const float* rope_sin;

@@ -106,6 +106,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     }
   }
   const int64_t per_cu = (total_blocks + kComputeUnits - 1) / kComputeUnits;
+  p.n_blocks = total_blocks;
   // How a tile of `blocks` blocks is cut: tiles longer than `cap` into even pieces, or into pieces
   // of exactly `cap` and a remainder.  Even pieces suit launches of one round, where the longest
   // piece decides; equal pieces with remainders fill the end of a launch of several.
@@ -427,8 +428,9 @@ void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
 // chunk instance (softmax does not care about the order of the keys).  A tile visits the blocks
 // that start at or before its last row, a prefix of both parts; the pieces of a tile that was cut
 // along the keys share those blocks in proportion to their key ranges, in list order.
-void build_key_blocks(mpic_plan& p) {
+void build_key_blocks(mpic_plan& p, int group) {
   const int B = p.n_requests;
+  p.lazy_half.clear();
   p.key_order.clear();
   p.key_order.reserve(p.n_ctx);
   for (int b = 0; b < B; ++b) {
@@ -475,6 +477,7 @@ void build_key_blocks(mpic_plan& p) {
     for (const AttnTile& t : p.tiles) {
       if (t.n_rows <= 0) {
         ranges.insert(ranges.end(), {0, 0, 0, 0});
+        if (bn == kHalfTileBlock) p.lazy_half.insert(p.lazy_half.end(), 8, 0);
         continue;
       }
       const int32_t end = t.part >= 0 ? tile_end[t.part] : t.n_keys;
@@ -489,7 +492,27 @@ void build_key_blocks(mpic_plan& p) {
       const int32_t nf = before_end(first[t.req], mid[t.req]), ns = before_end(mid[t.req], first[t.req + 1]);
       const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.key0 / end);
       const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.n_keys / end);
-      ranges.insert(ranges.end(), {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf});
+      const int32_t r[4] = {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf};
+      ranges.insert(ranges.end(), r, r + 4);
+      if (bn != kHalfTileBlock) continue;
+      // the same for the tile's halves of rows: the first one reaches less far (at least one block each, so that
+      // a half whose rows see nothing of a piece has something to walk)
+      for (int32_t row = 0; row < kAttnTileRows; row += kAttnTileRows / 2) {
+        if (row >= t.n_rows) {
+          p.lazy_half.insert(p.lazy_half.end(), {0, 0, 0, 0});
+          continue;
+        }
+        const int32_t last_row = t.row0 + std::min(t.n_rows, row + kAttnTileRows / 2) - 1;
+        const int32_t reach = p.q_pos[p.q_off[t.req] + last_row / group];
+        auto up_to = [&](int32_t lo_blk, int32_t hi_blk) {  // first block of [lo_blk, hi_blk) that starts behind the reach
+          return static_cast<int32_t>(std::upper_bound(blocks.data() + lo_blk, blocks.data() + hi_blk, reach,
+                                                       [](int32_t v, const KeyBlock& k) { return v < k.pos0; }) - blocks.data());
+        };
+        int32_t f1 = up_to(first[t.req] + r[0], first[t.req] + r[1]) - first[t.req];
+        int32_t s1 = up_to(mid[t.req] + r[2], mid[t.req] + r[3]) - mid[t.req];
+        if (f1 == r[0] && s1 == r[2]) (r[0] < r[1] ? f1 : s1) += 1;
+        p.lazy_half.insert(p.lazy_half.end(), {r[0], f1, r[2], s1});
+      }
     }
   }
 }
@@ -752,7 +775,7 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
     if (ctx->cfg.fresh_pre_rope) mpic::build_fresh_rope(*p, ctx->cfg);
     mpic::build_tiles(*p, ctx->group, ctx->cfg.n_kv_heads);
     if (ctx->cfg.dtype == MPIC_F32) mpic::build_pieces_f32(*p, ctx->group, ctx->cfg.n_kv_heads, ctx->cfg.head_dim);
-    if (ctx->cfg.lazy_rope) mpic::build_key_blocks(*p);
+    if (ctx->cfg.lazy_rope) mpic::build_key_blocks(*p, ctx->group);
     {
       auto clamp = [](int64_t x) { return static_cast<int32_t>(std::min<int64_t>(x, INT32_MAX)); };
       p->launch_est = {clamp(p->est_makespan_blocks), clamp(p->est_idle_blocks),

@@ -92,6 +92,23 @@ __device__ inline void load3x2_to_lds_16B(const char* k0, const char* k1, const 
       : "v"(k0), "v"(k1 - 1024), "v"(k2 - 2048), "v"(v0), "v"(v1 - 1024), "v"(v2 - 2048), "s"(lk), "s"(lv)
       : "memory", "m0");
 }
+__device__ inline void load4x2_to_lds_16B(const char* k0, const char* k1, const char* k2, const char* k3, const char* v0,
+                                          const char* v1, const char* v2, const char* v3, uint32_t lk, uint32_t lv) {
+  asm volatile(
+      "s_mov_b32 m0, %8\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, off\n\t"
+      "global_load_lds_dwordx4 %1, off offset:1024\n\t"
+      "global_load_lds_dwordx4 %2, off offset:2048\n\t"
+      "global_load_lds_dwordx4 %3, off offset:3072\n\t"
+      "s_mov_b32 m0, %9\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %4, off\n\t"
+      "global_load_lds_dwordx4 %5, off offset:1024\n\t"
+      "global_load_lds_dwordx4 %6, off offset:2048\n\t"
+      "global_load_lds_dwordx4 %7, off offset:3072"
+      :
+      : "v"(k0), "v"(k1 - 1024), "v"(k2 - 2048), "v"(k3 - 3072), "v"(v0), "v"(v1 - 1024), "v"(v2 - 2048), "v"(v3 - 3072), "s"(lk), "s"(lv)
+      : "memory", "m0");
+}
 __device__ inline void load2x2_to_lds_16B(const char* k0, const char* k1, const char* v0, const char* v1, uint32_t lk,
                                           uint32_t lv) {
   asm volatile(

@@ -1,0 +1,36 @@
+"""Attention over caches read in place in half tiles (needs an MI355X): tiles with no second half, with
+one row in it, rows that straddle it, pieces that a half sees nothing of, and head groupings whose heads
+split over the halves; both lazy routes against the oracle at the gates of the lazy tests."""
+import pytest
+
+from test_gpu_decode_sizes import _bf16
+from test_gpu_lazy import _run_lazy
+from test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+
+# fresh rows per request (one kv head: as many flattened rows): up to the half, one more, a whole tile, one more
+@pytest.mark.parametrize("heads", [(1, 1), (3, 1), (28, 4)])
+@pytest.mark.parametrize("fresh", [1, 127, 128, 129, 256, 257])
+def test_rows_around_the_half(fresh, heads):
+    p = _bf16((fresh + 300, 40), *heads)
+    requests = [[("text", fresh // 2), ("chunk", 0, p.src_len[0], 0), ("text", fresh - fresh // 2)], p.requests[1]]
+    q = _custom(requests, 2, p.src_len, 5)
+    q.sh = p.sh
+    import torch
+    import workloads
+    q.chunks = {s: workloads.gen_chunk(q.sh, 0, s, q.src_len[s]) for s in q.chunks}
+    q_off = q.oplan["q_off"]
+    rows = [workloads.gen_fresh(q.sh, 0, b, int(q_off[b + 1] - q_off[b])) for b in range(2)]
+    q.q, q.fresh_k, q.fresh_v = (torch.cat([r[i] for r in rows]) for i in range(3))
+    _run_lazy(q)
+
+
+@pytest.mark.parametrize("pre_rope,interleaved", [(False, False), (True, True)])
+def test_halves_of_cut_tiles(pre_rope, interleaved):
+    """One long request: pieces along the keys, the first half of whose rows sits at the start of the context."""
+    requests = [[("text", 40), ("chunk", 0, 1900, 7), ("text", 30), ("chunk", 1, 700, None), ("text", 9)]]
+    p = _custom(requests, 2, [1900, 700], 3)
+    p.pre_rope, p.interleaved = pre_rope, interleaved
+    _run_lazy(p)
