@@ -782,9 +782,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   }
 
   // ---- epilogue: normalise and store this lane's query column ----
-  if (!valid) return;
   const float l_tot = sum_across_halves(l_run);
   if (tile.part >= 0) {
+    if (!valid) return;
     // piece of a tile cut along the keys: normalised fp32 partial + log-sum-exp for the merge
     // kernel.  A row that lies below key0 saw no key (its registers may hold NaN: selected
     // away, never multiplied).  The partials lie in the order the registers have (see part_off):
@@ -806,7 +806,28 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     return;
   }
   const float inv = 1.f / l_tot;
-  __bf16* op = static_cast<__bf16*>(a.out) + (fresh_row * a.n_q_heads + head) * D;
+  if (kLazy || tile.n_rows <= kAttnTileRows / 2) {
+    if (!valid) return;
+    __bf16* op = static_cast<__bf16*>(a.out) + (fresh_row * a.n_q_heads + head) * D;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = acc_o[db][q4 * 4 + e] * inv;
+        *reinterpret_cast<bf16x4*>(op + db * 32 + q4 * 8 + hi * 4) = __builtin_convertvector(o, bf16x4);
+      }
+    if (a.lse && hi == 0) a.lse[fresh_row * a.n_q_heads + head] = m_run * a.scale + logf(l_tot);
+    return;
+  }
+  // Tall tiles go through LDS, so that the stores are runs of 256 bytes: eight bytes of 32 rows at a time, as the lanes
+  // hold them, take a tile 1.2 us more (attention of launches of one to four tiles per compute unit 0.95 to 0.99 of the
+  // time).  Launches of low tiles are over so soon that the way through LDS costs more (1.0 to 1.1 of the time), and
+  // in the kernels for caches in place it adds to what they spill (1.03 where tiles are long).
+  // Chunk c of 16 bytes of row r lies at chunk c ^ (r & 15).  Behind a barrier, since the rings are still read.
+  __syncthreads();
+  char* area = lds + wave * (ROWS_PER_WAVE * ROW_BYTES);
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -814,9 +835,29 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
       f32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = acc_o[db][q4 * 4 + e] * inv;
-      *reinterpret_cast<bf16x4*>(op + db * 32 + q4 * 8 + hi * 4) = __builtin_convertvector(o, bf16x4);
+      *reinterpret_cast<bf16x4*>(area + col * ROW_BYTES + (((db * 4 + q4) ^ (col & 15)) << 4) + hi * 8) = __builtin_convertvector(o, bf16x4);
     }
-  if (a.lse && hi == 0) a.lse[fresh_row * a.n_q_heads + head] = m_run * a.scale + logf(l_tot);
+  if (a.lse && hi == 0 && valid) a.lse[fresh_row * a.n_q_heads + head] = m_run * a.scale + logf(l_tot);
+  // lane i of step p stores chunk i & 15 of row 4 p + (i >> 4); (from a copy of the lane number that the compiler cannot
+  // connect with the one above, or what follows from it would be held across the loop)
+  int ln = lane;
+  asm volatile("" : "+v"(ln));
+  int r = ln >> 4;
+  int quot = (tile.row0 + first_row + wave * ROWS_PER_WAVE + r) / group;
+  int rem = tile.row0 + first_row + wave * ROWS_PER_WAVE + r - quot * group;
+#pragma unroll
+  for (int p = 0; p < ROWS_PER_WAVE / 4; ++p) {
+    const bf16x8 x = *reinterpret_cast<const bf16x8*>(area + r * ROW_BYTES + (((ln & 15) ^ (r & 15)) << 4));
+    const int64_t item = (a.q_off[b] + static_cast<int64_t>(quot)) * a.n_q_heads + g * group + rem;
+    if (first_row + wave * ROWS_PER_WAVE + r < tile.n_rows)
+      *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + item * ROW_BYTES + ((ln & 15) << 4)) = x;
+    r += 4;
+    quot += 4 / group;
+    rem += 4 % group;
+    const bool over = rem >= group;
+    quot += over ? 1 : 0;
+    rem -= over ? group : 0;
+  }
 }
 
 
