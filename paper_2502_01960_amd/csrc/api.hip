@@ -122,6 +122,27 @@ Scratch* spare_attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t str
   return w;
 }
 
+// The tiles of a plan as the bf16 attention kernel reads them (padding entries stay empty).
+std::vector<AttnWork> attn_work(const mpic_plan& p) {
+  std::vector<AttnWork> work(p.tiles.size());
+  for (size_t i = 0; i < work.size(); ++i) {
+    const AttnTile& t = p.tiles[i];
+    if (t.n_rows > 0) work[i] = AttnWork{t.kv_head, t.row0, t.n_rows, t.n_keys, t.key0, t.part, p.q_off[t.req], p.ctx_off[t.req]};
+  }
+  return work;
+}
+
+// Block ranges of the tiles ([n_tiles][..][4], relative to their requests) as indices into the batch's block list, for the
+// same reason.
+std::vector<int32_t> ranges_in_batch(const mpic_plan& p, int s, std::vector<int32_t> ranges) {
+  const size_t per_tile = p.tiles.empty() ? 0 : ranges.size() / p.tiles.size();
+  for (size_t i = 0; i < ranges.size(); ++i) {
+    const AttnTile& t = p.tiles[i / per_tile];
+    if (t.n_rows > 0) ranges[i] += i % 4 < 2 ? p.kblk_first[s][t.req] : p.kblk_mid[s][t.req];
+  }
+  return ranges;
+}
+
 // Copy the integer maps, rotary tables and tile list to the GPU (once per plan): the tables
 // are packed into one host image that crosses the bus in a single copy into a single
 // allocation.  May throw std::bad_alloc (host image); the entry points catch it.
@@ -168,13 +189,14 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
   const size_t o_fresh_rot = put(p->fresh_rot.data(), p->fresh_rot.size() * 4);
   const size_t o_fresh_cos = put(p->fresh_cos.data(), p->fresh_cos.size() * 4);
   const size_t o_fresh_sin = put(p->fresh_sin.data(), p->fresh_sin.size() * 4);
-  const size_t o_tiles = put(p->tiles.data(), p->tiles.size() * sizeof(AttnTile));
+  const std::vector<AttnWork> work = attn_work(*p);
+  const size_t o_tiles = put(work.data(), work.size() * sizeof(AttnWork));
   const std::vector<AttnMerge>& merges = ctx->cfg.dtype == MPIC_F32 ? p->merges_f32 : p->merges;
   const size_t o_merges = put(merges.data(), merges.size() * sizeof(AttnMerge));
   const size_t o_tiles_f32 = put(p->tiles_f32.data(), p->tiles_f32.size() * sizeof(AttnPieceF32));
   const size_t o_pieces_f32 = put(p->pieces_f32.data(), p->pieces_f32.size() * sizeof(AttnPieceF32));
   // lazy_rope contexts: key blocks, their row-offset tables in both views, tiles in block indices
-  size_t o_kblk[kNumBlockSizes] = {}, o_first[kNumBlockSizes] = {}, o_mid[kNumBlockSizes] = {}, o_vctx[kNumBlockSizes] = {},
+  size_t o_kblk[kNumBlockSizes] = {}, o_first[kNumBlockSizes] = {}, o_vctx[kNumBlockSizes] = {},
          o_vref[kNumBlockSizes] = {}, o_range[kNumBlockSizes] = {}, o_half = 0;
   const bool lazy = ctx->cfg.lazy_rope != 0;
   if (lazy) {
@@ -199,10 +221,11 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
       o_first[s] = put(p->kblk_first[s].data(), p->kblk_first[s].size() * 4);
       o_vctx[s] = put(vctx.data(), vctx.size() * 4);
       o_vref[s] = put(vref.data(), vref.size() * 4);
-      o_mid[s] = put(p->kblk_mid[s].data(), p->kblk_mid[s].size() * 4);
-      o_range[s] = put(p->lazy_range[s].data(), p->lazy_range[s].size() * 4);
+      const std::vector<int32_t> ranges = ranges_in_batch(*p, s, p->lazy_range[s]);
+      o_range[s] = put(ranges.data(), ranges.size() * 4);
     }
-    o_half = put(p->lazy_half.data(), p->lazy_half.size() * 4);
+    const std::vector<int32_t> halves = ranges_in_batch(*p, block_size_index(kHalfTileBlock), p->lazy_half);
+    o_half = put(halves.data(), halves.size() * 4);
   }
   image.resize(image.size() + 256, 0);
 
@@ -267,7 +290,7 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
     d.fresh_cos = reinterpret_cast<float*>(base + o_fresh_cos);
     d.fresh_sin = reinterpret_cast<float*>(base + o_fresh_sin);
   }
-  d.tiles = reinterpret_cast<AttnTile*>(base + o_tiles);
+  d.tiles = reinterpret_cast<AttnWork*>(base + o_tiles);
   d.merges = reinterpret_cast<AttnMerge*>(base + o_merges);
   d.tiles_f32 = reinterpret_cast<AttnPieceF32*>(base + o_tiles_f32);
   d.pieces_f32 = reinterpret_cast<AttnPieceF32*>(base + o_pieces_f32);
@@ -277,7 +300,6 @@ int upload_plan(mpic_ctx* ctx, mpic_plan* p, hipStream_t stream) {
       d.kblk_first[s] = reinterpret_cast<int32_t*>(base + o_first[s]);
       d.voff_ctx[s] = reinterpret_cast<uint32_t*>(base + o_vctx[s]);
       d.voff_ref[s] = reinterpret_cast<uint32_t*>(base + o_vref[s]);
-      d.kblk_mid[s] = reinterpret_cast<int32_t*>(base + o_mid[s]);
       d.lazy_range[s] = reinterpret_cast<int32_t*>(base + o_range[s]);
     }
     d.lazy_half = reinterpret_cast<int32_t*>(base + o_half);
@@ -301,7 +323,6 @@ int fill_lazy_refs(mpic_ctx* ctx, const mpic_plan* plan, int bn, const SrcRefs* 
   LazyRefs r{};
   r.blocks = plan->dev.kblk[s];
   r.first = plan->dev.kblk_first[s];
-  r.mid = plan->dev.kblk_mid[s];
   r.range = plan->dev.lazy_range[s];
   r.half = plan->dev.lazy_half;
   r.voff = refs ? plan->dev.voff_ref[s] : plan->dev.voff_ctx[s];
@@ -681,8 +702,6 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
   a.tiles = plan->dev.tiles;
   a.n_tiles = static_cast<int32_t>(plan->tiles.size());
   a.q_pos = plan->dev.q_pos;
-  a.q_off = plan->dev.q_off;
-  a.ctx_off = plan->dev.ctx_off;
   a.dst_slot = plan->dev.dst_slot;
   a.kv_off16 = plan->dev.kv_off16;
   a.q = fresh_q;

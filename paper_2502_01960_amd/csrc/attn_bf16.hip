@@ -140,6 +140,25 @@ __device__ inline void link_share(const LinkNext& ln, int j) {
   }
 }
 
+// Short launches wait for memory most of their time, so what a workgroup has to know before its first loads comes in few
+// trips.  Left to itself the compiler fetches the row count of a tile, waits, fetches the rest, and waits again for the ranges.
+// (With the request's offsets in the tile, ranges that need no others, and positions fetched without a branch: request of
+// 2.6K tokens, 32 heads, linked and attended 48.2 -> 47.8 us, one turn of a conversation 68.2 -> 67.2, two requests in
+// place 119.4 -> 118.8.)
+struct TileAndRanges {
+  AttnWork tile;
+  int ranges[4];  // lazy: blocks of the tile or half, zero otherwise
+};
+template <bool kRanges>
+__device__ inline TileAndRanges load_tile(const AttnWork* work, const int32_t* ranges) {
+  typedef int i32x8 __attribute__((ext_vector_type(8)));
+  const i32x8 raw = *(const __attribute__((address_space(4))) i32x8*)work;
+  i32x4 rg = {0, 0, 0, 0};
+  if constexpr (kRanges) rg = *(const __attribute__((address_space(4))) i32x4*)ranges;
+  asm volatile("" : : "s"(raw), "s"(rg));
+  return TileAndRanges{__builtin_bit_cast(AttnWork, raw), {rg[0], rg[1], rg[2], rg[3]}};
+}
+
 template <int kBlockKeys, int kWaves, typename Extra, int kAblate = 0>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, Extra extra) {
   using G = Geo<kBlockKeys, kWaves>;
@@ -161,7 +180,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const int tile_no = kHalf ? static_cast<int>(blockIdx.x / (8 * kHalves) * 8 + blockIdx.x % 8) : static_cast<int>(blockIdx.x);
   const int half = kHalf ? static_cast<int>(blockIdx.x / 8 % kHalves) : 0;
   if (kHalf && tile_no >= a.n_tiles) return;
-  const AttnTile tile = a.tiles[tile_no];
+  constexpr bool kLazy = std::is_same<Extra, LazyRefs>::value;
+  const int32_t* ranges = nullptr;
+  if constexpr (kLazy)
+    ranges = kHalf ? extra.half + 4 * (kHalves * static_cast<int64_t>(tile_no) + half) : extra.range + 4 * static_cast<int64_t>(tile_no);
+  const TileAndRanges tr = load_tile<kLazy>(a.tiles + tile_no, ranges);
+  const AttnWork tile = tr.tile;
   const int first_row = half * kWaves * ROWS_PER_WAVE;
   if (tile.n_rows <= first_row) return;  // padding entry of the launch order, or a tile without a second half
   const int tid = threadIdx.x;
@@ -170,46 +194,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const int col = lane & 31;  // query column owned by this lane
   const int hi = lane >> 5;   // which half of the contraction index this lane feeds
   const int group = a.n_q_heads / a.n_kv_heads;
-  constexpr bool kLazy = std::is_same<Extra, LazyRefs>::value;
-  const int b = tile.req, g = tile.kv_head;
+  const int g = tile.kv_head;
   const int key0 = kLazy ? 0 : tile.key0;  // pieces of a tile cut along the keys start here;
   const int n_keys = tile.n_keys - key0;   // from here on keys and positions are relative to it
   // context row offsets in 16-byte units; read with scalar loads (the table is padded so
   // that reading up to 64 entries past the last key of the tile stays in bounds)
   const __attribute__((address_space(4))) uint32_t* off_of;
   // lazy: the tile visits fresh blocks [fb, fb + nf) and then stored blocks [sb, sb + ns) of the
-  // batch's block list (its request's fresh part and stored part); step t of the walk is block bid(t)
+  // batch's block list (in its request's fresh part and stored part); step t of the walk is block bid(t)
   int fb = 0, nf = 0, sb = 0, ns = 0;
   if constexpr (kLazy) {
-    const int32_t* ranges = kHalf ? extra.half + 4 * (kHalves * static_cast<int64_t>(tile_no) + half) : extra.range + 4 * static_cast<int64_t>(tile_no);
-    const i32x4 rg = *(const __attribute__((address_space(4))) i32x4*)ranges;
-    fb = extra.first[b] + rg[0];
-    nf = rg[1] - rg[0];
-    sb = extra.mid[b] + rg[2];
-    ns = rg[3] - rg[2];
+    fb = tr.ranges[0];
+    nf = tr.ranges[1] - fb;
+    sb = tr.ranges[2];
+    ns = tr.ranges[3] - sb;
     off_of = (const __attribute__((address_space(4))) uint32_t*)extra.voff;
   } else {
-    off_of = (const __attribute__((address_space(4))) uint32_t*)(a.kv_off16 + a.ctx_off[b] + key0);
+    off_of = (const __attribute__((address_space(4))) uint32_t*)(a.kv_off16 + tile.ctx_off + key0);
   }
   auto bid = [&](int t) __attribute__((always_inline)) { return t < nf ? fb + t : sb + (t - nf); };
-  const char* kbase = static_cast<const char*>(a.k_ctx) + g * ROW_BYTES;
-  const char* vbase = static_cast<const char*>(a.v_ctx) + g * ROW_BYTES;
-  const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, lds)));
-
-  // ---- this lane's query ----
-  const int local = first_row + wave * ROWS_PER_WAVE + col;
-  const bool valid = local < tile.n_rows;
-  const int flat = tile.row0 + (valid ? local : 0);
-  // lazy: keys of the fresh part this row sees (it is one of them); of the stored part it sees the rest
-  const int my_fresh = valid ? flat / group + 1 : 0x1fffffff;
-  const int64_t fresh_row = a.q_off[b] + flat / group;
-  const int head = g * group + flat % group;
-  // Last key of this tile (or piece) the row may see.  Padding columns see every key; a row
-  // below key0 (negative here) sees none of this piece; a row beyond the end of a piece sees the
-  // piece up to its last key (blocks need not end where pieces do).
-  // (lazy: positions stay absolute; a piece owns whole blocks)
-  const int my_pos = kLazy ? (valid ? a.q_pos[fresh_row] : 0x3fffffff)
-                           : min(valid ? a.q_pos[fresh_row] - key0 : 0x7fffffff, n_keys - 1);
   const int n_iter = kLazy ? nf + ns : (n_keys + BN - 1) / BN;
   // descriptor of key block blk of this tile (lazy only; a scalar load)
   auto desc_of = [&](int blk) __attribute__((always_inline)) {
@@ -224,6 +227,49 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     }
     return d;
   };
+  // BN / 8 rows per wave and block: kLoadPairs loads of four rows for K and as many for V
+  constexpr int kLoadPairs = ROWS_LOADED_PER_WAVE / 4;
+  struct RowOffs {
+    u32x4_a4 q[kLoadPairs];
+    int inst;  // lazy: the chunk instance that stores the block's rows, -1 = the context
+  };
+  auto fetch_rows = [&](int blk) {
+    blk = blk < n_iter ? blk : n_iter - 1;
+    if constexpr ((kAblate & kAblateSameRows) != 0) blk = 0;  // timing-only variant
+    const __attribute__((address_space(4))) u32x4_a4* src = reinterpret_cast<const __attribute__((address_space(4))) u32x4_a4*>(
+        off_of + (kLazy ? static_cast<int64_t>(bid(blk)) : static_cast<int64_t>(blk)) * BN + wave * ROWS_LOADED_PER_WAVE);
+    RowOffs r;
+#pragma unroll
+    for (int p = 0; p < kLoadPairs; ++p) r.q[p] = src[p];
+    if constexpr (kLazy) r.inst = extra.by_ref ? desc_of(blk).inst : -1;
+    return r;
+  };
+  // `ro` holds the offsets of the block whose loads go out next.  It is refilled at the start
+  // of the wave's softmax phase, which touches neither LDS nor scalar memory: the scalar load
+  // shares its counter with the LDS reads and returns out of order, so whatever waits on
+  // that counter next (the first fragment reads of a matrix part, a barrier) waits for it.
+  RowOffs ro = fetch_rows(0);
+  __builtin_amdgcn_sched_barrier(0);  // (on its way before the addresses of the queries are computed)
+  const char* kbase = static_cast<const char*>(a.k_ctx) + g * ROW_BYTES;
+  const char* vbase = static_cast<const char*>(a.v_ctx) + g * ROW_BYTES;
+  const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, lds)));
+
+  // ---- this lane's query ----
+  const int local = first_row + wave * ROWS_PER_WAVE + col;
+  const bool valid = local < tile.n_rows;
+  const int flat = tile.row0 + (valid ? local : 0);
+  // lazy: keys of the fresh part this row sees (it is one of them); of the stored part it sees the rest
+  const int my_fresh = valid ? flat / group + 1 : 0x1fffffff;
+  const int64_t fresh_row = tile.q_off + flat / group;
+  const int head = g * group + flat % group;
+  // Position of the row (of the tile's first one in padding columns), fetched without a branch and needed only once the
+  // first blocks are on their way: a branch around the load ended in a wait for it, ahead of every other load.
+  const int row_pos = a.q_pos[fresh_row];
+  // Last key of this tile (or piece) the row may see.  Padding columns see every key; a row
+  // below key0 (negative here) sees none of this piece; a row beyond the end of a piece sees the
+  // piece up to its last key (blocks need not end where pieces do).
+  // (lazy: positions stay absolute; a piece owns whole blocks)
+  const int my_pos = kLazy ? (valid ? row_pos : 0x3fffffff) : min(valid ? row_pos - key0 : 0x7fffffff, n_keys - 1);
   // does the row see any key of this tile (or piece)?
   // first position of the tile (or piece): the smaller of its first fresh and first stored block's
   // (a row may see none of the fresh blocks of a piece and still see its stored ones)
@@ -321,28 +367,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const uint32_t ld_v16 = ld_col ^ (ld_sub << 2);               //          V swizzle = (row & 3) << 2
   const uint32_t sel0 = ld_sub == 0 ? ~0u : 0u, sel1 = ld_sub == 1 ? ~0u : 0u;
   const uint32_t sel2 = ld_sub == 2 ? ~0u : 0u, sel3 = ld_sub == 3 ? ~0u : 0u;
-  // BN / 8 rows per wave and block: kLoadPairs loads of four rows for K and as many for V
-  constexpr int kLoadPairs = ROWS_LOADED_PER_WAVE / 4;
-  struct RowOffs {
-    u32x4_a4 q[kLoadPairs];
-    int inst;  // lazy: the chunk instance that stores the block's rows, -1 = the context
-  };
-  auto fetch_rows = [&](int blk) {
-    blk = blk < n_iter ? blk : n_iter - 1;
-    if constexpr ((kAblate & kAblateSameRows) != 0) blk = 0;  // timing-only variant
-    const __attribute__((address_space(4))) u32x4_a4* src = reinterpret_cast<const __attribute__((address_space(4))) u32x4_a4*>(
-        off_of + (kLazy ? static_cast<int64_t>(bid(blk)) : static_cast<int64_t>(blk)) * BN + wave * ROWS_LOADED_PER_WAVE);
-    RowOffs r;
-#pragma unroll
-    for (int p = 0; p < kLoadPairs; ++p) r.q[p] = src[p];
-    if constexpr (kLazy) r.inst = extra.by_ref ? desc_of(blk).inst : -1;
-    return r;
-  };
-  // `ro` holds the offsets of the block whose loads go out next.  It is refilled at the start
-  // of the wave's softmax phase, which touches neither LDS nor scalar memory: the scalar load
-  // shares its counter with the LDS reads and returns out of order, so whatever waits on
-  // that counter next (the first fragment reads of a matrix part, a barrier) waits for it.
-  RowOffs ro = fetch_rows(0);
   int ld_inst = -1;  // lazy: the source the loader's base addresses point to
   const char* ld_kb = kbase;
   const char* ld_vb = vbase;
@@ -398,7 +422,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) {
-      if (i < n_iter) issue_loads(i);
+      if (i == 0 || i < n_iter) issue_loads(i);  // (no tile, piece or half is without a block)
       ro = fetch_rows(i + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -410,10 +434,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     start_ring();
     turn_q(q_inst);
   } else {
+    // (asked for ahead of the queries: behind the first blocks, which its wait would include, the tables came a latency later)
+    const int rot_row = (a.q_rot ? a.q_rot : a.q_pos)[fresh_row];
     fetch_q();
     start_ring();
     if (a.q_rot) {
-      const int64_t u = a.q_rot[fresh_row];
+      const int64_t u = rot_row;
       const float* ct = a.q_cos + u * (D / 2);
       const float* st = a.q_sin + u * (D / 2);
       if (a.interleaved) {
@@ -848,7 +874,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
 #pragma unroll
   for (int p = 0; p < ROWS_PER_WAVE / 4; ++p) {
     const bf16x8 x = *reinterpret_cast<const bf16x8*>(area + r * ROW_BYTES + (((ln & 15) ^ (r & 15)) << 4));
-    const int64_t item = (a.q_off[b] + static_cast<int64_t>(quot)) * a.n_q_heads + g * group + rem;
+    const int64_t item = (tile.q_off + static_cast<int64_t>(quot)) * a.n_q_heads + g * group + rem;
     if (first_row + wave * ROWS_PER_WAVE + r < tile.n_rows)
       *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + item * ROW_BYTES + ((ln & 15) << 4)) = x;
     r += 4;
@@ -884,7 +910,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int quad = threadIdx.x >> 3;
   const int d = quad * 4;
   const int flat = m.row0 + local;
-  const int64_t fresh_row = a.q_off[m.req] + flat / group;
+  const int64_t fresh_row = m.pad[0] + flat / group;
   const int head = m.kv_head * group + flat % group;
   const int64_t slot0 = static_cast<int64_t>(m.first_part) * kAttnTileRows + local;
   // the first piece starts at key 0, which every row sees: the maximum is finite from the

@@ -26,7 +26,11 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void attn_f32_kernel(AttnArgs
   const int row0 = piece.row0, n_cols = piece.n_rows;
   const int flat = row0 + min(col, n_cols - 1);
   const int64_t r = piece.q_off + flat / group;
-  const int my_pos = col < n_cols ? a.q_pos[r] : piece.key1 - 1;
+  // fetched without a branch and first looked at behind the first keys: nothing waits for it on the way to them (152
+  // tokens of 4 heads linked and attended 13.5 -> 13.4 us, one image with 32 heads 39.1 -> 38.8)
+  const int row_pos = a.q_pos[r];
+  const int rot_row = (a.q_rot ? a.q_rot : a.q_pos)[r];
+  const int my_pos = col < n_cols ? row_pos : piece.key1 - 1;
 
   f32tile::Rows src{};
   src.off16 = a.kv_off16 + piece.ctx_off;
@@ -49,8 +53,8 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void attn_f32_kernel(AttnArgs
   auto turn = [&](float(&q)[D / 2]) __attribute__((always_inline)) {
     if (!a.q_rot) return;
     // a query that arrives without its position is turned by its position id first
-    const float* ct = a.q_cos + static_cast<int64_t>(a.q_rot[r]) * (D / 2);
-    const float* st = a.q_sin + static_cast<int64_t>(a.q_rot[r]) * (D / 2);
+    const float* ct = a.q_cos + static_cast<int64_t>(rot_row) * (D / 2);
+    const float* st = a.q_sin + static_cast<int64_t>(rot_row) * (D / 2);
     if (a.interleaved) {
 #pragma unroll
       for (int j = 0; j < D / 8; ++j)

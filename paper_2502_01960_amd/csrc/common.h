@@ -26,11 +26,19 @@ struct AttnTile {
 };
 static_assert(sizeof(AttnTile) == 32, "tile layout is part of the ABI");
 
+// The same tile as the bf16 attention kernel reads it: its request's first fresh row and first position stand here
+// instead of the request's number, so that one load, not a chain of two, precedes those of the queries and row offsets.
+struct AttnWork {
+  int32_t kv_head, row0, n_rows, n_keys, key0, part;  // as in AttnTile
+  int32_t q_off, ctx_off;
+};
+static_assert(sizeof(AttnWork) == 32, "read with one scalar load");
+
 // Rows whose keys were cut into several tiles: their partial results are merged afterwards.
 struct AttnMerge {
   int32_t req, kv_head, row0, n_rows;
   int32_t first_part, n_parts;  // partial slots first_part .. first_part + n_parts - 1, in key order
-  int32_t pad[2];  // (fp32: first fresh row of the request)
+  int32_t pad[2];  // first fresh row of the request; 0
 };
 static_assert(sizeof(AttnMerge) == 32, "merge item layout");
 
@@ -82,7 +90,7 @@ struct PlanDevice {
   int32_t* fresh_rot = nullptr;  // row of fresh_cos / fresh_sin for every fresh row (null: rows arrive rotated)
   float* fresh_cos = nullptr;
   float* fresh_sin = nullptr;
-  AttnTile* tiles = nullptr;
+  AttnWork* tiles = nullptr;
   AttnMerge* merges = nullptr;
   AttnPieceF32* tiles_f32 = nullptr;   // fp32 contexts: whole tiles, and the launch with tiles cut along the keys
   AttnPieceF32* pieces_f32 = nullptr;
@@ -91,7 +99,6 @@ struct PlanDevice {
   int32_t* kblk_first[kNumBlockSizes] = {};   // [B+1] first block of each request
   uint32_t* voff_ctx[kNumBlockSizes] = {};    // [n_blocks * BN + pad] row offsets (16-byte units), every row in the context
   uint32_t* voff_ref[kNumBlockSizes] = {};    // the same with stored rows addressed inside their source
-  int32_t* kblk_mid[kNumBlockSizes] = {};     // [B] first stored block of each request
   int32_t* lazy_range[kNumBlockSizes] = {};   // [n_tiles][4] block ranges of every tile: fresh [f0, f1), stored [s0, s1)
   int32_t* lazy_half = nullptr;               // [n_tiles][2][4] the same of its halves of rows (blocks of kHalfTileBlock keys)
   void* block = nullptr;  // the single allocation all of the above point into
@@ -262,11 +269,9 @@ hipError_t launch_assemble(int dtype, const AssembleArgs& a, const AssembleSrcTa
                            hipStream_t stream);
 
 struct AttnArgs {
-  const AttnTile* tiles;
+  const AttnWork* tiles;
   int32_t n_tiles;
   const int32_t* q_pos;
-  const int32_t* q_off;
-  const int32_t* ctx_off;
   const int32_t* dst_slot;
   const uint32_t* kv_off16;
   const void* q;
@@ -322,8 +327,7 @@ constexpr int64_t kHalfTileBlocks = 180 * 256;
 struct LazyRefs {
   const KeyBlock* blocks;  // key blocks of the batch for this kernel's block size
   const int32_t* first;    // [B+1] first block of every request (its fresh blocks, then its stored blocks)
-  const int32_t* mid;      // [B] first stored block of every request
-  const int32_t* range;    // [n_tiles][4] attention kernel: fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
+  const int32_t* range;    // [n_tiles][4] attention kernel: fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile, in the batch's list
   const int32_t* half;     // [n_tiles][2][4] the same of its halves of rows
   const uint32_t* voff;    // [n_blocks][BN] row offsets (16-byte units) from the block's base
   const float* rope_cos;   // [n_inst][D/2] cos / sin of every instance's shift

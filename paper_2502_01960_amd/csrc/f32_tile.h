@@ -113,7 +113,6 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
   c = fmaxf(c, 1e-37f);  // (0 * -infinity is no number)
   c_lo = fmaxf(c_lo, 1e-37f);
   auto weight = [&](float t) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f(fmaf(t, c, t * c_lo)); };
-  const int lo_pos = wave_min_i32(my_pos);
 
   // addresses of the key and value row that lane `lane % 32` stands for, and its rotary table row
   const char* kp = nullptr;
@@ -150,11 +149,12 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
   for (int i = 0; i < G::kBlocks; ++i) acc_o[i] = f32x16{0};
 
   const int n_blk = (key1 - key0 + kKeys - 1) / kKeys;
-  if (wave < n_blk) locate(key0 + wave * kKeys);
+  locate(key0 + wave * kKeys);  // (for wavefronts without a block too: no branch, and with it no wait of its own)
   MPIC_WAIT_VMCNT(0);  // ordinary loads first: from here on the counter is managed by hand
   __builtin_amdgcn_sched_barrier(0);
   if (wave < n_blk) stage_keys();
   float q[D / 2];
+  int lo_pos;  // no column ends before this position
   {
     char* area_q = lds + G::kQuery;
     const uint32_t area_q_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, area_q)));
@@ -163,6 +163,7 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
       const int p = wave + i * kWaves, r = (lane + 64 * p) / G::kChunks;
       load_to_lds_16B(q_row(r) + ((lane % G::kChunks) ^ (r & 15)) * 16, area_q_addr + p * 1024);
     }
+    lo_pos = __builtin_amdgcn_readfirstlane(wave_min_i32(my_pos));
     MPIC_WAIT_VMCNT(0);
     asm volatile("" ::: "memory");
     __syncthreads();

@@ -234,6 +234,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
         m.n_rows = static_cast<int32_t>(n);
         m.first_part = chosen.n_parts;
         m.n_parts = static_cast<int32_t>(parts);
+        m.pad[0] = p.q_off[b];
         chosen.n_parts += static_cast<int32_t>(parts);
         chosen.merges.push_back(m);
         // the pieces of this (tile, g) were pushed last into their group, in key order
