@@ -818,7 +818,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     const bool seen = sees();
     const float inv_p = seen ? 1.f / l_tot : 0.f;
     const int64_t slot = static_cast<int64_t>(tile.part) * kAttnTileRows + local;
-    float* po = a.ws_o + static_cast<int64_t>(tile.part) * kAttnTileRows * D + ((half * kWaves + wave) * 16 * 64 + lane) * 4;
+    // They are stored past the L2 (cache policy sc1): the merge reads them from other L2 domains, and left to the write-back
+    // at the end of the launch they take longer.  2.6K tokens with 32 heads linked and attended 47.6 -> 46.9 us, two requests in
+    // place 117.1 -> 115.8, plan and four layers of a 2.7K-token request 162 -> 157 (with the non-temporal hint instead
+    // 1.02 of the time).
+    constexpr int kWaveFloats = 16 * 64 * 4, kPastL2 = 16;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    float* po = a.ws_o + static_cast<int64_t>(tile.part) * kAttnTileRows * D + (half * kWaves + wave) * kWaveFloats;
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(po, 0, kWaveFloats * sizeof(float), 0x00027000);
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -826,7 +833,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = seen ? acc_o[db][q4 * 4 + e] * inv_p : 0.f;
-        *reinterpret_cast<f32x4*>(po + (db * 4 + q4) * 256) = o;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rows, (db * 4 + q4) * 1024 + lane * 16, 0, kPastL2);
       }
     if (hi == 0) a.ws_lse[slot] = seen ? m_run * a.scale + logf(l_tot) : -INFINITY;
     return;
