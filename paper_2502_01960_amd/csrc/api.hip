@@ -551,6 +551,8 @@ int mpic::assemble_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* s
   a.fresh_v = fresh_v;
   a.k_ctx = k_ctx;
   a.v_ctx = v_ctx;
+  const int64_t ctx_bytes = (plan->max_slot + 1) * c.n_kv_heads * c.head_dim * (c.dtype == MPIC_F32 ? 4 : 2);
+  a.ctx_bytes = ctx_bytes < (int64_t{1} << 32) ? static_cast<uint32_t>(ctx_bytes) : 0;
   a.n_kv_heads = c.n_kv_heads;
   a.head_dim = c.head_dim;
   a.interleaved = c.rope_interleaved;

@@ -12,12 +12,14 @@
 #include <algorithm>
 
 #include "common.h"
+#include <type_traits>
+
 #include "link_rows.h"
 
 namespace mpic {
 namespace {
 
-template <typename T, bool kInterleaved>
+template <typename T, bool kInterleaved, bool kPastL2>
 __global__ __launch_bounds__(256) void assemble_kernel(AssembleArgs a, AssembleSrcTable tab) {
   const link::Shape sh = link::shape_of<T>(a);
   // one work item (a pair of 16-byte units of one context row) per thread; launches that
@@ -25,7 +27,7 @@ __global__ __launch_bounds__(256) void assemble_kernel(AssembleArgs a, AssembleS
   const int64_t n_items = (a.pos_end - a.pos_begin) * sh.pairs_per_row;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t w = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w < n_items; w += stride)
-    link::link_item<T, kInterleaved>(a, tab, sh, w);
+    link::link_item<T, kInterleaved, kPastL2>(a, tab, sh, w);
 }
 
 }  // namespace
@@ -44,17 +46,28 @@ hipError_t launch_assemble(int dtype, const AssembleArgs& a, const AssembleSrcTa
   int64_t blocks = (threads + 255) / 256;
   if (a.grid_limit > 0) blocks = std::min<int64_t>(blocks, a.grid_limit);
   const dim3 grid(static_cast<unsigned>(blocks));
-  if (dtype == MPIC_F32) {
-    if (a.interleaved)
-      hipLaunchKernelGGL((assemble_kernel<float, true>), grid, block, 0, stream, a, t);
+  // Stores past the L2 where the launch has the chip to itself (link_rows.h has the figures); launches held to a small
+  // grid run beside others, and contexts of 4 GiB or more are out of a buffer store's reach.
+  const bool past_l2 = a.ctx_bytes != 0 && blocks * 256 >= threads;
+  auto go = [&](auto type, auto interleaved, auto past) {
+    hipLaunchKernelGGL((assemble_kernel<decltype(type), decltype(interleaved)::value, decltype(past)::value>), grid, block, 0, stream, a, t);
+  };
+  auto with_policy = [&](auto type, auto interleaved) {
+    if (past_l2)
+      go(type, interleaved, std::true_type{});
     else
-      hipLaunchKernelGGL((assemble_kernel<float, false>), grid, block, 0, stream, a, t);
-  } else {
+      go(type, interleaved, std::false_type{});
+  };
+  auto with_pairing = [&](auto type) {
     if (a.interleaved)
-      hipLaunchKernelGGL((assemble_kernel<__bf16, true>), grid, block, 0, stream, a, t);
+      with_policy(type, std::true_type{});
     else
-      hipLaunchKernelGGL((assemble_kernel<__bf16, false>), grid, block, 0, stream, a, t);
-  }
+      with_policy(type, std::false_type{});
+  };
+  if (dtype == MPIC_F32)
+    with_pairing(float{});
+  else
+    with_pairing(__bf16{});
   return hipGetLastError();
 }
 

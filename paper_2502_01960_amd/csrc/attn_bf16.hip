@@ -130,7 +130,7 @@ __device__ inline void link_share(const LinkNext& ln, int j) {
         if (r < hi) it[d] = link::load_item_at<__bf16, kI>(ln.args, ln.tab, sh, r, u);
       }
 #pragma unroll
-      for (int d = 0; d < kLinkDepth; ++d) link::finish_item<__bf16, kI>(it[d], sh);
+      for (int d = 0; d < kLinkDepth; ++d) link::finish_item<__bf16, kI, false>(ln.args, it[d], sh);
     }
   };
   if (ln.args.interleaved) {

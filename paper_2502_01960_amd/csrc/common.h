@@ -252,6 +252,7 @@ struct AssembleArgs {
   const void* fresh_v;
   void* k_ctx;
   void* v_ctx;
+  uint32_t ctx_bytes;          // of k_ctx (and of v_ctx) up to the plan's last slot; 0: 4 GiB or more, or not set
   int64_t pos_begin, pos_end;  // batch-flattened context positions handled by this launch
   int32_t inst_base;           // first chunk instance present in src_k / src_v
   int32_t n_inst;              // entries in src_k / src_v
