@@ -109,14 +109,12 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
 }
 
 // The same for a launch that can also do without (fp32): null if no workspace is free or has the room, and
-// nothing waits or goes to make some.
+// nothing waits or goes to make some.  Only a workspace that is this stream's alone will do, so none under capture (the
+// graph may run beside other calls) and none where the handle means another stream in every thread.
 Scratch* spare_attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
-  const size_t need = attn_ws_need(ctx, p);
+  if (!trackable(stream)) return nullptr;
   Scratch* w = find_attn_ws(ctx, stream);
-  if (!(w && w->claimed) && !trackable(stream)) w = largest_attn_ws(ctx);
-  if (!w || (need > w->bytes && !trackable(stream))) return nullptr;  // (nothing can be allocated under capture)
-  if (!trackable(stream)) return w;
-  if (!grow(ctx, w, need, false)) return nullptr;
+  if (!w || !grow(ctx, w, attn_ws_need(ctx, p), false)) return nullptr;
   w->claimed = true;
   w->stream = stream;
   return w;
@@ -457,9 +455,9 @@ int mpic::assemble_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src* s
   const bool first_use = !plan->dev.block;
   rc = mpic::upload_plan(ctx, plan, stream);
   if (rc != MPIC_OK) return rc;
-  // The attention call that most likely follows on this stream can be captured if its workspace is there.
-  // Nothing is lost if it cannot be had yet.
-  if (first_use && !(ctx->link_stream && stream == ctx->link_stream))
+  // The attention call that most likely follows on this stream can be captured if its workspace is there (fp32
+  // takes none under capture).  Nothing is lost if it cannot be had yet.
+  if (first_use && ctx->cfg.dtype == MPIC_BF16 && !(ctx->link_stream && stream == ctx->link_stream))
     if (mpic::Scratch* w = mpic::find_attn_ws(ctx, stream)) (void)mpic::grow(ctx, w, mpic::attn_ws_need(ctx, plan), false);
   const mpic_config& c = ctx->cfg;
   const size_t elem = c.dtype == MPIC_F32 ? 4 : 2;

@@ -17,7 +17,8 @@ int n_syncs = 0;
 struct Stream { bool capturing = false; };
 bool capturing_any = false;
 Stream null_stream;
-Stream* of(hipStream_t s) { return s ? reinterpret_cast<Stream*>(s) : &null_stream; }
+Stream per_thread;
+Stream* of(hipStream_t s) { return s == hipStreamPerThread ? &per_thread : s ? reinterpret_cast<Stream*>(s) : &null_stream; }
 }  // namespace
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
@@ -172,11 +173,46 @@ int main() {
     mpic_destroy(c);
     CHECK(in_use == 0);
   }
-  {  // fp32: no workspace for the attention; decode steps of one batch size stay valid as contexts grow
+  {  // fp32: tiles are cut only where the stream itself has room for their partial results, and whole otherwise
+    mpic_ctx* c = context(MPIC_F32);
+    mpic_plan* p = plan_of(c, 700);
+    CHECK(p->n_parts_f32 > 0);
+    const auto cut = [&] {  // pieces, merge list and workspace go together
+      const mpic::AttnArgs& a = mpic::last_attn;
+      CHECK(a.pieces_f32 == (a.ws_o ? p->dev.pieces_f32 : p->dev.tiles_f32));
+      CHECK(a.n_merges == (a.ws_o ? static_cast<int32_t>(p->merges_f32.size()) : 0));
+      return a.ws_o != nullptr;
+    };
+    limit = in_use + mb / 2;  // the plan's tables fit, the workspace does not
+    CHECK(assemble(c, p, &s[0]) == MPIC_OK && attend(c, p, &s[0]) == MPIC_OK && !cut());
+    limit = SIZE_MAX;
+    CHECK(attend(c, p, &s[0]) == MPIC_OK && cut());
+    std::vector<const float*> of_stream = {mpic::last_attn.ws_o};
+    // a capture may run at any time: it takes no workspace, of its own stream or of another
+    for (Stream* x : {&s[0], &s[5]}) {
+      capture(x, true);
+      CHECK(attend(c, p, x) == MPIC_OK && !cut());
+      capture(x, false);
+    }
+    // nor does a stream whose handle means another one in every thread
+    CHECK(attend(c, p, reinterpret_cast<Stream*>(hipStreamPerThread)) == MPIC_OK && !cut());
+    for (int i = 1; i < 4; ++i) {
+      CHECK(attend(c, p, &s[i]) == MPIC_OK && cut());
+      for (const float* w : of_stream) CHECK(mpic::last_attn.ws_o != w);
+      of_stream.push_back(mpic::last_attn.ws_o);
+    }
+    const int syncs = n_syncs;
+    CHECK(attend(c, p, &s[4]) == MPIC_OK && !cut() && n_syncs == syncs);  // a fifth stream waits for nothing
+    CHECK(attend(c, p, &s[1]) == MPIC_OK && mpic::last_attn.ws_o == of_stream[1]);
+    mpic_plan_destroy(p);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  {  // fp32 plans that are not cut take no workspace; decode steps of one batch size stay valid as contexts grow
     mpic_ctx* c = context(MPIC_F32);
     mpic_plan *p = plan_of(c, 200), *q = plan_of(c, 5000);
     CHECK(assemble(c, p, &s[0]) == MPIC_OK && assemble(c, q, &s[0]) == MPIC_OK);
-    CHECK(attend(c, q, &s[0]) == MPIC_OK);
+    CHECK(p->n_parts_f32 == 0 && q->n_parts_f32 == 0 && attend(c, q, &s[0]) == MPIC_OK);
     for (const mpic::Scratch& w : c->attn_ws) CHECK(!w.ptr);
     CHECK(decode(c, p, &s[0]) == MPIC_OK && mpic::last_decode.n_splits == 1);
     float* const first = mpic::last_decode.ws_o;  // as a captured step holds it
