@@ -341,12 +341,12 @@ int mpic_assemble_kv_parts(mpic_ctx* ctx, mpic_plan* plan, const mpic_chunk_src*
  * the stream, grown by a plan that needs more (what it outgrew stays until mpic_destroy, for
  * graphs that captured it, unless memory is short).  mpic_assemble_kv tries to provide it (BF16) when
  * it brings a plan to the GPU, so that the attention can be captured; if it cannot be had, only
- * the attention call fails.  Calls of one context may overlap on up to four streams; on a fifth
- * the call waits for the GPU to be idle.  A graph uses the workspace of the stream it was
+ * the attention call fails.  Calls of one context may overlap on up to four streams (hipStreamPerThread
+ * is one per thread); on a fifth the call waits for the GPU to be idle.  A graph uses the workspace of the stream it was
  * captured on, or the largest one if that stream had none, and must not run beside other
  * calls that use it.  F32 calls are cut only where the workspace is the stream's own and can be
- * had: under capture, on hipStreamPerThread and on a fifth stream they run uncut, wait for nothing
- * and use no workspace (the same result up to rounding).
+ * had: under capture and on a fifth stream they run uncut, wait for nothing and use no workspace
+ * (the same result up to rounding).
  * Errors: MPIC_ERR_INVALID, MPIC_ERR_OOM (workspace), MPIC_ERR_HIP.
  */
 int mpic_selective_attn(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q, int64_t n_fresh_rows,

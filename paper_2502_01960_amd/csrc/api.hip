@@ -2,6 +2,7 @@
 // plan, the side-stream transfer of host-resident chunk caches (Sec. 3.2: transfer
 // and linking proceed concurrently) and the kernel launches.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <iterator>
@@ -69,11 +70,24 @@ size_t attn_ws_need(const mpic_ctx* ctx, const mpic_plan* p) {
   return rows * (ctx->cfg.head_dim + 1) * sizeof(float);
 }
 
+// hipStreamPerThread means another stream in every thread: a number that no other thread has, 0 for other streams.
+uint64_t thread_of(hipStream_t stream) {
+  static std::atomic<uint64_t> threads{0};
+  static thread_local const uint64_t mine = ++threads;
+  return stream == hipStreamPerThread ? mine : 0;
+}
+
+void claim(Scratch* w, hipStream_t stream) {
+  w->claimed = true;
+  w->stream = stream;
+  w->thread = thread_of(stream);
+}
+
 // The workspace of the stream's attention calls, or the largest that no stream has yet (null: none left).
 Scratch* find_attn_ws(mpic_ctx* ctx, hipStream_t stream) {
   Scratch* w = nullptr;
   for (Scratch& x : ctx->attn_ws) {
-    if (x.claimed && x.stream == stream) return &x;
+    if (x.claimed && x.stream == stream && x.thread == thread_of(stream)) return &x;
     if (!x.claimed && (!w || x.bytes > w->bytes)) w = &x;
   }
   return w;
@@ -93,7 +107,7 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
   const size_t need = attn_ws_need(ctx, p);
   Scratch* w = find_attn_ws(ctx, stream);
   if (!(w && w->claimed)) {
-    if (!trackable(stream)) {
+    if (capturing(stream)) {
       w = largest_attn_ws(ctx);
     } else {
       if (!w) {
@@ -101,8 +115,7 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
         w = &ctx->attn_ws[ctx->next_attn_ws];
         ctx->next_attn_ws = (ctx->next_attn_ws + 1) % kAttnWorkspaces;
       }
-      w->claimed = true;
-      w->stream = stream;
+      claim(w, stream);
     }
   }
   return grow(ctx, w, need) ? w : nullptr;
@@ -110,13 +123,12 @@ Scratch* attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
 
 // The same for a launch that can also do without (fp32): null if no workspace is free or has the room, and
 // nothing waits or goes to make some.  Only a workspace that is this stream's alone will do, so none under capture (the
-// graph may run beside other calls) and none where the handle means another stream in every thread.
+// graph may run beside other calls).
 Scratch* spare_attn_workspace(mpic_ctx* ctx, const mpic_plan* p, hipStream_t stream) {
-  if (!trackable(stream)) return nullptr;
+  if (capturing(stream)) return nullptr;
   Scratch* w = find_attn_ws(ctx, stream);
   if (!w || !grow(ctx, w, attn_ws_need(ctx, p), false)) return nullptr;
-  w->claimed = true;
-  w->stream = stream;
+  claim(w, stream);
   return w;
 }
 

@@ -112,6 +112,7 @@ struct Scratch {
   size_t bytes = 0;
   bool claimed = false;  // by the work of `stream`
   hipStream_t stream = nullptr;
+  uint64_t thread = 0;  // hipStreamPerThread: of this thread
 };
 constexpr int kAttnWorkspaces = 4;
 

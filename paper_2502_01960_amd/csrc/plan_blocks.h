@@ -17,15 +17,16 @@
 
 namespace mpic {
 
+inline bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Not a stream that work can be followed on: it is being captured (a graph may run at any time), or
 // its handle means another stream in every thread.
-inline bool trackable(hipStream_t stream) {
-  if (stream == hipStreamPerThread) return false;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st == hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return false;
-}
+inline bool trackable(hipStream_t stream) { return stream != hipStreamPerThread && !capturing(stream); }
 
 // Where the work that reads a plan's tables was enqueued.
 struct PlanUse {

@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <thread>
 #include <vector>
 
 #include "common.h"
@@ -173,6 +174,22 @@ int main() {
     mpic_destroy(c);
     CHECK(in_use == 0);
   }
+  for (int dtype : {MPIC_BF16, MPIC_F32}) {  // hipStreamPerThread is another stream in every thread, each with its own workspace
+    mpic_ctx* c = context(dtype);
+    mpic_plan* p = plan_of(c, dtype == MPIC_BF16 ? 3000 : 700);
+    Stream* mine = reinterpret_cast<Stream*>(hipStreamPerThread);
+    const auto ws = [&](Stream* x) {
+      CHECK(attend(c, p, x) == MPIC_OK && mpic::last_attn.ws_o);
+      return mpic::last_attn.ws_o;
+    };
+    const int syncs = n_syncs;
+    const float *first = ws(&s[0]), *here = ws(mine), *there = nullptr;
+    std::thread([&] { there = ws(mine); }).join();
+    CHECK(first != here && there != here && there != first && ws(mine) == here && ws(&s[0]) == first && n_syncs == syncs);
+    mpic_plan_destroy(p);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
   {  // fp32: tiles are cut only where the stream itself has room for their partial results, and whole otherwise
     mpic_ctx* c = context(MPIC_F32);
     mpic_plan* p = plan_of(c, 700);
@@ -194,8 +211,6 @@ int main() {
       CHECK(attend(c, p, x) == MPIC_OK && !cut());
       capture(x, false);
     }
-    // nor does a stream whose handle means another one in every thread
-    CHECK(attend(c, p, reinterpret_cast<Stream*>(hipStreamPerThread)) == MPIC_OK && !cut());
     for (int i = 1; i < 4; ++i) {
       CHECK(attend(c, p, &s[i]) == MPIC_OK && cut());
       for (const float* w : of_stream) CHECK(mpic::last_attn.ws_o != w);
