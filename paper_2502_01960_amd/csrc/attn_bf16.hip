@@ -181,6 +181,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const int half = kHalf ? static_cast<int>(blockIdx.x / 8 % kHalves) : 0;
   if (kHalf && tile_no >= a.n_tiles) return;
   constexpr bool kLazy = std::is_same<Extra, LazyRefs>::value;
+  // Row offsets and position go out early (below), except where caches in place are attended by eight wavefronts: those
+  // kernels spill, and what is fetched early there costs one register more in the loop.  Early and late: 4 requests of 8
+  // images of 2304 tokens 1185 and 1157 us, 8 of 16K tokens out of a pool 2205 and 2115, one of 40K tokens 2839 and 2757.
+  constexpr bool kEarly = !kLazy || kHalf;
   const int32_t* ranges = nullptr;
   if constexpr (kLazy)
     ranges = kHalf ? extra.half + 4 * (kHalves * static_cast<int64_t>(tile_no) + half) : extra.range + 4 * static_cast<int64_t>(tile_no);
@@ -248,8 +252,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   // of the wave's softmax phase, which touches neither LDS nor scalar memory: the scalar load
   // shares its counter with the LDS reads and returns out of order, so whatever waits on
   // that counter next (the first fragment reads of a matrix part, a barrier) waits for it.
-  RowOffs ro = fetch_rows(0);
-  __builtin_amdgcn_sched_barrier(0);  // (on its way before the addresses of the queries are computed)
+  RowOffs ro{};
+  if constexpr (kEarly) {
+    ro = fetch_rows(0);
+    __builtin_amdgcn_sched_barrier(0);  // (on its way before the addresses of the queries are computed)
+  }
   const char* kbase = static_cast<const char*>(a.k_ctx) + g * ROW_BYTES;
   const char* vbase = static_cast<const char*>(a.v_ctx) + g * ROW_BYTES;
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, lds)));
@@ -264,7 +271,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const int head = g * group + flat % group;
   // Position of the row (of the tile's first one in padding columns), fetched without a branch and needed only once the
   // first blocks are on their way: a branch around the load ended in a wait for it, ahead of every other load.
-  const int row_pos = a.q_pos[fresh_row];
+  int row_pos = 0;
+  if (kEarly || valid) row_pos = a.q_pos[fresh_row];
   // Last key of this tile (or piece) the row may see.  Padding columns see every key; a row
   // below key0 (negative here) sees none of this piece; a row beyond the end of a piece sees the
   // piece up to its last key (blocks need not end where pieces do).
@@ -367,6 +375,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
   const uint32_t ld_v16 = ld_col ^ (ld_sub << 2);               //          V swizzle = (row & 3) << 2
   const uint32_t sel0 = ld_sub == 0 ? ~0u : 0u, sel1 = ld_sub == 1 ? ~0u : 0u;
   const uint32_t sel2 = ld_sub == 2 ? ~0u : 0u, sel3 = ld_sub == 3 ? ~0u : 0u;
+  if constexpr (!kEarly) ro = fetch_rows(0);
   int ld_inst = -1;  // lazy: the source the loader's base addresses point to
   const char* ld_kb = kbase;
   const char* ld_vb = vbase;
@@ -422,7 +431,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_bf16_kernel(AttnArgs a, E
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) {
-      if (i == 0 || i < n_iter) issue_loads(i);  // (no tile, piece or half is without a block)
+      if ((kEarly && i == 0) || i < n_iter) issue_loads(i);  // (no tile, piece or half is without a block)
       ro = fetch_rows(i + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
