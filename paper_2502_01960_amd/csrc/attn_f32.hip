@@ -77,7 +77,7 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void attn_f32_kernel(AttnArgs
         }
     }
   };
-  f32tile::attend<D, kLazy>(src, q_row, turn, my_pos, piece.key0, piece.key1, a.scale, lds,
+  f32tile::attend<D, kLazy, true>(src, q_row, turn, my_pos, piece.key0, piece.key1, a.scale, lds,
                             [&](int c, int d0, const float(&o)[f32tile::Geo<D>::kPerThread], float m, float l) {
     if (c >= n_cols) return;
     const float inv = 1.f / l;

@@ -601,13 +601,13 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
     src.row_bytes = static_cast<int64_t>(a.n_kv_heads) * kD * 4;
     src.interleaved = a.interleaved;
   }
-  f32tile::attend<kD, kLazy>(src, [&](int c) { return static_cast<const char*>(a.q) + (row0 + min(c, n_cols - 1)) * (kD * 4); },
-                             [](float(&)[kD / 2]) {}, key1 - 1, key0, key1, a.scale, lds,
-                             [&](int c, int d0, const float(&o)[f32tile::Geo<kD>::kPerThread], float m, float l) {
+  f32tile::attend<kD, kLazy, kD == 128>(src, [&](int c) { return static_cast<const char*>(a.q) + (row0 + min(c, n_cols - 1)) * (kD * 4); },
+                                        [](float(&)[kD / 2]) {}, key1 - 1, key0, key1, a.scale, lds,
+                                        [&](int c, int d0, const float(&o)[f32tile::Geo<kD>::kPerThread], float m, float l) {
     if constexpr (kUnsplit) __syncthreads();  // (every thread is here once: what lies in LDS has been read)
     if (c >= n_cols) return;
     const int64_t part = (row0 + c) * a.n_splits + split;
-    const float inv = 1.f / l, lse = m * a.scale + logf(l);
+    const float inv = 1.f / l;
 #pragma unroll
     for (int i = 0; i < f32tile::Geo<kD>::kPerThread; i += 4) {
       const f32x4 x = f32x4{o[i], o[i + 1], o[i + 2], o[i + 3]} * inv;
@@ -618,6 +618,7 @@ __global__ __launch_bounds__(f32tile::kThreads, 2) void decode_f32_kernel(Decode
       }
     }
     if (d0 != 0) return;
+    const float lse = m * a.scale + logf(l);
     if constexpr (kUnsplit) {
       fin[f32tile::kCols * kD + c] = lse;
     } else {

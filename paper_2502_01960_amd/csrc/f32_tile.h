@@ -89,10 +89,12 @@ __device__ inline int here(int x) {
 // the range.  emit(column, first coordinate, values, reference maximum of the raw logits, denominator) is called
 // once per thread and column.
 //
-// The eight wavefronts have the same queries, which come through LDS, behind the first keys.  (Fetched by each
-// wavefront from memory, 16 bytes of 64 rows at a time and before anything else: 149 rows over 693 keys with
-// 32 heads 29.2 us instead of 26.5, uncut 41.0 instead of 38.3.)
-template <int D, bool kLazy, typename QRow, typename Turn, typename Emit>
+// The eight wavefronts have the same queries.  kStagedQ: they come through LDS, behind the first keys.  (Fetched by
+// each wavefront from memory, 16 bytes of 64 rows at a time and before anything else: 149 rows over 693 keys with
+// 32 heads 29.2 us instead of 26.5, uncut 41.0 instead of 38.3.)  Otherwise every wavefront fetches them itself, with its first
+// row offsets: the way through LDS and its barrier are longer than that for the few short rows of a decode step with heads
+// of 64 (843 keys with 4 heads 13.4 us through LDS, 13.1 so; with 32 heads of 128 through LDS 27.7, so 28.8).
+template <int D, bool kLazy, bool kStagedQ, typename QRow, typename Turn, typename Emit>
 __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& turn, int my_pos, int key0, int key1, float scale,
                                        char* lds, Emit&& emit) {
   using G = Geo<D>;
@@ -113,6 +115,8 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
   c = fmaxf(c, 1e-37f);  // (0 * -infinity is no number)
   c_lo = fmaxf(c_lo, 1e-37f);
   auto weight = [&](float t) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f(fmaf(t, c, t * c_lo)); };
+
+  int lo_pos = kStagedQ ? 0 : wave_min_i32(my_pos);  // no column ends before this position
 
   // addresses of the key and value row that lane `lane % 32` stands for, and its rotary table row
   const char* kp = nullptr;
@@ -148,14 +152,22 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
 #pragma unroll
   for (int i = 0; i < G::kBlocks; ++i) acc_o[i] = f32x16{0};
 
+  float q[D / 2];
+  if constexpr (!kStagedQ) {
+    const f32x4* row = reinterpret_cast<const f32x4*>(q_row(col)) + hi;
+#pragma unroll
+    for (int j = 0; j < G::kChunks / 2; ++j) {
+      const f32x4 x = row[2 * j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[4 * j + e] = x[e];
+    }
+  }
   const int n_blk = (key1 - key0 + kKeys - 1) / kKeys;
   locate(key0 + wave * kKeys);  // (for wavefronts without a block too: no branch, and with it no wait of its own)
   MPIC_WAIT_VMCNT(0);  // ordinary loads first: from here on the counter is managed by hand
   __builtin_amdgcn_sched_barrier(0);
   if (wave < n_blk) stage_keys();
-  float q[D / 2];
-  int lo_pos;  // no column ends before this position
-  {
+  if constexpr (kStagedQ) {
     char* area_q = lds + G::kQuery;
     const uint32_t area_q_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(MPIC_LDS_PTR(char, area_q)));
 #pragma unroll
@@ -173,9 +185,9 @@ __device__ __forceinline__ void attend(const Rows& src, QRow&& q_row, Turn&& tur
 #pragma unroll
       for (int e = 0; e < 4; ++e) q[4 * j + e] = x[e];
     }
-    turn(q);
   }
-  __builtin_amdgcn_sched_barrier(0);
+  turn(q);
+  if constexpr (kStagedQ) __builtin_amdgcn_sched_barrier(0);
   for (int t = wave; t < n_blk; t += kWaves) {
     const int j0 = key0 + t * kKeys;
     MPIC_WAIT_VMCNT(0);  // this block's keys have landed

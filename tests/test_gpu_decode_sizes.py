@@ -41,9 +41,10 @@ def test_lazy_context_lengths(n):
     _run_lazy(_bf16((n, 50), 14, 2))
 
 
+@pytest.mark.parametrize("heads", [(6, 2, 128), (4, 4, 64), (40, 1, 64)])
 @pytest.mark.parametrize("lens", [(1, 0), (255, 256), (257, 0, 3)])
-def test_fp32_context_lengths(lens):
-    p = _f32([[("text", n)] for n in lens], [], 0, 6, 2, 128)
+def test_fp32_context_lengths(lens, heads):
+    p = _f32([[("text", n)] for n in lens], [], 0, *heads)
     p.gpu_setup(False)
     p.gpu_assemble()
     _check_decode(p, True)
