@@ -92,7 +92,7 @@ __device__ inline void finish_rows(const DecodeArgs& a, int b, int g, int h0, in
       self *= a.scale;
     }
     const float lse = any_key ? part_lse[c] : -INFINITY;
-    const float m = fmaxf(lse, self);
+    const float m = any_key ? fmaxf(lse, self) : self;  // (a maximum would drop a self that is no number)
     f32x4 o = f32x4{0};
     float z = 0.f;
     if (m != -INFINITY) {

@@ -49,3 +49,16 @@ def test_fp32_context_lengths(lens, heads):
     p.gpu_assemble()
     _check_decode(p, True)
     _check_decode(p, False)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_new_token_that_is_no_number(dtype):
+    """A NaN in the key of the new token reaches its request's rows, whether or not the request has a context."""
+    p = _bf16((5, 0, 0), 14, 2) if dtype == "bf16" else _f32([[("text", n)] for n in (5, 0, 0)], [], 0, 6, 2, 128)
+    p.gpu_setup(False)
+    p.gpu_assemble()
+    q, nk, nv = p.decode_inputs()
+    nk[:2, :, 3] = float("nan")
+    out, lse = p.gpu_decode(q, nk, nv)
+    assert torch.isnan(torch.from_numpy(out[:2])).all() and torch.isnan(torch.from_numpy(lse[:2])).all()
+    assert (out[2] == nv[2].double().repeat_interleave(p.sh.n_q_heads // p.sh.n_kv_heads, 0).numpy()).all()
