@@ -577,12 +577,11 @@ int mpic_store_layer(mpic_store* store, uint64_t id, int32_t layer, mpic_chunk_s
  * not read may carry any id).  Per layer l the call does what mpic_assemble_kv followed
  * by mpic_selective_attn do with that layer's slices:
  *   fresh_q[l], fresh_k[l], fresh_v[l]  device, [n_fresh_rows][H][D]
- *   k_ctx[l], v_ctx[l]                  device, n_ctx_slots rows; the same buffer may be
- *                                       given to several layers (the library orders the
- *                                       linking of a later layer after the attention of
- *                                       the earlier one), distinct buffers let linking
- *                                       run further ahead
+ *   k_ctx[l], v_ctx[l]                  device, n_ctx_slots rows; distinct buffers let
+ *                                       linking run ahead
  *   out[l], lse[l]                      device; lse or lse[l] may be NULL
+ * Buffers of different layers may share memory (one context for all layers, an output that is
+ * the next layer's input): what shares it runs in the order of the layers.
  * Schedule: the stored part of layer l is linked on a library stream (host and disk
  * tiers: the kernel reads pinned memory in place over the bus, held to a few workgroups
  * so that it runs beside the attention of earlier layers -- or, when the batch uses its
@@ -591,8 +590,8 @@ int mpic_store_layer(mpic_store* store, uint64_t id, int32_t layer, mpic_chunk_s
  * layer ahead of the linking),
  * fresh rows and attention run on `stream`, joined by events.  When every cache the plan
  * reads is in GPU memory there is nothing to fetch ahead: the stored rows of layer l+1 are
- * then linked by the attention launch of layer l (mpic_selective_attn_link_next), all on
- * `stream`.  On a lazy_rope context such caches are not linked at all but read in place
+ * then linked by the attention launch of layer l (mpic_selective_attn_link_next), its fresh
+ * rows too, all on `stream`; F32 layers are each linked when their turn comes.  On a lazy_rope context such caches are not linked at all but read in place
  * (mpic_selective_attn_in_place): the context buffers then receive the fresh rows only;
  * caches of the other tiers are linked as stored.  The call returns when everything is enqueued; the host thread waits only for
  * file reads.

@@ -13,6 +13,7 @@
 #include <unistd.h>
 
 #include <algorithm>
+#include <array>
 #include <cerrno>
 #include <cinttypes>
 #include <cmath>
@@ -637,12 +638,32 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
     }
   };
 
+  // The linking of layer l may run beside earlier layers: which buffers those use that l's context lies in.
+  struct Span {
+    const void* at;
+    size_t bytes;
+  };
+  auto overlap = [](const Span& x, const Span& y) {
+    const char *a0 = static_cast<const char*>(x.at), *b0 = static_cast<const char*>(y.at);
+    return a0 && b0 && a0 < b0 + y.bytes && b0 < a0 + x.bytes;
+  };
+  const size_t ctx_bytes = static_cast<size_t>(n_ctx_slots) * st->row_bytes;
+  const size_t fresh_bytes = static_cast<size_t>(n_fresh_rows) * st->row_bytes, q_bytes = fresh_bytes * ctx->group;
+  const size_t lse_bytes = static_cast<size_t>(n_fresh_rows) * ctx->cfg.n_q_heads * sizeof(float);
+  auto in_context_of = [&](int32_t l, const Span& x) { return overlap(x, {k_ctx[l], ctx_bytes}) || overlap(x, {v_ctx[l], ctx_bytes}); };
+  auto written_by = [&](int32_t j) { return std::array<Span, 2>{Span{out[j], q_bytes}, Span{lse ? lse[j] : nullptr, lse_bytes}}; };
+  auto attention_meets = [&](int32_t j, int32_t l) {  // attention of layer j, context of layer l
+    bool meets = in_context_of(l, {fresh_q[j], q_bytes}) || in_context_of(l, {k_ctx[j], ctx_bytes}) || in_context_of(l, {v_ctx[j], ctx_bytes});
+    for (const Span& x : written_by(j)) meets = meets || in_context_of(l, x);
+    return meets;
+  };
+
   // Every cache the plan reads is in GPU memory: nothing to fetch ahead.  When the planner's
   // simulation of the attention launch leaves anything idle at its end, the stored rows of
   // layer l+1 are linked by the attention launch of layer l itself, in workgroups that run as
   // that attention drains: one stream, no events (link_fits_attention_tail has the rule and both
-  // sides).  A context buffer shared by consecutive layers cannot be
-  // written while it is read: those layers are linked by a launch of their own.
+  // sides).  A context that shares memory with what the layer before reads or writes
+  // cannot be written meanwhile: those layers are linked by a launch of their own.
   // lazy_rope context with every cache in GPU memory: the caches are linked by reference.  No
   // stored row is copied; each layer is the scatter of its fresh rows and an attention launch
   // that reads the caches where the store keeps them.
@@ -660,20 +681,9 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
     return MPIC_OK;
   }
   if (rows_stored == 0 && mpic::can_link_in_attention(ctx, plan) && mpic::link_fits_attention_tail(ctx, plan)) {
-    // The fresh rows of layer l+1 go along where nothing that layer l reads or writes is among the buffers
-    // concerned: a scatter of its own costs 4 us a layer (four layers of a 2.7K-token request 183 -> 165 us).
+    // The fresh rows of layer l+1 go along where they share no memory with what layer l writes or with the context they go
+    // to: a scatter of its own costs 4 us a layer (four layers of a 2.7K-token request 183 -> 165 us).
     std::vector<mpic_chunk_src> next_srcs(std::max(n_srcs, 0));
-    struct Span {
-      const void* at;
-      size_t bytes;
-    };
-    auto overlap = [](const Span& x, const Span& y) {
-      const char *a0 = static_cast<const char*>(x.at), *b0 = static_cast<const char*>(y.at);
-      return a0 && b0 && a0 < b0 + y.bytes && b0 < a0 + x.bytes;
-    };
-    const size_t ctx_bytes = static_cast<size_t>(n_ctx_slots) * st->row_bytes;
-    const size_t fresh_bytes = static_cast<size_t>(n_fresh_rows) * st->row_bytes, q_bytes = fresh_bytes * ctx->group;
-    const size_t lse_bytes = static_cast<size_t>(n_fresh_rows) * ctx->cfg.n_q_heads * sizeof(float);
     bool linked = false, scattered = false;  // stored / fresh rows of the current layer are already in place
     for (int32_t l = 0; l < n_layers; ++l) {
       if (!linked) fill_srcs(l, srcs);
@@ -682,20 +692,17 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
                                   k_ctx[l], v_ctx[l], n_ctx_slots, linked ? MPIC_PART_FRESH : MPIC_PART_CACHED | MPIC_PART_FRESH, stream);
         if (rc != MPIC_OK) return rc;
       }
-      linked = l + 1 < n_layers;
-      for (const void* next : {l + 1 < n_layers ? k_ctx[l + 1] : nullptr, l + 1 < n_layers ? v_ctx[l + 1] : nullptr})
-        for (const void* now : {k_ctx[l], v_ctx[l]}) linked = linked && !overlap({next, ctx_bytes}, {now, ctx_bytes});
+      linked = l + 1 < n_layers && !attention_meets(l, l + 1);
       scattered = false;
       mpic::NextLink next{next_srcs.data(), n_srcs, nullptr, nullptr, nullptr, nullptr, &scattered};
       if (linked) {
         fill_srcs(l + 1, next_srcs);
         next.k_ctx = k_ctx[l + 1];
         next.v_ctx = v_ctx[l + 1];
-        const Span in_k{fresh_k[l + 1], fresh_bytes}, in_v{fresh_v[l + 1], fresh_bytes}, to_k{next.k_ctx, ctx_bytes}, to_v{next.v_ctx, ctx_bytes};
-        const Span q{fresh_q[l], q_bytes}, o{out[l], q_bytes}, e{lse ? lse[l] : nullptr, lse_bytes};
-        bool apart = !overlap(in_k, to_k) && !overlap(in_k, to_v) && !overlap(in_v, to_k) && !overlap(in_v, to_v);
-        for (const Span& x : {o, e}) apart = apart && !overlap(x, in_k) && !overlap(x, in_v) && !overlap(x, to_k) && !overlap(x, to_v);
-        if (apart && !overlap(q, to_k) && !overlap(q, to_v)) {
+        const Span in_k{fresh_k[l + 1], fresh_bytes}, in_v{fresh_v[l + 1], fresh_bytes};
+        bool apart = !in_context_of(l + 1, in_k) && !in_context_of(l + 1, in_v);
+        for (const Span& x : written_by(l)) apart = apart && !overlap(x, in_k) && !overlap(x, in_v);
+        if (apart) {
           next.fresh_k = fresh_k[l + 1];
           next.fresh_v = fresh_v[l + 1];
         }
@@ -721,7 +728,6 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
     }
     return MPIC_OK;
   }
-  std::unordered_map<const void*, int32_t> last_reader;  // context buffer -> layer whose attention read it last
   for (int32_t l = 0; l < n_layers; ++l) {
     if (n_disk > 0) {
       std::unique_lock<std::mutex> lock(st->mu);
@@ -743,12 +749,12 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
       }
     }
     fill_srcs(l, srcs);
-    // stored rows: on the library's stream, after whatever last read these buffers
-    for (const void* buf : {static_cast<const void*>(k_ctx[l]), static_cast<const void*>(v_ctx[l])}) {
-      auto it = last_reader.find(buf);
-      if (it != last_reader.end())
-        MPIC_HIP(ctx, hipStreamWaitEvent(ctx->link_stream, ctx->ev_layer[2 * it->second + 1], 0));
-    }
+    // stored rows: on the library's stream, after the last layer that used the memory these buffers lie in
+    for (int32_t j = l - 1; j >= 0; --j)
+      if (attention_meets(j, l) || in_context_of(l, {fresh_k[j], fresh_bytes}) || in_context_of(l, {fresh_v[j], fresh_bytes})) {
+        MPIC_HIP(ctx, hipStreamWaitEvent(ctx->link_stream, ctx->ev_layer[2 * j + 1], 0));
+        break;
+      }
     rc = mpic::assemble_parts(ctx, plan, srcs.data(), n_srcs, nullptr, nullptr, 0, k_ctx[l], v_ctx[l], n_ctx_slots,
                               MPIC_PART_CACHED | MPIC_PART_BACKGROUND, ctx->link_stream);
     if (rc != MPIC_OK) return rc;
@@ -768,8 +774,6 @@ int prefill_layers(mpic_ctx* ctx, mpic_plan* plan, mpic_store* st, const uint64_
                       lse ? lse[l] : nullptr, stream, nullptr, ctx->attn_block_keys ? 0 : 64);
     if (rc != MPIC_OK) return rc;
     MPIC_HIP(ctx, hipEventRecord(ctx->ev_layer[2 * l + 1], stream));
-    last_reader[k_ctx[l]] = l;
-    last_reader[v_ctx[l]] = l;
   }
   return MPIC_OK;
 }
