@@ -424,9 +424,9 @@ int mpic_selective_attn_link_next(mpic_ctx* ctx, mpic_plan* plan, const void* fr
  *   lse               device float [B][Hq], written; may be NULL
  * Partial results of the key splits live in a workspace owned by the context, allocated on
  * the first call and grown when a later call needs more (what it outgrew stays, as above);
- * calls on one context must therefore not overlap on different streams.  Under capture the
- * workspace has to be there already; an F32 step whose splits do not fit it runs unsplit
- * if an earlier step has been over as many rows.
+ * calls on one context must therefore not overlap on different streams.  Under capture a BF16
+ * step that is split needs the workspace to be there already; an F32 step whose splits do not
+ * fit what is there runs unsplit.  A step that is not split does without.
  * Errors: MPIC_ERR_INVALID, MPIC_ERR_OOM (workspace), MPIC_ERR_HIP.
  */
 int mpic_decode_attn(mpic_ctx* ctx, mpic_plan* plan, const void* q, const void* new_k,

@@ -884,29 +884,29 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
     n_splits = static_cast<int32_t>((max_ctx + kps - 1) / kps);  // <= 256, the merge kernel holds up to 1024 weights
   }
   const size_t rows = static_cast<size_t>(plan->n_requests) * c.n_q_heads;
-  size_t need = rows * n_splits * (c.head_dim + 1) * sizeof(float);
-  float* ws = nullptr;
+  const auto need = [&] { return rows * n_splits * (c.head_dim + 1) * sizeof(float); };
+  const auto unsplit = [&] {
+    n_splits = 1;
+    keys_per_split = std::max(max_ctx, 1);
+  };
+  float* ws = nullptr;  // (only split steps write there)
   if (static_scratch) {
     size_t have = 0;
     MPIC_HIP(ctx, mpic::decode_static_scratch(&ws, &have));
-    if (need > have && c.dtype == MPIC_F32) {  // fp32 also runs unsplit: fits whenever a row's partial does
-      n_splits = 1;
-      keys_per_split = max_ctx;
-      need = rows * (c.head_dim + 1) * sizeof(float);
-    }
-    if (need > have)
-      return fail(ctx, MPIC_ERR_UNSUPPORTED, "decode_attn_static: the partial results of this batch (" + std::to_string(need) +
+    if (need() > have && c.dtype == MPIC_F32) unsplit();
+    // (the limit of the entry point counts a row's result also where it is the only one)
+    if (need() > have)
+      return fail(ctx, MPIC_ERR_UNSUPPORTED, "decode_attn_static: the partial results of this batch (" + std::to_string(need()) +
                                              " bytes) exceed the static scratch array (" + std::to_string(have) + " bytes)");
   } else {
-    // A captured fp32 step whose splits find no room runs unsplit in what is there (nothing can be
-    // allocated under capture, and one split per row is what an earlier step over as many rows has left).
-    const size_t unsplit = rows * (c.head_dim + 1) * sizeof(float);
-    if (need > ctx->decode_ws.bytes && c.dtype == MPIC_F32 && unsplit <= ctx->decode_ws.bytes && !mpic::trackable(stream)) {
-      n_splits = 1;
-      keys_per_split = max_ctx;
-      need = unsplit;
+    if (need() > ctx->decode_ws.bytes) {
+      // Nothing can be allocated under capture: an fp32 step whose splits find no room runs unsplit.  A step that is
+      // not split does without the workspace; it leaves one for a captured step that may follow.
+      const bool captured = mpic::capturing(stream);
+      if (captured && c.dtype == MPIC_F32) unsplit();
+      if ((n_splits > 1 || !captured) && !mpic::grow(ctx, &ctx->decode_ws, need(), n_splits > 1) && n_splits > 1)
+        return fail(ctx, MPIC_ERR_OOM, "decode_attn: workspace allocation failed");
     }
-    if (!mpic::grow(ctx, &ctx->decode_ws, need)) return fail(ctx, MPIC_ERR_OOM, "decode_attn: workspace allocation failed");
     ws = static_cast<float*>(ctx->decode_ws.ptr);
   }
   mpic::DecodeArgs a{};
@@ -921,7 +921,7 @@ static int decode_attn_impl(mpic_ctx* ctx, mpic_plan* plan, const void* q, const
   a.out = out;
   a.lse = lse;
   a.ws_o = ws;
-  a.ws_lse = a.ws_o + rows * n_splits * c.head_dim;
+  a.ws_lse = ws ? ws + rows * n_splits * c.head_dim : nullptr;
   a.scale = static_cast<float>(softmax_scale);
   a.n_q_heads = c.n_q_heads;
   a.n_kv_heads = c.n_kv_heads;

@@ -229,6 +229,9 @@ int main() {
     CHECK(assemble(c, p, &s[0]) == MPIC_OK && assemble(c, q, &s[0]) == MPIC_OK);
     CHECK(p->n_parts_f32 == 0 && q->n_parts_f32 == 0 && attend(c, q, &s[0]) == MPIC_OK);
     for (const mpic::Scratch& w : c->attn_ws) CHECK(!w.ptr);
+    capture(&s[1], true);  // no step before has left any room
+    CHECK(decode(c, q, &s[1]) == MPIC_OK && mpic::last_decode.n_splits == 1 && mpic::last_decode.keys_per_split == 5000);
+    capture(&s[1], false);
     CHECK(decode(c, p, &s[0]) == MPIC_OK && mpic::last_decode.n_splits == 1);
     float* const first = mpic::last_decode.ws_o;  // as a captured step holds it
     capture(&s[1], true);
@@ -238,6 +241,23 @@ int main() {
     const int syncs = n_syncs;
     CHECK(decode(c, q, &s[0]) == MPIC_OK && mpic::last_decode.n_splits > 1 && mpic::last_decode.ws_o != first);
     CHECK(sizes.count(first) == 1 && n_syncs == syncs);
+    mpic_plan_destroy(p);
+    mpic_plan_destroy(q);
+    mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  {  // a decode step whose keys are not split needs no memory, captured or not; a split one that finds none fails
+    mpic_ctx* c = context(MPIC_BF16);
+    mpic_plan *p = plan_of(c, 200), *q = plan_of(c, 600);
+    CHECK(assemble(c, p, &s[0]) == MPIC_OK && assemble(c, q, &s[0]) == MPIC_OK);
+    capture(&s[1], true);
+    CHECK(decode(c, p, &s[1]) == MPIC_OK && mpic::last_decode.n_splits == 1);
+    capture(&s[1], false);
+    limit = in_use;
+    CHECK(decode(c, p, &s[0]) == MPIC_OK && mpic::last_decode.n_splits == 1);
+    CHECK(decode(c, q, &s[0]) == MPIC_ERR_OOM);
+    limit = SIZE_MAX;
+    CHECK(!c->decode_ws.ptr);
     mpic_plan_destroy(p);
     mpic_plan_destroy(q);
     mpic_destroy(c);
