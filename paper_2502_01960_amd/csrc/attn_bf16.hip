@@ -926,7 +926,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int quad = threadIdx.x >> 3;
   const int d = quad * 4;
   const int flat = m.row0 + local;
-  const int64_t fresh_row = m.pad[0] + flat / group;
+  const int64_t fresh_row = m.q_off + flat / group;
   const int head = m.kv_head * group + flat % group;
   const int64_t slot0 = static_cast<int64_t>(m.first_part) * kAttnTileRows + local;
   // the first piece starts at key 0, which every row sees: the maximum is finite from the

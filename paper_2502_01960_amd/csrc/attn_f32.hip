@@ -135,7 +135,7 @@ __global__ __launch_bounds__(2 * D) void merge_f32_kernel(AttnArgs a) {
     }
   }
   const int flat = m.row0 + row;
-  const int64_t item = (m.pad[0] + flat / group) * static_cast<int64_t>(a.n_q_heads) + g * group + flat % group;
+  const int64_t item = (m.q_off + flat / group) * static_cast<int64_t>(a.n_q_heads) + g * group + flat % group;
   *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + item * D + d) = o * (1.f / z);
   if (a.lse && d == 0) a.lse[item] = mx + logf(z);
 }

@@ -38,7 +38,8 @@ static_assert(sizeof(AttnWork) == 32, "read with one scalar load");
 struct AttnMerge {
   int32_t req, kv_head, row0, n_rows;
   int32_t first_part, n_parts;  // partial slots first_part .. first_part + n_parts - 1, in key order
-  int32_t pad[2];  // first fresh row of the request; 0
+  int32_t q_off;  // first fresh row of the request
+  int32_t pad;
 };
 static_assert(sizeof(AttnMerge) == 32, "merge item layout");
 

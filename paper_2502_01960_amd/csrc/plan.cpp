@@ -234,7 +234,7 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
         m.n_rows = static_cast<int32_t>(n);
         m.first_part = chosen.n_parts;
         m.n_parts = static_cast<int32_t>(parts);
-        m.pad[0] = p.q_off[b];
+        m.q_off = p.q_off[b];
         chosen.n_parts += static_cast<int32_t>(parts);
         chosen.merges.push_back(m);
         // the pieces of this (tile, g) were pushed last into their group, in key order
@@ -410,7 +410,7 @@ void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
   for (const AttnPieceF32& t : tiles) {
     const int64_t blocks = blocks_of(t), parts = (blocks + cut - 1) / cut;
     if (parts > 1) {
-      p.merges_f32.push_back(AttnMerge{t.req, 0, t.row0, t.n_rows, p.n_parts_f32, static_cast<int32_t>(parts), {t.q_off, 0}});
+      p.merges_f32.push_back(AttnMerge{t.req, 0, t.row0, t.n_rows, p.n_parts_f32, static_cast<int32_t>(parts), t.q_off, 0});
     }
     for (int64_t i = 0; i < parts; ++i) {
       AttnPieceF32 x = t;

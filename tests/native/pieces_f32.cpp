@@ -72,7 +72,7 @@ int main() {
       std::vector<int> merged(p->n_parts_f32, 0);
       for (const auto& m : p->merges_f32) {
         const auto& pieces = of_tile.at({m.req, m.row0});
-        CHECK(static_cast<int>(pieces.size()) == m.n_parts && m.n_parts > 1 && m.pad[0] == p->q_off[m.req]);
+        CHECK(static_cast<int>(pieces.size()) == m.n_parts && m.n_parts > 1 && m.q_off == p->q_off[m.req]);
         CHECK(m.n_rows == tiles.at({m.req, m.row0}).n_rows);
         int part = m.first_part;
         for (const auto& x : pieces) {  // in key order
