@@ -399,9 +399,18 @@ void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
   if (total * heads >= 4 * longest * cus) return;  // several rounds of the longest tile: even enough
   int64_t cut = longest, best = simulate(longest, INT64_MAX);
   best -= best * 5 / 100;  // a cut launch has to be worth its partial results
-  for (int64_t cap = kSimds; cap < longest; cap += std::max<int64_t>(1, cap / 5)) {
-    const int64_t end = simulate(cap, best);
-    if (end < best) {
+  std::vector<int64_t> caps;
+  for (int64_t cap = kSimds; cap < longest; cap += std::max<int64_t>(1, cap / 5)) caps.push_back(cap);
+  // Tried from a compute unit's share outwards, where the best one mostly lies: the others are then seen to be no better
+  // without a look at most of their pieces.  Of equally good ones the shortest is taken.
+  const int64_t share = total * heads / cus;
+  size_t lo = std::lower_bound(caps.begin(), caps.end(), share) - caps.begin(), hi = lo;
+  while (lo > 0 || hi < caps.size()) {
+    const bool up = lo == 0 || (hi < caps.size() && caps[hi] * caps[lo - 1] <= share * share);
+    const int64_t cap = up ? caps[hi++] : caps[--lo];
+    const int64_t bound = best + (cap < cut && cut < longest);
+    const int64_t end = simulate(cap, bound);
+    if (end < bound) {
       best = end;
       cut = cap;
     }
