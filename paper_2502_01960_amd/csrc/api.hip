@@ -736,7 +736,7 @@ int mpic::attend(mpic_ctx* ctx, mpic_plan* plan, const void* fresh_q,
     a.n_merges = static_cast<int32_t>(plan->merges.size());
   }
   a.block_keys = block_keys ? block_keys : ctx->attn_block_keys ? ctx->attn_block_keys : ctx->background_seen ? 64 : 96;
-  if (lazy && !block_keys && !ctx->attn_block_keys && !ctx->background_seen && plan->n_blocks <= mpic::kHalfTileBlocks) {
+  if (lazy && !block_keys && !ctx->attn_block_keys && !ctx->background_seen && plan->half_tiles) {
     a.half_tiles = 1;
     a.block_keys = mpic::kHalfTileBlock;
   }

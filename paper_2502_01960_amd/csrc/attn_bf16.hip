@@ -50,7 +50,7 @@ constexpr int ROW_BYTES = D * 2;  // one staged key or value row
 //            two workgroups share a compute unit and one computes while the other starts, turns its queries
 //            or stores; and a half walks only the blocks its own rows reach.  Twice the K/V stream per flop makes it 14 %
 //            slower where tiles are long.  Built for caches read in place only: there the kernel of eight
-//            wavefronts spills, and short launches are 4 to 22 % faster in halves (launch_attn_bf16 has the rule), while
+//            wavefronts spills, and short launches are mostly faster in halves (runs_in_halves of the planner has the rule), while
 //            those over linked contexts are 0.92 to 1.14 of the time, 1.04 on average.
 template <int kBlockKeys, int kWaves>
 struct Geo {

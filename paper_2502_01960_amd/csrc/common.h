@@ -180,7 +180,7 @@ struct mpic_plan {
   // last workgroup ends, and the compute-unit time left idle until then (summed over the chip)
   int64_t est_makespan_blocks = 0;
   int64_t est_idle_blocks = 0;
-  int64_t n_blocks = 0;  // 64-key blocks of all tiles
+  bool half_tiles = false;  // lazy_rope contexts: the attention is faster in half tiles
   std::vector<int32_t> launch_est;  // MPIC_PLAN_LAUNCH_ESTIMATE
   std::vector<float> rope_cos, rope_sin;
   // contexts with lazy_rope only: key blocks per block size, first block of every request,
@@ -190,7 +190,7 @@ struct mpic_plan {
   std::vector<int32_t> kblk_first[mpic::kNumBlockSizes];
   std::vector<int32_t> kblk_mid[mpic::kNumBlockSizes];    // [B] first stored block of every request (its fresh blocks come first)
   std::vector<int32_t> lazy_range[mpic::kNumBlockSizes];  // [n_tiles][4] fresh blocks [f0, f1) and stored blocks [s0, s1) of every tile
-  std::vector<int32_t> lazy_half;  // [n_tiles][2][4] the same for the halves of every tile (kHalfTileBlock)
+  std::vector<int32_t> lazy_half;  // [n_tiles][2][4] the same for the halves of every tile (kHalfTileBlock; only with half_tiles)
   std::vector<int32_t> kblk_parts[mpic::kNumBlockSizes];  // [B][3] first fresh block, first stored block, end, for mpic_plan_get
   std::vector<int32_t> fresh_rot;            // contexts with fresh_pre_rope only
   std::vector<float> fresh_cos, fresh_sin;   // one row per distinct position id
@@ -317,10 +317,6 @@ enum { kAblateLoads = 1,     // K/V blocks are staged only until every ring slot
        kAblateNoLoadWaits = 32,    // no wait for staged blocks inside the loop (only with kAblateLdsReads)
        kAblateAddressesOnly = 64 };// the addresses of the direct loads are formed, the loads are not issued
 constexpr int kProbeOptionAblate = 1000;  // mpic_set_option of the probe library: value = mask of kAblate*
-// Launches over caches read in place of up to this many 64-key blocks per compute unit run in half tiles: of 51 drawn batches
-// below it 46 took 0.78 to 0.99 of the time of the 96-key shape (0.91 on average, 1.11 at most), of 19 above it 15
-// were 0 to 14 % slower.
-constexpr int64_t kHalfTileBlocks = 180 * 256;
 // Contexts with lazy_rope: stored keys are never turned to their global position.  The kernel
 // walks the request's key blocks (KeyBlock: all keys of a block come from one source and lack
 // the same shift) and turns its *queries* back by that shift whenever the

@@ -106,7 +106,6 @@ void build_tiles(mpic_plan& p, int group, int n_kv_heads) {
     }
   }
   const int64_t per_cu = (total_blocks + kComputeUnits - 1) / kComputeUnits;
-  p.n_blocks = total_blocks;
   // How a tile of `blocks` blocks is cut: tiles longer than `cap` into even pieces, or into pieces
   // of exactly `cap` and a remainder.  Even pieces suit launches of one round, where the longest
   // piece decides; equal pieces with remainders fill the end of a launch of several.
@@ -432,6 +431,29 @@ void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
   std::stable_sort(p.pieces_f32.begin(), p.pieces_f32.end(), longer);
 }
 
+// Whether the attention over caches in place runs in half tiles, two workgroups of four wavefronts for each, or in whole
+// ones of eight.  Halves start sooner, fill each other's gaps on a compute unit and skip blocks that only the other half's rows
+// reach; whole tiles read every block once for all rows and have fewer barriers per key.  Time of 164 launches of 17 to
+// 440 us in halves, relative to whole tiles:
+//   tall tiles (more than half the rows) hold most of the blocks: 0.76 to 1.01 (0.90 on average; one 1.08) where they are short
+//     or not cut; cut into long pieces, which gain neither start nor balance, 0.98 to 1.07 (1.03);
+//   low tiles, which leave one wavefront on a SIMD in either shape: up to four blocks per compute unit 0.76 to 1.01 (0.92),
+//     above that 0.86 to 1.33 (1.04);
+//   more than 180 blocks per compute unit: 1.0 to 1.14.
+bool runs_in_halves(const mpic_plan& p) {
+  int64_t pieces = 0, cut = 0, blocks = 0, tall = 0;
+  for (const AttnTile& t : p.tiles) {
+    if (t.n_rows <= 0) continue;
+    const int64_t b = (t.n_keys - t.key0 + 63) / 64;
+    ++pieces;
+    cut += t.part >= 0;
+    blocks += b;
+    if (t.n_rows > kAttnTileRows / 2) tall += b;
+  }
+  if (2 * tall < blocks) return blocks <= 4 * kComputeUnits;
+  return blocks <= 180 * kComputeUnits && (3 * cut < 2 * pieces || blocks <= 28 * pieces);
+}
+
 // Key blocks of a lazy_rope plan (see KeyBlock), as the kernels walk them.  The list of a request
 // holds its fresh blocks first and its stored blocks after them, each part in position order: a
 // kernel that walks a tile in list order changes the shift its queries are turned back by once per
@@ -487,7 +509,7 @@ void build_key_blocks(mpic_plan& p, int group) {
     for (const AttnTile& t : p.tiles) {
       if (t.n_rows <= 0) {
         ranges.insert(ranges.end(), {0, 0, 0, 0});
-        if (bn == kHalfTileBlock) p.lazy_half.insert(p.lazy_half.end(), 8, 0);
+        if (p.half_tiles && bn == kHalfTileBlock) p.lazy_half.insert(p.lazy_half.end(), 8, 0);
         continue;
       }
       const int32_t end = t.part >= 0 ? tile_end[t.part] : t.n_keys;
@@ -504,7 +526,7 @@ void build_key_blocks(mpic_plan& p, int group) {
       const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.n_keys / end);
       const int32_t r[4] = {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf};
       ranges.insert(ranges.end(), r, r + 4);
-      if (bn != kHalfTileBlock) continue;
+      if (!p.half_tiles || bn != kHalfTileBlock) continue;
       // the same for the tile's halves of rows: the first one reaches less far (at least one block each, so that
       // a half whose rows see nothing of a piece has something to walk)
       for (int32_t row = 0; row < kAttnTileRows; row += kAttnTileRows / 2) {
@@ -785,7 +807,10 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
     if (ctx->cfg.fresh_pre_rope) mpic::build_fresh_rope(*p, ctx->cfg);
     mpic::build_tiles(*p, ctx->group, ctx->cfg.n_kv_heads);
     if (ctx->cfg.dtype == MPIC_F32) mpic::build_pieces_f32(*p, ctx->group, ctx->cfg.n_kv_heads, ctx->cfg.head_dim);
-    if (ctx->cfg.lazy_rope) mpic::build_key_blocks(*p, ctx->group);
+    if (ctx->cfg.lazy_rope) {
+      p->half_tiles = mpic::runs_in_halves(*p);
+      mpic::build_key_blocks(*p, ctx->group);
+    }
     {
       auto clamp = [](int64_t x) { return static_cast<int32_t>(std::min<int64_t>(x, INT32_MAX)); };
       p->launch_est = {clamp(p->est_makespan_blocks), clamp(p->est_idle_blocks),

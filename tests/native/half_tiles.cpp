@@ -19,7 +19,41 @@ hipError_t decode_static_scratch(float**, size_t*) { return hipErrorInvalidDevic
 
 #define CHECK(...) do { if (!(__VA_ARGS__)) { std::fprintf(stderr, "check failed: %s (line %d, case %d)\n", #__VA_ARGS__, __LINE__, iter); return 1; } } while (0)
 
+// One request per entry of `rows`: that many fresh rows behind a chunk of `len` stored ones.
+bool in_halves(int hq, int hkv, int requests, int rows, int len) {
+  mpic_config cfg{};
+  cfg.n_q_heads = hq;
+  cfg.n_kv_heads = hkv;
+  cfg.head_dim = 128;
+  cfg.dtype = MPIC_BF16;
+  cfg.rope_theta = 1e4;
+  cfg.lazy_rope = 1;
+  mpic_ctx* ctx = nullptr;
+  mpic_plan* p = nullptr;
+  if (mpic_create(&ctx, &cfg) != MPIC_OK) return false;
+  std::vector<int32_t> seg_off(1, 0);
+  std::vector<mpic_segment> segs(2 * requests);
+  for (int b = 0; b < requests; ++b) {
+    segs[2 * b].kind = 1;
+    segs[2 * b].chunk = b;
+    segs[2 * b].len = len;
+    segs[2 * b + 1].len = rows;
+    seg_off.push_back(2 * b + 2);
+  }
+  const bool halves = mpic_plan_create(ctx, requests, seg_off.data(), segs.data(), 0, nullptr, nullptr, 0, &p) == MPIC_OK && p->half_tiles;
+  mpic_plan_destroy(p);
+  mpic_destroy(ctx);
+  return halves;
+}
+
 int main() {
+  {  // which launches run in halves: low tiles up to four blocks per compute unit, tall ones unless they are cut into long pieces, or very many
+    const int iter = -2;
+    CHECK(in_halves(32, 32, 4, 40, 400) && !in_halves(32, 32, 4, 40, 600));
+    CHECK(!in_halves(32, 32, 8, 96, 5000));
+    CHECK(in_halves(32, 32, 3, 240, 1000) && !in_halves(32, 32, 3, 240, 6000));
+    CHECK(in_halves(32, 32, 12, 240, 3000) && !in_halves(32, 32, 30, 240, 6000));
+  }
   std::mt19937 rng(11);
   auto rnd = [&](int lo, int hi) { return lo + static_cast<int>(rng() % static_cast<unsigned>(hi - lo + 1)); };
   const int heads[][2] = {{4, 4}, {28, 4}, {32, 8}, {7, 1}, {40, 1}, {64, 8}};
@@ -58,8 +92,8 @@ int main() {
     mpic_plan* p = nullptr;
     CHECK(mpic_plan_create_selected(ctx, B, seg_off.data(), segs.data(), 8, sel_off.data(), sel.data(), nullptr, nullptr, 0, &p) == MPIC_OK);
     const int s = mpic::block_size_index(mpic::kHalfTileBlock), group = ctx->group;
-    CHECK(p->lazy_half.size() == p->tiles.size() * 8 && p->lazy_range[s].size() == p->tiles.size() * 4);
-    for (size_t i = 0; i < p->tiles.size(); ++i) {
+    CHECK(p->lazy_half.size() == (p->half_tiles ? p->tiles.size() * 8 : 0) && p->lazy_range[s].size() == p->tiles.size() * 4);
+    for (size_t i = 0; p->half_tiles && i < p->tiles.size(); ++i) {
       const mpic::AttnTile& t = p->tiles[i];
       const int32_t* r = p->lazy_range[s].data() + 4 * i;
       for (int half = 0; half < 2; ++half) {
