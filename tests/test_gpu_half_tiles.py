@@ -1,8 +1,10 @@
 """Attention over caches read in place in half tiles (needs an MI355X): tiles with no second half, with
 one row in it, rows that straddle it, pieces that a half sees nothing of, and head groupings whose heads
 split over the halves; both lazy routes against the oracle at the gates of the lazy tests."""
+import numpy as np
 import pytest
 
+import paper_2502_01960_amd as mpic
 from test_gpu_decode_sizes import _bf16
 from test_gpu_lazy import _run_lazy
 from test_gpu_parity import _custom
@@ -34,3 +36,21 @@ def test_halves_of_cut_tiles(pre_rope, interleaved):
     p = _custom(requests, 2, [1900, 700], 3)
     p.pre_rope, p.interleaved = pre_rope, interleaved
     _run_lazy(p)
+
+
+@pytest.mark.parametrize("k", [16, 64])
+def test_error_is_no_larger_than_in_whole_tiles(k):
+    """Against float64: both round their weights to bf16, relative to reference points that halves take from more keys."""
+    p = _custom([[("text", 190), ("chunk", i, 400, k), ("text", 160)] for i in range(4)], 4, [400] * 4, 3)
+    p.lazy = True
+    p.gpu_setup(False)
+    p.gpu_assemble()
+    ref, _ = p.oracle_attend(*p.oracle_link())
+    outs, err = {}, {}
+    for block_keys in (0, 96):
+        p.ctx.set_option(mpic.MPIC_OPT_ATTN_BLOCK_KEYS, block_keys)
+        p.gpu_attend()
+        outs[block_keys] = p.out.double().cpu().numpy()
+        err[block_keys] = np.linalg.norm(outs[block_keys] - ref) / np.linalg.norm(ref)
+    assert not np.array_equal(outs[0], outs[96]), "the launch is to run in half tiles"
+    assert err[0] <= err[96], err
