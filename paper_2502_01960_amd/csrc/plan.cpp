@@ -431,38 +431,14 @@ void build_pieces_f32(mpic_plan& p, int group, int n_kv_heads, int head_dim) {
   std::stable_sort(p.pieces_f32.begin(), p.pieces_f32.end(), longer);
 }
 
-// Whether the attention over caches in place runs in half tiles, two workgroups of four wavefronts for each, or in whole
-// ones of eight.  Halves start sooner, fill each other's gaps on a compute unit and skip blocks that only the other half's rows
-// reach; whole tiles read every block once for all rows and have fewer barriers per key.  Time of 164 launches of 17 to
-// 440 us in halves, relative to whole tiles:
-//   tall tiles (more than half the rows) hold most of the blocks: 0.76 to 1.01 (0.90 on average; one 1.08) where they are short
-//     or not cut; cut into long pieces, which gain neither start nor balance, 0.98 to 1.07 (1.03);
-//   low tiles, which leave one wavefront on a SIMD in either shape: up to four blocks per compute unit 0.76 to 1.01 (0.92),
-//     above that 0.86 to 1.33 (1.04);
-//   more than 180 blocks per compute unit: 1.0 to 1.14.
-bool runs_in_halves(const mpic_plan& p) {
-  int64_t pieces = 0, cut = 0, blocks = 0, tall = 0;
-  for (const AttnTile& t : p.tiles) {
-    if (t.n_rows <= 0) continue;
-    const int64_t b = (t.n_keys - t.key0 + 63) / 64;
-    ++pieces;
-    cut += t.part >= 0;
-    blocks += b;
-    if (t.n_rows > kAttnTileRows / 2) tall += b;
-  }
-  if (2 * tall < blocks) return blocks <= 4 * kComputeUnits;
-  return blocks <= 180 * kComputeUnits && (3 * cut < 2 * pieces || blocks <= 28 * pieces);
-}
-
 // Key blocks of a lazy_rope plan (see KeyBlock), as the kernels walk them.  The list of a request
 // holds its fresh blocks first and its stored blocks after them, each part in position order: a
 // kernel that walks a tile in list order changes the shift its queries are turned back by once per
 // chunk instance (softmax does not care about the order of the keys).  A tile visits the blocks
 // that start at or before its last row, a prefix of both parts; the pieces of a tile that was cut
 // along the keys share those blocks in proportion to their key ranges, in list order.
-void build_key_blocks(mpic_plan& p, int group) {
+void build_key_blocks(mpic_plan& p) {
   const int B = p.n_requests;
-  p.lazy_half.clear();
   p.key_order.clear();
   p.key_order.reserve(p.n_ctx);
   for (int b = 0; b < B; ++b) {
@@ -509,7 +485,6 @@ void build_key_blocks(mpic_plan& p, int group) {
     for (const AttnTile& t : p.tiles) {
       if (t.n_rows <= 0) {
         ranges.insert(ranges.end(), {0, 0, 0, 0});
-        if (p.half_tiles && bn == kHalfTileBlock) p.lazy_half.insert(p.lazy_half.end(), 8, 0);
         continue;
       }
       const int32_t end = t.part >= 0 ? tile_end[t.part] : t.n_keys;
@@ -526,25 +501,75 @@ void build_key_blocks(mpic_plan& p, int group) {
       const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(nf + ns) * t.n_keys / end);
       const int32_t r[4] = {std::min(lo, nf), std::min(hi, nf), std::max(lo, nf) - nf, std::max(hi, nf) - nf};
       ranges.insert(ranges.end(), r, r + 4);
-      if (!p.half_tiles || bn != kHalfTileBlock) continue;
-      // the same for the tile's halves of rows: the first one reaches less far (at least one block each, so that
-      // a half whose rows see nothing of a piece has something to walk)
-      for (int32_t row = 0; row < kAttnTileRows; row += kAttnTileRows / 2) {
-        if (row >= t.n_rows) {
-          p.lazy_half.insert(p.lazy_half.end(), {0, 0, 0, 0});
-          continue;
-        }
-        const int32_t last_row = t.row0 + std::min(t.n_rows, row + kAttnTileRows / 2) - 1;
-        const int32_t reach = p.q_pos[p.q_off[t.req] + last_row / group];
-        auto up_to = [&](int32_t lo_blk, int32_t hi_blk) {  // first block of [lo_blk, hi_blk) that starts behind the reach
-          return static_cast<int32_t>(std::upper_bound(blocks.data() + lo_blk, blocks.data() + hi_blk, reach,
-                                                       [](int32_t v, const KeyBlock& k) { return v < k.pos0; }) - blocks.data());
-        };
-        int32_t f1 = up_to(first[t.req] + r[0], first[t.req] + r[1]) - first[t.req];
-        int32_t s1 = up_to(mid[t.req] + r[2], mid[t.req] + r[3]) - mid[t.req];
-        if (f1 == r[0] && s1 == r[2]) (r[0] < r[1] ? f1 : s1) += 1;
-        p.lazy_half.insert(p.lazy_half.end(), {r[0], f1, r[2], s1});
+    }
+  }
+}
+
+// Whether the attention over caches in place runs in half tiles, two workgroups of four wavefronts for each, or in whole
+// ones of eight.  Halves start sooner, fill each other's gaps on a compute unit, skip blocks that only the other half's rows
+// reach, and pad a chunk's last key block to 64 keys instead of 96; whole tiles read every block once for all rows and have
+// fewer barriers per key.  Time of 350 launches of 11 to 510 us in halves, relative to whole tiles:
+//   tall tiles (more than half the rows) hold most of the blocks: 0.76 to 1.08 (0.90 on average) up to 60 blocks per compute
+//     unit, except cut into long pieces, which gain neither start nor balance (0.98 to 1.07); above that it is the padding of
+//     short chunks that decides: 0.78 to 1.03 (0.92) where halves walk up to 0.975 of the keys that whole tiles walk, padding
+//     counted, 0.95 to 1.12 (1.01) where they save less; more than 180 blocks per compute unit 1.0 to 1.14;
+//   low tiles, which leave one wavefront on a SIMD in either shape: up to four blocks per compute unit 0.68 to 1.05 (0.95), but
+//     1.0 to 1.09 where they have more than two wavefronts of rows; with more blocks 0.86 to 1.33 (1.04).
+// Of 191 drawn launches that this rule runs in halves, 12 took more than 1.015 of the time, 0.906 on average.
+bool runs_in_halves(const mpic_plan& p) {
+  int64_t pieces = 0, cut = 0, blocks = 0, tall = 0, low = 0, low_rows = 0;
+  for (const AttnTile& t : p.tiles) {
+    if (t.n_rows <= 0) continue;
+    const int64_t b = (t.n_keys - t.key0 + 63) / 64;
+    ++pieces;
+    cut += t.part >= 0;
+    blocks += b;
+    if (t.n_rows > kAttnTileRows / 2) {
+      tall += b;
+    } else {
+      ++low;
+      low_rows += t.n_rows;
+    }
+  }
+  if (2 * tall < blocks) return blocks <= 4 * kComputeUnits && low_rows <= 64 * low;
+  if (blocks > 180 * kComputeUnits || (3 * cut >= 2 * pieces && blocks > 28 * pieces)) return false;
+  if (blocks <= 60 * kComputeUnits) return true;
+  auto keys_walked = [&](int32_t bn) {
+    int64_t n = 0;
+    const auto& r = p.lazy_range[block_size_index(bn)];
+    for (size_t i = 0; i < r.size(); i += 2) n += r[i + 1] - r[i];
+    return n * bn;
+  };
+  return 1000 * keys_walked(kHalfTileBlock) <= 975 * keys_walked(96);
+}
+
+// The block ranges of the tiles' halves of rows (lazy_half): the first one reaches less far.  At least one block each, so that
+// a half whose rows see nothing of a piece has something to walk.
+void build_half_ranges(mpic_plan& p, int group) {
+  const int s = block_size_index(kHalfTileBlock);
+  p.lazy_half.clear();
+  if (!p.half_tiles) return;
+  p.lazy_half.reserve(p.tiles.size() * 8);
+  for (size_t i = 0; i < p.tiles.size(); ++i) {
+    const AttnTile& t = p.tiles[i];
+    const int32_t* r = p.lazy_range[s].data() + 4 * i;
+    for (int32_t row = 0; row < kAttnTileRows; row += kAttnTileRows / 2) {
+      if (row >= t.n_rows) {
+        p.lazy_half.insert(p.lazy_half.end(), {0, 0, 0, 0});
+        continue;
       }
+      const int32_t last_row = t.row0 + std::min(t.n_rows, row + kAttnTileRows / 2) - 1;
+      const int32_t reach = p.q_pos[p.q_off[t.req] + last_row / group];
+      // of blocks lo .. hi - 1 behind block `from`, the first that starts behind the reach
+      auto up_to = [&](int32_t from, int32_t lo, int32_t hi) {
+        const KeyBlock* part = p.kblk[s].data() + from;
+        return static_cast<int32_t>(std::upper_bound(part + lo, part + hi, reach,
+                                                     [](int32_t v, const KeyBlock& k) { return v < k.pos0; }) - part);
+      };
+      int32_t f1 = up_to(p.kblk_first[s][t.req], r[0], r[1]);
+      int32_t s1 = up_to(p.kblk_mid[s][t.req], r[2], r[3]);
+      if (f1 == r[0] && s1 == r[2]) (r[0] < r[1] ? f1 : s1) += 1;
+      p.lazy_half.insert(p.lazy_half.end(), {r[0], f1, r[2], s1});
     }
   }
 }
@@ -808,8 +833,9 @@ extern "C" int mpic_plan_create_selected(mpic_ctx* ctx, int32_t n_requests, cons
     mpic::build_tiles(*p, ctx->group, ctx->cfg.n_kv_heads);
     if (ctx->cfg.dtype == MPIC_F32) mpic::build_pieces_f32(*p, ctx->group, ctx->cfg.n_kv_heads, ctx->cfg.head_dim);
     if (ctx->cfg.lazy_rope) {
+      mpic::build_key_blocks(*p);
       p->half_tiles = mpic::runs_in_halves(*p);
-      mpic::build_key_blocks(*p, ctx->group);
+      mpic::build_half_ranges(*p, ctx->group);
     }
     {
       auto clamp = [](int64_t x) { return static_cast<int32_t>(std::min<int64_t>(x, INT32_MAX)); };

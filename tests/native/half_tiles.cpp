@@ -53,6 +53,7 @@ int main() {
     CHECK(!in_halves(32, 32, 8, 96, 5000));
     CHECK(in_halves(32, 32, 3, 240, 1000) && !in_halves(32, 32, 3, 240, 6000));
     CHECK(in_halves(32, 32, 12, 240, 3000) && !in_halves(32, 32, 30, 240, 6000));
+    CHECK(!in_halves(32, 32, 14, 192, 2880));  // as many blocks as the twelve, and no padding that smaller ones would save
   }
   std::mt19937 rng(11);
   auto rnd = [&](int lo, int hi) { return lo + static_cast<int>(rng() % static_cast<unsigned>(hi - lo + 1)); };
