@@ -61,7 +61,8 @@ const char* hipGetErrorString(hipError_t) { return "stub"; }
 namespace mpic {
 AttnArgs last_attn;
 DecodeArgs last_decode;
-hipError_t launch_assemble(int, const AssembleArgs&, const AssembleSrcTable&, hipStream_t) { return hipSuccess; }
+AssembleArgs last_assemble;
+hipError_t launch_assemble(int, const AssembleArgs& a, const AssembleSrcTable&, hipStream_t) { last_assemble = a; return hipSuccess; }
 hipError_t launch_attn_bf16(const AttnArgs& a, const AssembleArgs*, const AssembleSrcTable*, const LazyRefs*, hipStream_t) {
   last_attn = a;
   return hipSuccess;
@@ -261,6 +262,25 @@ int main() {
     mpic_plan_destroy(p);
     mpic_plan_destroy(q);
     mpic_destroy(c);
+    CHECK(in_use == 0);
+  }
+  {  // the linking kernel is told how far its contexts reach, except from 4 GiB on, which offsets of 32 bits do not cover
+    for (const int dtype : {MPIC_BF16, MPIC_F32})
+      for (const int past : {0, 1}) {
+        mpic_config cfg{8, 8, 128, dtype, 1e4, 0, 16, 0, 0};
+        mpic_ctx* c = nullptr;
+        CHECK(mpic_create(&c, &cfg) == MPIC_OK);
+        const int64_t row = dtype == MPIC_F32 ? 4096 : 2048, pages = (int64_t{1} << 32) / row / 16 - 1 + past;
+        const int32_t seg_off[2] = {0, 1}, table_off[2] = {0, 1}, table[1] = {static_cast<int32_t>(pages - 1)};
+        mpic_segment seg{};
+        seg.len = 16;
+        mpic_plan* p = nullptr;
+        CHECK(mpic_plan_create(c, 1, seg_off, &seg, 0, table, table_off, pages, &p) == MPIC_OK);
+        CHECK(mpic_assemble_kv(c, p, nullptr, 0, any, any, p->n_q, any, any, pages * 16, &s[0]) == MPIC_OK);
+        CHECK(mpic::last_assemble.ctx_bytes == (past ? 0 : pages * 16 * row));
+        mpic_plan_destroy(p);
+        mpic_destroy(c);
+      }
     CHECK(in_use == 0);
   }
   std::puts("scratch ok");
