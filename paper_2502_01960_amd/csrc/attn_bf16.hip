@@ -41,7 +41,7 @@ constexpr int ROW_BYTES = D * 2;  // one staged key or value row
 
 // Keys per LDS block, wavefronts per workgroup and what follows from them.  Three shapes are built, two of eight
 // wavefronts and one of four:
-//   64 keys: K and V rings of four slots (128 KB), loads two blocks ahead, 202 registers -- leaves
+//   64 keys: K and V rings of four slots (128 KB), loads two blocks ahead, 206 registers -- leaves
 //            room on every SIMD for a wave of another kernel (linking on a second stream);
 //   96 keys: K ring of two slots, V ring of three (120 KB), loads one block ahead, 238 registers --
 //            a third fewer barriers and phase changes per key, 1 to 2.6 % faster alone, but nothing
